@@ -210,21 +210,22 @@ __device__ inline void small_sylvester(int p, int q, const T (&A)[2][2], const T
   }
 }
 
-// Diagonal block structure of the LDS tile X[col][row] of order mm: block
-// starts in bs[0..nb], block index of every row in blk[].  A 2x2 block starts
-// at i when X(i+1, i) != 0.  Thread 0 only; the caller synchronises.
+// Diagonal block structure of the LDS tile X[col][row] of order mm: block b
+// starts at bs[b] & 0xff and has bs[b] >> 8 rows, blk[i] is the block of row
+// i.  Row i is the second row of a 2x2 block when X(i, i-1) != 0.  Called by
+// one whole wave; returns the number of blocks in every lane of it.
 template <typename T>
 __device__ inline int tile_blocks(const T (*X)[kQb + 1], int mm, int* bs, int* blk) {
-  int nb = 0;
-  for (int i = 0; i < mm;) {
-    bs[nb] = i;
-    const int sz = (i + 1 < mm && X[i][i + 1] != T(0)) ? 2 : 1;
-    for (int k = 0; k < sz; ++k) blk[i + k] = nb;
-    ++nb;
-    i += sz;
+  const int i = threadIdx.x % kWave;
+  const bool start = i < mm && (i == 0 || X[i - 1][i] == T(0));
+  const unsigned mask = (unsigned)__ballot(start);
+  if (i < mm) {
+    const int b = __popc(mask & (~0u >> (31 - i))) - 1;
+    const bool two = i + 1 < mm && !((mask >> (i + 1)) & 1u);
+    blk[i] = b;
+    if (start) bs[b] = i | ((two ? 2 : 1) << 8);
   }
-  bs[nb] = mm;
-  return nb;
+  return __popc(mask);
 }
 
 template <typename T>
@@ -232,9 +233,10 @@ __global__ __launch_bounds__(kQThreads) void qtile_kernel(QTileArgs a, const T* 
   __shared__ T ABs[4][kQb][kQb + 1];  // As = ABs[0], Bs = ABs[1]; products overlay all four
   T (*As)[kQb + 1] = ABs[0];
   T (*Bs)[kQb + 1] = ABs[1];
+  __shared__ T Ad[kQb][kQb + 1], Bd[kQb][kQb + 1];  // the diagonal tiles S_II and S2_JJ
   __shared__ T Ys[kQb][kQb + 1];
   __shared__ T Cs[kQb][kQb + 1];
-  __shared__ int rbs[kQb + 1], cbs[kQb + 1], rblk[kQb], cblk[kQb];
+  __shared__ int rbs[kQb], cbs[kQb], rblk[kQb], cblk[kQb];
   __shared__ int sh_nrb, sh_ncb, sh_tk;
   const int t = threadIdx.x;
   const int ti = t % kQb, tj0 = t / kQb;  // owned entries (ti, tj0 + 8 q)
@@ -278,11 +280,11 @@ __global__ __launch_bounds__(kQThreads) void qtile_kernel(QTileArgs a, const T* 
     for (int q = 0; q < 4; ++q) Ys[tj0 + 8 * q][ti] = acc[q];
     for (int x = t; x < kQb * kQb; x += blockDim.x) As[x / kQb][x % kQb] = T(0);
     __syncthreads();
-    if (t == 0) sh_nrb = tile_blocks<T>(Ys, mi, rbs, rblk);
+    if (wave == 0) sh_nrb = tile_blocks<T>(Ys, mi, rbs, rblk);
     __syncthreads();
     const int nb = sh_nrb;
     if (t < nb) {
-      const int i0 = rbs[t], sz = rbs[t + 1] - i0;
+      const int i0 = rbs[t] & 0xff, sz = rbs[t] >> 8;
       const T eps = qeps<T>();
       if (sz == 1) {
         const T d = Ys[i0][i0];
@@ -310,8 +312,8 @@ __global__ __launch_bounds__(kQThreads) void qtile_kernel(QTileArgs a, const T* 
     for (int d = 1; d < nb; ++d) {
       if (t < nb - d) {
         const int bi = t, bj = t + d;
-        const int i0 = rbs[bi], p = rbs[bi + 1] - i0, j0 = rbs[bj], q = rbs[bj + 1] - j0;
-        const int klo = rbs[bi + 1];
+        const int i0 = rbs[bi] & 0xff, p = rbs[bi] >> 8, j0 = rbs[bj] & 0xff, q = rbs[bj] >> 8;
+        const int klo = i0 + p;
         T Cv[4], Yv[4], Am[2][2], Bm[2][2];
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
@@ -344,6 +346,53 @@ __global__ __launch_bounds__(kQThreads) void qtile_kernel(QTileArgs a, const T* 
       if (i < mi && j < mj) qstore_c(X, a.ldx, r0 + i, c0 + j, As[j][i]);
     }
   } else {
+    // What the tile's own equation needs besides its right-hand side is
+    // prepared first, while the tiles it waits for are still being computed:
+    // the diagonal tiles, their block structure, and for every owned entry
+    // its row of the inverse of the block equation's Kronecker matrix (the
+    // solution of the transposed equation for a unit right-hand side).
+    if (a.mode == 0) {
+      qwait_tile(a, I, I);
+      qwait_tile(a, J, J);
+      qload_tile(Ad, X, a.ldx, r0, r0, mi, mi, true);
+      qload_tile(Bd, X, a.ldx, c0, c0, mj, mj, true);
+    } else {
+      qload_tile(Ad, A, a.lda, r0, r0, mi, mi, false);
+      qload_tile(Bd, B, a.ldb, c0, c0, mj, mj, false);
+    }
+    __syncthreads();
+    if (wave == 0) sh_nrb = tile_blocks<T>(Ad, mi, rbs, rblk);
+    if (wave == 1) sh_ncb = tile_blocks<T>(Bd, mj, cbs, cblk);
+    __syncthreads();
+    const int nrb = sh_nrb, ncb = sh_ncb;
+    T coef[4][4];   // entry (ti, tj0 + 8 q): Y = sum_v coef[v] C(i0 + v % 2, j0 + v / 2)
+    int ed[4];      // block anti-diagonal of the entry (-1: outside the tile)
+    int src[4][4];  // C(i0 + v % 2, j0 + v / 2) as an offset into Cs
+    const int ib = ti < mi ? rblk[ti] : 0;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int j = tj0 + 8 * q;
+      ed[q] = -1;
+      if (ti < mi && j < mj) {
+        const int jb = cblk[j];
+        const int i0 = rbs[ib] & 0xff, pr = rbs[ib] >> 8, j0 = cbs[jb] & 0xff, qc = cbs[jb] >> 8;
+        T At[2][2], Bt[2][2], ev[4];
+#pragma unroll
+        for (int r = 0; r < 2; ++r)
+#pragma unroll
+          for (int c = 0; c < 2; ++c) {
+            At[c][r] = (r < pr && c < pr) ? Ad[i0 + c][i0 + r] : T(0);
+            Bt[c][r] = (r < qc && c < qc) ? Bd[j0 + c][j0 + r] : T(0);
+          }
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+          ev[v] = v == (ti - i0) + 2 * (j - j0) ? T(1) : T(0);
+          src[q][v] = (j0 + ((v >> 1) < qc ? v >> 1 : 0)) * (kQb + 1) + i0 + ((v & 1) < pr ? v & 1 : 0);
+        }
+        small_sylvester<T>(pr, qc, At, Bt, ev, coef[q]);
+        ed[q] = (nrb - 1 - ib) + jb;
+      }
+    }
     if (a.mode == 0) {
       // U_IK U_KJ is ready once tiles (I, K) and (K, J) are: K from the
       // middle outwards
@@ -359,10 +408,6 @@ __global__ __launch_bounds__(kQThreads) void qtile_kernel(QTileArgs a, const T* 
         qload_tile(Bs, X, a.ldx, k0, c0, mk, mj, true);
         subtract();
       }
-      qwait_tile(a, I, I);
-      qwait_tile(a, J, J);
-      qload_tile(As, X, a.ldx, r0, r0, mi, mi, true);
-      qload_tile(Bs, X, a.ldx, c0, c0, mj, mj, true);
     } else {
       // column terms S_IK Y_KJ (K > I) and row terms Y_IK S2_KJ (K < J),
       // taken merged in order of readiness
@@ -372,72 +417,56 @@ __global__ __launch_bounds__(kQThreads) void qtile_kernel(QTileArgs a, const T* 
         const int dr = kr < J ? a.mt - 1 - I + kr : 1 << 30;
         if (dc <= dr) {
           const int K = kc--;
-          qwait_tile(a, K, J);
           const int k0 = a.rb[K], mk = a.rb[K + 1] - k0;
           qload_tile(As, A, a.lda, r0, k0, mi, mk, false);
+          qwait_tile(a, K, J);
           qload_tile(Bs, X, a.ldx, k0, c0, mk, mj, true);
         } else {
           const int K = kr++;
-          qwait_tile(a, I, K);
           const int k0 = a.cb[K], mk = a.cb[K + 1] - k0;
-          qload_tile(As, X, a.ldx, r0, k0, mi, mk, true);
           qload_tile(Bs, B, a.ldb, k0, c0, mk, mj, false);
+          qwait_tile(a, I, K);
+          qload_tile(As, X, a.ldx, r0, k0, mi, mk, true);
         }
         subtract();
       }
-      qload_tile(As, A, a.lda, r0, r0, mi, mi, false);
-      qload_tile(Bs, B, a.ldb, c0, c0, mj, mj, false);
     }
 #pragma unroll
     for (int q = 0; q < 4; ++q) Cs[tj0 + 8 * q][ti] = acc[q];
     __syncthreads();
-    if (t == 0) sh_nrb = tile_blocks<T>(As, mi, rbs, rblk);
-    if (t == kWave) sh_ncb = tile_blocks<T>(Bs, mj, cbs, cblk);
-    __syncthreads();
-    const int nrb = sh_nrb, ncb = sh_ncb;
-    // S_II Y + Y S2_JJ = C by block anti-diagonals e = (nrb - 1 - ib) + jb
+    // S_II Y + Y S2_JJ = C by block anti-diagonals e = (nrb - 1 - ib) + jb:
+    // the blocks of e from their right-hand sides, then every later entry
+    // takes the two blocks of e it depends on.  Entries stay in registers;
+    // those of the next anti-diagonal go back to Cs.  (With the block
+    // equations eliminated on the spot a tile's solve took 58 us of a
+    // wavefront's 65.)
     const int ne = nrb + ncb - 1;
     for (int e = 0; e < ne; ++e) {
-      const int jlo = max(0, e - (nrb - 1)), jhi = min(ncb - 1, e);
-      if (t <= jhi - jlo) {
-        const int jb = jlo + t, ib = nrb - 1 - e + jb;
-        const int i0 = rbs[ib], p = rbs[ib + 1] - i0, j0 = cbs[jb], q = cbs[jb + 1] - j0;
-        T Cv[4], Yv[4], Am[2][2], Bm[2][2];
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
-          const int r = u & 1, c = u >> 1;
-          Cv[u] = (r < p && c < q) ? Cs[j0 + c][i0 + r] : T(0);
+      for (int q = 0; q < 4; ++q)
+        if (ed[q] == e) {
+          const T* c = &Cs[0][0];
+          Ys[tj0 + 8 * q][ti] = (coef[q][0] * c[src[q][0]] + coef[q][1] * c[src[q][1]]) +
+                                (coef[q][2] * c[src[q][2]] + coef[q][3] * c[src[q][3]]);
         }
-#pragma unroll
-        for (int r = 0; r < 2; ++r)
-#pragma unroll
-          for (int c = 0; c < 2; ++c) {
-            Am[r][c] = (r < p && c < p) ? As[i0 + c][i0 + r] : T(0);
-            Bm[r][c] = (r < q && c < q) ? Bs[j0 + c][j0 + r] : T(0);
-          }
-        small_sylvester<T>(p, q, Am, Bm, Cv, Yv);
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-          const int r = u & 1, c = u >> 1;
-          if (r < p && c < q) Ys[j0 + c][i0 + r] = Yv[u];
-        }
-      }
       __syncthreads();
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
-        const int j = tj0 + 8 * q;
-        if (ti < mi && j < mj) {
-          const int ib = rblk[ti], jb = cblk[j];
-          if ((nrb - 1 - ib) + jb > e) {
-            T c = Cs[j][ti];
-            const int kb = nrb - 1 - e + jb;  // block (kb, jb) finished on e
-            if (kb > ib && kb < nrb)
-              for (int k = rbs[kb]; k < rbs[kb + 1]; ++k) c -= As[k][ti] * Ys[j][k];
-            const int lb = e - (nrb - 1 - ib);  // block (ib, lb) finished on e
-            if (lb >= 0 && lb < jb)
-              for (int l = cbs[lb]; l < cbs[lb + 1]; ++l) c -= Ys[l][ti] * Bs[j][l];
-            Cs[j][ti] = c;
+        if (ed[q] > e) {
+          const int j = tj0 + 8 * q;
+          const int kb = ib + ed[q] - e;  // block (kb, jb) finished on e
+          if (kb < nrb) {
+            const int k = rbs[kb] & 0xff;
+            acc[q] -= Ad[k][ti] * Ys[j][k];
+            if ((rbs[kb] >> 8) == 2) acc[q] -= Ad[k + 1][ti] * Ys[j][k + 1];
           }
+          const int lb = e - (nrb - 1 - ib);  // block (ib, lb) finished on e
+          if (lb >= 0) {
+            const int l = cbs[lb] & 0xff;
+            acc[q] -= Ys[l][ti] * Bd[j][l];
+            if ((cbs[lb] >> 8) == 2) acc[q] -= Ys[l + 1][ti] * Bd[j][l + 1];
+          }
+          if (ed[q] == e + 1) Cs[j][ti] = acc[q];
         }
       }
       __syncthreads();

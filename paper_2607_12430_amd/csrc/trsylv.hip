@@ -180,6 +180,7 @@ __global__ __launch_bounds__(kTThreads) void tile_kernel(TileArgs a, const T* A,
   cx<T> (*Bs)[kTb + 1] = ABs[1];
   T (*Pp)[kTb][kTb + 1] = reinterpret_cast<T (*)[kTb][kTb + 1]>(&ABs[0][0][0]);
   static_assert(sizeof(ABs) == 4 * kTb * (kTb + 1) * sizeof(T), "product overlay");
+  __shared__ cx<T> Ad[kTb][kTb + 1], Bd[kTb][kTb + 1];  // the diagonal tiles S_II and S2_JJ
   __shared__ cx<T> Ys[kTb][kTb + 1];
   __shared__ int sh_tk;
   const int t = threadIdx.x;
@@ -251,6 +252,29 @@ __global__ __launch_bounds__(kTThreads) void tile_kernel(TileArgs a, const T* A,
         if (i < mi && j < mj) tstore_c(X, a.ldx, kTb * I + i, kTb * J + j, i <= j ? As[j][i] : cx<T>{T(0), T(0)});
       }
     } else {
+      // What the tile's own equation needs besides its right-hand side is
+      // prepared first, while the tiles it waits for are still being
+      // computed: the diagonal tiles and 1 / (s_ii + s_jj) of every owned
+      // entry.
+      if (a.mode == 0) {
+        wait_tile(a, I, I);
+        wait_tile(a, J, J);
+        load_tile(Ad, X, a.ldx, kTb * I, kTb * I, mi, mi, true);
+        load_tile(Bd, X, a.ldx, kTb * J, kTb * J, mj, mj, true);
+      } else {
+        load_tile(Ad, A, a.lda, kTb * I, kTb * I, mi, mi, false);
+        load_tile(Bd, B, a.ldb, kTb * J, kTb * J, mj, mj, false);
+      }
+      __syncthreads();
+      cx<T> inv[4];
+      int ed[4];  // anti-diagonal of the entry (-1: outside the tile)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const int j = tj0 + 8 * q;
+        const bool in = ti < mi && j < mj;
+        ed[q] = in ? (mi - 1 - ti) + j : -1;
+        inv[q] = in ? cdiv(cx<T>{T(1), T(0)}, cadd(Ad[ti][ti], Bd[j][j])) : cx<T>{T(0), T(0)};
+      }
       if (a.mode == 0) {
         // S_IK S_KJ is ready once tiles (I, K) and (K, J) are, i.e. at
         // superdiagonal max(K - I, J - K): take K from the middle outwards
@@ -266,56 +290,49 @@ __global__ __launch_bounds__(kTThreads) void tile_kernel(TileArgs a, const T* A,
           load_tile(Bs, X, a.ldx, kTb * K, kTb * J, mk, mj, true);
           subtract();
         }
-        wait_tile(a, I, I);
-        wait_tile(a, J, J);
-        load_tile(As, X, a.ldx, kTb * I, kTb * I, mi, mi, true);
-        load_tile(Bs, X, a.ldx, kTb * J, kTb * J, mj, mj, true);
       } else {
         // the column terms S_IK Y_KJ (K > I, ready at wavefront
         // mt-1-K+J) and the row terms Y_IK S2_KJ (K < J, ready at mt-1-I+K)
         // are taken merged in order of readiness, so that only the last two
-        // products remain once the final dependencies arrive
+        // products remain once the final dependencies arrive; the operand
+        // that is an input is loaded before the wait
         int kc = a.mt - 1, kr = 0;
         while (kc > I || kr < J) {
           const int dc = kc > I ? a.mt - 1 - kc + J : 1 << 30;
           const int dr = kr < J ? a.mt - 1 - I + kr : 1 << 30;
           if (dc <= dr) {
             const int K = kc--;
-            wait_tile(a, K, J);
             const int mk = min(kTb, a.m - kTb * K);
             load_tile(As, A, a.lda, kTb * I, kTb * K, mi, mk, false);
+            wait_tile(a, K, J);
             load_tile(Bs, X, a.ldx, kTb * K, kTb * J, mk, mj, true);
           } else {
             const int K = kr++;
-            wait_tile(a, I, K);
             const int mk = min(kTb, a.p - kTb * K);
-            load_tile(As, X, a.ldx, kTb * I, kTb * K, mi, mk, true);
             load_tile(Bs, B, a.ldb, kTb * K, kTb * J, mk, mj, false);
+            wait_tile(a, I, K);
+            load_tile(As, X, a.ldx, kTb * I, kTb * K, mi, mk, true);
           }
           subtract();
         }
-        load_tile(As, A, a.lda, kTb * I, kTb * I, mi, mi, false);
-        load_tile(Bs, B, a.ldb, kTb * J, kTb * J, mj, mj, false);
       }
-      __syncthreads();
-      // S_II Y + Y S2_JJ = acc by anti-diagonals e = (mi - 1 - i) + j
+      // S_II Y + Y S2_JJ = acc by anti-diagonals e = (mi - 1 - i) + j (with a
+      // complex division per entry instead of the prepared reciprocals, and
+      // the diagonal tiles loaded here, a wavefront took 58 us)
       const int ne = mi + mj - 1;
       for (int e = 0; e < ne; ++e) {
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          const int j = tj0 + 8 * q;
-          if (ti < mi && j < mj && (mi - 1 - ti) + j == e)
-            Ys[j][ti] = cdiv(acc[q], cadd(As[ti][ti], Bs[j][j]));
-        }
+        for (int q = 0; q < 4; ++q)
+          if (ed[q] == e) Ys[tj0 + 8 * q][ti] = cmul(acc[q], inv[q]);
         __syncthreads();
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
-          const int j = tj0 + 8 * q;
-          if (ti < mi && j < mj && (mi - 1 - ti) + j > e) {
+          if (ed[q] > e) {
+            const int j = tj0 + 8 * q;
             const int k = mi - 1 - e + j;  // (k, j) on wavefront e
-            if (k > ti && k < mi) acc[q] = csub(acc[q], cmul(As[k][ti], Ys[j][k]));
+            if (k < mi) acc[q] = csub(acc[q], cmul(Ad[k][ti], Ys[j][k]));
             const int k2 = e - (mi - 1 - ti);  // (ti, k2) on wavefront e
-            if (k2 >= 0 && k2 < j) acc[q] = csub(acc[q], cmul(Ys[k2][ti], Bs[j][k2]));
+            if (k2 >= 0) acc[q] = csub(acc[q], cmul(Ys[k2][ti], Bd[j][k2]));
           }
         }
       }
