@@ -61,29 +61,4 @@ __device__ inline cx<T> csqrt_principal(cx<T> z) {
   return {fabs(z.i) / (T(2) * t), copysign(t, z.i)};
 }
 
-// A complex matrix as two real planes with a common leading dimension.
-template <typename T>
-struct CMat {
-  T* re;
-  T* im;
-  int64_t ld;
-};
-template <typename T>
-inline CMat<T> stacked(T* base, int64_t m, int64_t ld) { return {base, base + m, ld}; }
-template <typename T>
-inline CMat<T> sub(CMat<T> a, int64_t i, int64_t j) {
-  return {a.re + i + j * a.ld, a.im ? a.im + i + j * a.ld : nullptr, a.ld};
-}
-
-// C = alpha op(A) op(B) + beta C  (op: 'N', 'T' transpose, 'C' conjugate
-// transpose); four real GEMMs over the planes.  A.im or B.im may be NULL for
-// real operands.
-template <typename T>
-void cgemm(hipStream_t st, char opA, char opB, int M, int N, int K, CMat<T> A, CMat<T> B,
-           T alpha, T beta, CMat<T> C);
-
-// Elementwise helpers (general.hip).
-template <typename T>
-void launch_cset_identity(hipStream_t st, int n, CMat<T> A);
-
 }  // namespace msqrt

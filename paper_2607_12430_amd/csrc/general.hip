@@ -398,6 +398,7 @@ msqrt_status factor_general(Factor* f, const double* A, int64_t lda, int cplx, h
   HseqrWork hw;
   // ||H||_F = ||A||_F / 4^k (unitary similarity)
   const bool ok = hseqr<T>(st, n, H, Q, hw, (T)f->anorm_scaled[0]);
+  gehrd_check(st, gw);
   if (!ok) {
     if (tm) tm->end();
     set_last_error("complex Schur QR did not converge");
@@ -576,6 +577,7 @@ msqrt_status factor_root3(Factor* f, const double* A, int64_t lda, int cplx, hip
   if (tm) tm->begin(MSQRT_T_EIG);
   HseqrWork hw;
   const bool ok = hseqr<T>(st, n, H, Q, hw, (T)f->anorm_scaled[0]);
+  gehrd_check(st, gw);
   if (!ok) {
     if (tm) tm->end();
     set_last_error("complex Schur QR did not converge");
@@ -885,6 +887,7 @@ msqrt_status factor_real(Factor* f, const double* A, int64_t lda, hipStream_t st
   if (tm) tm->begin(MSQRT_T_EIG);
   HseqrWork hw;
   const bool ok = rhseqr<T>(st, n, H, Q, hw, (T)f->anorm_scaled[0]);
+  gehrd_check(st, gw);
   if (!ok) {
     if (tm) tm->end();
     set_last_error("real Schur QR did not converge");

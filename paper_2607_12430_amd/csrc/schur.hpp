@@ -10,7 +10,8 @@
 namespace msqrt {
 
 struct GehrdWork {
-  DevBuf V, Tall, Y, W, W2, part, VT;
+  DevBuf V, Tall, Y, W, W2, part, bar;
+  int nbar = 0;  // 1 once a reduction has used the grid barrier state
 };
 
 // H (stacked, n x n) is reduced in place to upper Hessenberg form
@@ -23,6 +24,10 @@ void gehrd(hipStream_t st, int n, T* H, T* Z, GehrdWork& w);
 // Q1 formed in Z (n x n, ld n).
 template <typename T>
 void gehrd_real(hipStream_t st, int n, T* H, T* Z, GehrdWork& w);
+
+// Throws if a grid barrier of the reductions that used w timed out (waits for
+// the stream).
+void gehrd_check(hipStream_t st, GehrdWork& w);
 
 struct HseqrWork {
   DevBuf U, shifts, flag, scratch;

@@ -24,6 +24,7 @@
 #include <vector>
 
 #include "gemm.hpp"
+#include "gridsync.hpp"
 #include "kernels.hpp"
 #include "profile.hpp"
 #include "tridiag.hpp"
@@ -32,7 +33,7 @@ namespace msqrt {
 
 namespace {
 
-constexpr int kThreads = 1024;
+constexpr int kThreads = kSyncThreads;
 constexpr int kMaxTs = 192;  // max tile size handled by one workgroup
 constexpr int kTRMax = 22;   // max tiles per dimension: 253 workgroups, one per CU
 constexpr int kGMax = kTRMax * (kTRMax + 1) / 2;
@@ -43,161 +44,6 @@ constexpr int kNbMax = 32;
 constexpr int kPivT = 256;
 constexpr int kKT = 512;
 static_assert(kMaxTs <= kPivT && kPivT + kNbMax <= kKT && kKT + kMaxTs <= 1024, "thread ranges");
-
-// Values exchanged between workgroups inside a launch (partial products and
-// sums) are written and read with agent-scope atomic stores and loads, which
-// are coherent across the XCDs' L2 caches, so the barrier needs no device-wide
-// fence: such a fence writes back and invalidates the whole L2 of every XCD
-// on every column, and the tiles cached there would be fetched again.
-template <typename T>
-__device__ inline void cstore(T* p, T v) {
-  __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-template <typename T>
-__device__ inline T cload(const T* p) {
-  return __hip_atomic_load(const_cast<T*>(p), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-
-// Wavefront sum by DPP: butterflies inside every row of 16 lanes (two quad
-// permutations, the half-row mirror, the row mirror) leave each lane with
-// its row's sum; the four row sums are then read with readlane.  Every lane
-// gets the total (in a fixed order, so results are reproducible).  All 64
-// lanes must be active: every call site in this file is reached by whole
-// wavefronts.
-template <int CTRL>
-__device__ inline int dpp_i(int v) {
-  return __builtin_amdgcn_update_dpp(0, v, CTRL, 0xF, 0xF, false);
-}
-template <int CTRL>
-__device__ inline float dpp_v(float v) {
-  return __int_as_float(dpp_i<CTRL>(__float_as_int(v)));
-}
-template <int CTRL>
-__device__ inline double dpp_v(double v) {
-  const long long b = __double_as_longlong(v);
-  const int lo = dpp_i<CTRL>((int)b), hi = dpp_i<CTRL>((int)(b >> 32));
-  return __longlong_as_double(((long long)hi << 32) | (unsigned)lo);
-}
-__device__ inline float lane_of(float v, int l) {
-  return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), l));
-}
-__device__ inline double lane_of(double v, int l) {
-  const long long b = __double_as_longlong(v);
-  const int lo = __builtin_amdgcn_readlane((int)b, l), hi = __builtin_amdgcn_readlane((int)(b >> 32), l);
-  return __longlong_as_double(((long long)hi << 32) | (unsigned)lo);
-}
-// Sum over each row of 16 lanes, left in every lane of the row.
-template <typename V>
-__device__ inline V rsum16(V v) {
-  v += dpp_v<0xB1>(v);
-  v += dpp_v<0x4E>(v);
-  v += dpp_v<0x141>(v);
-  v += dpp_v<0x140>(v);
-  return v;
-}
-// Sum over each group of 8 lanes (half a row), left in every lane of it.
-template <typename V>
-__device__ inline V hsum8(V v) {
-  v += dpp_v<0xB1>(v);
-  v += dpp_v<0x4E>(v);
-  v += dpp_v<0x141>(v);
-  return v;
-}
-template <typename V>
-__device__ inline V wsum(V v) {
-  v += dpp_v<0xB1>(v);   // quad_perm [1, 0, 3, 2]
-  v += dpp_v<0x4E>(v);   // quad_perm [2, 3, 0, 1]
-  v += dpp_v<0x141>(v);  // row_half_mirror
-  v += dpp_v<0x140>(v);  // row_mirror
-  return (lane_of(v, 0) + lane_of(v, 16)) + (lane_of(v, 32) + lane_of(v, 48));
-}
-
-// Grid barrier state of one batch entry (unsigned words): the top counter,
-// the sticky failure flag, the release word and 8 group counters, each on a
-// 256-byte line of its own.
-constexpr int kBarTop = 0, kBarFail = 1, kBarRel = 64, kBarSub = 128, kBarSubStride = 64;
-
-// Counter values at the start of a launch.  All counters only grow within one
-// reduction, so a barrier needs no reset: the host adds what every launch
-// contributes.
-struct BarrierBase {
-  unsigned gen;     // release word: barriers completed
-  unsigned top;     // top counter
-  unsigned sub[8];  // group counters
-};
-
-// Two-level grid barrier, split into arrival and wait so that a workgroup
-// can do work that needs no other workgroup's results while the barrier
-// completes.  The G workgroups of a batch entry form 8 groups (workgroup
-// index mod 8, which is the XCD a workgroup is dispatched to when the entry
-// starts on a multiple of 8); a workgroup adds 1 to its group's counter, the
-// group's last arrival (known from the value its add returns) adds 1 to the
-// top counter, and the last arrival there writes the barrier's generation
-// number to the release word, which the other workgroups poll.  Spreading the
-// arrivals over 8 counters halves the cost of a barrier of 253 workgroups
-// against one shared counter.  Every thread waits for its own coherent
-// stores to complete before the workgroup arrives.  The counters are handled
-// by the first lane of the last wave (kBarT), which has no row work, so the
-// atomics' round trips hold up no thread that has.  A spin limit keeps a
-// broken launch from hanging: it raises the sticky failure flag.
-constexpr int kBarT = kThreads - kWave;
-
-// Arrival; returns true in thread kBarT if this workgroup released barrier k.
-__device__ inline bool grid_arrive(unsigned* bar, const BarrierBase& base, unsigned sub_base, int blk,
-                                   int G, int k) {
-  __builtin_amdgcn_s_waitcnt(0);
-  __syncthreads();
-  // A launch of one workgroup per batch entry synchronises with itself only:
-  // the wait above and the workgroup barrier make its stores visible to its
-  // own later loads.  (The trailing order only shrinks, so every later launch
-  // of the reduction has G = 1 too and no counter is read again.)
-  if (G == 1) return true;
-  bool released = false;
-  if (threadIdx.x == kBarT) {
-    const unsigned g = (unsigned)blk & 7u;
-    const unsigned gsz = (unsigned)G / 8u + (g < ((unsigned)G & 7u) ? 1u : 0u);
-    const unsigned ng = G < 8 ? (unsigned)G : 8u;
-    // with G <= 8 every group has one member, which is always its group's
-    // last arrival: its counter is skipped (later launches of the reduction
-    // have G <= 8 too, so the group counters are not read again)
-    const unsigned old =
-        G <= 8 ? sub_base + gsz * (unsigned)k - 1u
-               : __hip_atomic_fetch_add(&bar[kBarSub + kBarSubStride * g], 1u, __ATOMIC_RELAXED,
-                                        __HIP_MEMORY_SCOPE_AGENT);
-    if (old + 1u == sub_base + gsz * (unsigned)k) {
-      const unsigned o2 = __hip_atomic_fetch_add(&bar[kBarTop], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      if (o2 + 1u == base.top + ng * (unsigned)k) {
-        cstore(&bar[kBarRel], base.gen + (unsigned)k);
-        released = true;
-      }
-    }
-  }
-  return released;
-}
-
-// Wait for barrier k (released: what grid_arrive returned).
-__device__ inline void grid_wait(unsigned* bar, const BarrierBase& base, int k, bool released) {
-  if (threadIdx.x == kBarT && !released) {
-    const unsigned gen = base.gen + (unsigned)k;
-    unsigned spins = 0;
-    while (cload(&bar[kBarRel]) < gen) {
-      __builtin_amdgcn_s_sleep(1);
-      if ((++spins & 255u) == 0u) {
-        if (cload(&bar[kBarFail]) != 0u) break;
-        if (spins > (1u << 24)) {
-          cstore(&bar[kBarFail], 1u);
-          break;
-        }
-      }
-    }
-  }
-  __syncthreads();
-}
-
-__device__ inline void grid_barrier(unsigned* bar, const BarrierBase& base, unsigned sub_base, int blk,
-                                    int G, int k) {
-  grid_wait(bar, base, k, grid_arrive(bar, base, sub_base, blk, G, k));
-}
 
 template <typename T>
 struct PanelArgs {
@@ -939,7 +785,7 @@ void sytrd_batched(hipStream_t st, int n, int batch, T* A, int64_t sA, T* d, T* 
     attr_set[sizeof(T) == 8] = true;
   }
   const int64_t sVW = (int64_t)n * 2 * kNbMax, sYP = (int64_t)2 * kTRMax * n,
-                sSP = (int64_t)2 * kGMax * 4, sVP = (int64_t)2 * kTRMax * 2 * kNbMax, sBar = 32 * 40;
+                sSP = (int64_t)2 * kGMax * 4, sVP = (int64_t)2 * kTRMax * 2 * kNbMax, sBar = kBarWords;
   T* VW = w.VW.ensure<T>(sVW * batch);
   T* WV = w.WV.ensure<T>(sVW * batch);
   T* ypart = w.ypart.ensure<T>(sYP * batch);
@@ -1020,10 +866,10 @@ void sytrd(hipStream_t st, int n, T* A, T* d, T* e, T* tau, SytrdWork& w) {
 
 bool sytrd_failed(SytrdWork& w) {
   if (!w.bar.p || w.nbar <= 0) return false;
-  std::vector<unsigned> flags((size_t)32 * 40 * w.nbar);
+  std::vector<unsigned> flags((size_t)kBarWords * w.nbar);
   MSQRT_HIP(hipMemcpy(flags.data(), w.bar.p, sizeof(unsigned) * flags.size(), hipMemcpyDeviceToHost));
   for (int b = 0; b < w.nbar; ++b)
-    if (flags[(size_t)b * 32 * 40 + kBarFail]) return true;
+    if (flags[(size_t)b * kBarWords + kBarFail]) return true;
   return false;
 }
 

@@ -52,6 +52,7 @@ msqrt_status gehrd_impl(int n, const double* A, double* H, double* Q, bool schur
   T* dQ = qb.ensure<T>(2 * (int64_t)n * n);
   GehrdWork gw;
   gehrd<T>(nullptr, n, dH, dQ, gw);
+  gehrd_check(nullptr, gw);
   if (schur) {
     HseqrWork hw;
     double fro = 0.0;
