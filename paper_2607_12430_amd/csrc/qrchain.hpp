@@ -19,14 +19,14 @@
 //    row per round: bulge j applies its reflector at position kbase - SPAN j
 //    + r in round r.  The reflectors of a round act on disjoint rows and none
 //    changes an entry another one is formed from, so all row operations run
-//    together, then all column operations.  One wave owns a bulge's rows and
-//    columns of H, another its columns of U, where two of the three columns
-//    of a step are already in registers from the step before.
+//    together, then all column operations.  A wave owns a bulge; of the columns
+//    of U that it changes all but one are in registers from the round before.
 //  * Blocks of at most W rows are left until the end and finished side by
 //    side, one workgroup each, with the same rounds in LDS (qr_small_kernel).
 //
-// What bounds it: latency of one round (LDS round trips, the reflector's
-// serial arithmetic, two workgroup barriers) times the rounds of a batch.
+// What bounds it: the instructions of a round (16 waves, four to a SIMD) times
+// the rounds of a batch; 16 bulges on 128 rows cost 69 us for 79 rows, eight
+// 60 us for 103, so long chains win although their windows advance less.
 #pragma once
 
 #include <algorithm>
@@ -40,8 +40,15 @@ namespace msqrt {
 namespace qr {
 
 constexpr int kThreads = 1024;
-constexpr int kNb = 8;       // bulges per chain: waves 0..7 their H, 8..15 their U
-constexpr int kMaxChains = 12;
+constexpr int kNb = kThreads / kWave;  // bulges per chain, one wave each
+// Bulges of a batch: a sixth of the active block (a third with single shifts),
+// at most kMaxBatch.  A longer batch fills the pipeline of chains better and
+// deflates more per pass; past 192 the eigenvalues of the far 2 x 2 blocks are
+// too poor as shifts (QR phase at n = 2048: 83, 70, 57, 57 ms for 64, 96, 192,
+// 320; complex n = 1024: 54, 51, 42, 42 ms).
+constexpr int kMaxBatch = 192;
+constexpr int kMaxChains = 13;  // kMaxBatch over the smallest chain_bulges()
+constexpr int kPad = 4;      // elements between the H and the U window in LDS
 constexpr int kLag = 2;      // windows between consecutive chains of a batch
 
 template <typename T>
@@ -53,9 +60,9 @@ __device__ inline T tiny_of();
 template <> __device__ inline float tiny_of<float>() { return 1.1754944e-38f; }
 template <> __device__ inline double tiny_of<double>() { return 2.2250738585072014e-308; }
 
-// 1/x and 1/sqrt(x) for x of ordinary size.  Float: the hardware estimate
-// (1 ulp) and one Newton step, a third of the instructions of the IEEE
-// sequences, which sat on the serial path of every round.
+// 1/x and 1/sqrt(x) for x of ordinary size.  Float: the hardware estimates
+// (1 ulp; the IEEE sequences sat on the serial path of every round), with one
+// Newton step where the result decides how orthogonal a reflector is.
 __device__ inline double rcp_of(double x) { return 1.0 / x; }
 __device__ inline double rsq_of(double x) { return 1.0 / sqrt(x); }
 __device__ inline float rcp_of(float x) {
@@ -66,8 +73,22 @@ __device__ inline float rsq_of(float x) {
   const float r = __builtin_amdgcn_rsqf(x);
   return fmaf(0.5f * r, fmaf(-x * r, r, 1.f), r);
 }
-__device__ inline double scale_rcp(double x) { return 1.0 / x; }
-__device__ inline float scale_rcp(float x) { return __builtin_amdgcn_rcpf(x); }
+__device__ inline double rcp_est(double x) { return 1.0 / x; }
+__device__ inline float rcp_est(float x) { return __builtin_amdgcn_rcpf(x); }
+__device__ inline double rsq_est(double x) { return 1.0 / sqrt(x); }
+__device__ inline float rsq_est(float x) { return __builtin_amdgcn_rsqf(x); }
+
+// The first lane's value in every lane (as a scalar operand).
+__device__ inline float bcast(float x) {
+  return __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(x)));
+}
+__device__ inline double bcast(double x) {
+  const long long b = __double_as_longlong(x);
+  const int lo = __builtin_amdgcn_readfirstlane((int)b), hi = __builtin_amdgcn_readfirstlane((int)(b >> 32));
+  return __longlong_as_double(((long long)hi << 32) | (unsigned)lo);
+}
+template <typename T>
+__device__ inline cx<T> bcast(cx<T> x) { return {bcast(x.r), bcast(x.i)}; }
 
 template <typename T>
 __device__ inline T abs1(T x) { return fabs(x); }
@@ -99,7 +120,7 @@ struct RealRoute {
   // to rounding whatever the error of v.
   __device__ static Refl make(const E (&x)[3], E& beta) {
     const T sc = fmax(fabs(x[0]), fmax(fabs(x[1]), fabs(x[2])));
-    const T rs = scale_rcp(sc);
+    const T rs = rcp_est(sc);
     const T a = x[0] * rs, b = x[1] * rs, c = x[2] * rs;
     const T t = b * b + c * c;
     if (!(sc > tiny_of<T>() * T(4)) || t == T(0)) {
@@ -107,9 +128,9 @@ struct RealRoute {
       return {T(0), T(0), T(0)};
     }
     const T n2 = a * a + t;
-    const T nrm = n2 * rsq_of(n2);
+    const T nrm = n2 * rsq_est(n2);
     const T den = a + copysign(nrm, a);
-    const T id = rcp_of(den);
+    const T id = rcp_est(den);
     const T w1 = b * id, w2 = c * id;
     beta = -copysign(nrm, a) * sc;
     return {T(2) * rcp_of(T(1) + w1 * w1 + w2 * w2), w1, w2};
@@ -139,8 +160,7 @@ struct RealRoute {
   // bulges of an in-LDS sweep / of a batch on an active block of order m
   __host__ __device__ static int small_bulges(int m) { return m / 6 < 1 ? 1 : (m / 6 > kNb ? kNb : m / 6); }
   __host__ __device__ static int batch_bulges(int m) {
-    const int cap = m < 768 ? 32 : 48;
-    return m / 6 > cap ? cap : m / 6;
+    return m / 6 > kMaxBatch ? kMaxBatch : m / 6;
   }
 };
 
@@ -176,7 +196,7 @@ struct CplxRoute {
       beta = f;
       return {T(1), zero()};
     }
-    const T rs = scale_rcp(sc);
+    const T rs = rcp_est(sc);
     const E fs = cscale(f, rs), gs = cscale(g, rs);
     const T f2 = cabs2(fs), g2 = cabs2(gs);
     Refl o;
@@ -220,8 +240,7 @@ struct CplxRoute {
   }
   __host__ __device__ static int small_bulges(int m) { return m / 3 < 1 ? 1 : (m / 3 > kNb ? kNb : m / 3); }
   __host__ __device__ static int batch_bulges(int m) {
-    const int cap = m < 768 ? 48 : 64;
-    return m / 3 > cap ? cap : m / 3;
+    return m / 3 > kMaxBatch ? kMaxBatch : m / 3;
   }
 };
 
@@ -237,157 +256,252 @@ __device__ inline bool negligible(E sub, E d0, E d1, T hnorm) {
   return a <= ulp * (abs1(d0) + abs1(d1)) || a <= fmax(tiny_of<T>() * T(1e4), ulp * hnorm);
 }
 
-// One bulge's share of a round, first half (its H wave): the reflector on
-// rows c0 .. c0+NR-1 (c0 = k + 1) from column k, or from the shift when it
-// enters, and the row operation on the columns right of k.  The rows' entries
-// are loaded before the reflector is formed, so the LDS latencies overlap.
-template <class A, int NR>
-__device__ __forceinline__ void row_step(typename A::E* h, int wl, int k, int lo, const typename A::Shift* sh,
-                                         typename A::Refl* rf, int lane) {
+// Keeps a loaded value where it was loaded: without a use outside the lane
+// predicate the compiler sinks the load into the predicated store and its
+// latency adds to the next one's.
+__device__ inline void pin(float& x) { asm volatile("" : "+v"(x)); }
+__device__ inline void pin(double& x) { asm volatile("" : "+v"(x)); }
+template <typename T>
+__device__ inline void pin(cx<T>& x) {
+  pin(x.r);
+  pin(x.i);
+}
+
+// One bulge's share of a round, first half: the reflector on rows c0 ..
+// c0+NR-1 (c0 = k + 1) from column k, or from the shift when it enters, and
+// the row operation on the columns right of k, RI per lane.
+template <class A, int NR, int RI>
+__device__ __forceinline__ typename A::Refl row_step(typename A::E* h, int wl, int k, int lo,
+                                                     const typename A::Shift* sh, int lane) {
   using E = typename A::E;
-  constexpr int S = A::SPAN, LD = A::W + 1, RI = (A::W + kWave - 1) / kWave;
+  constexpr int S = A::SPAN, LD = A::W + 1;
   const int c0 = k + 1;
+  E* const row = h + c0;
   E y[RI][S], x[S];
+  int off[RI];
 #pragma unroll
   for (int e = 0; e < RI; ++e) {
-    const E* p = h + c0 + min(c0 + lane + kWave * e, wl - 1) * LD;
+    off[e] = __mul24(min(c0 + lane + kWave * e, A::W - 1), LD);
 #pragma unroll
-    for (int q = 0; q < S; ++q) y[e][q] = q < NR ? p[q] : A::zero();
+    for (int q = 0; q < S; ++q) y[e][q] = q < NR ? row[off[e] + q] : A::zero();
   }
   if (k < lo) {
     A::intro(h, LD, lo, *sh, x);
   } else {
 #pragma unroll
-    for (int q = 0; q < S; ++q) x[q] = q < NR ? h[c0 + q + k * LD] : A::zero();
+    for (int q = 0; q < S; ++q) x[q] = q < NR ? row[q + k * LD] : A::zero();
   }
+#pragma unroll
+  for (int e = 0; e < RI; ++e)
+#pragma unroll
+    for (int q = 0; q < NR; ++q) pin(y[e][q]);
   E beta;
   const typename A::Refl f = A::make(x, beta);
-  if (lane == 0) {
-    *rf = f;
-    if (k >= lo) {
-      h[c0 + k * LD] = beta;
+  if (lane == 0 && k >= lo) {
+    row[k * LD] = beta;
 #pragma unroll
-      for (int q = 1; q < NR; ++q) h[c0 + q + k * LD] = A::zero();
-    }
+    for (int q = 1; q < NR; ++q) row[q + k * LD] = A::zero();
   }
 #pragma unroll
   for (int e = 0; e < RI; ++e) {
-    const int c = c0 + lane + kWave * e;
     A::rows(f, y[e]);
-    if (c < wl) {
-      E* p = h + c0 + c * LD;
+    if (c0 + lane + kWave * e < wl) {
 #pragma unroll
-      for (int q = 0; q < NR; ++q) p[q] = y[e][q];
+      for (int q = 0; q < NR; ++q) row[off[e] + q] = y[e][q];
     }
   }
+  return f;
 }
 
-// Second half, H wave: the column operation on rows 0 .. r1.
-template <class A, int NR>
-__device__ __forceinline__ void col_step(typename A::E* h, int c0, int r1, const typename A::Refl f, int lane) {
+// Second half: the column operation on rows 0 .. r1 of H and on U.  Of the
+// columns c0 .. c0+SPAN-1 of U all but the last are in ua from the bulge's
+// round before (loaded here if this is its first); the column that the bulge
+// leaves is stored (all of them if it is its last).  RI rows per lane; ua is
+// rolled on for all of them, so a lane's second row finds zeros there (the
+// columns of U are zero in rows that far down) when its turn comes.
+template <class A, int NR, int RI>
+__device__ __forceinline__ void col_step(typename A::E* h, typename A::E* u, int c0, int r1,
+                                         const typename A::Refl f,
+                                         typename A::E (&ua)[(A::W + kWave - 1) / kWave][A::SPAN], bool first,
+                                         bool last, int wl, int lane) {
   using E = typename A::E;
-  constexpr int S = A::SPAN, LD = A::W + 1, RI = (A::W + kWave - 1) / kWave;
+  constexpr int S = A::SPAN, LD = A::W + 1;
+  E* const hc = h + c0 * LD;
+  E* const uc = u + c0 * LD;
   E y[RI][S];
-#pragma unroll
-  for (int e = 0; e < RI; ++e) {
-    const E* p = h + min(lane + kWave * e, r1) + c0 * LD;
-#pragma unroll
-    for (int q = 0; q < S; ++q) y[e][q] = q < NR ? p[q * LD] : A::zero();
-  }
-#pragma unroll
-  for (int e = 0; e < RI; ++e) {
-    A::cols(f, y[e]);
-    if (lane + kWave * e <= r1) {
-      E* p = h + lane + kWave * e + c0 * LD;
-#pragma unroll
-      for (int q = 0; q < NR; ++q) p[q * LD] = y[e][q];
-    }
-  }
-}
-
-// Second half, U wave: columns c0 .. c0+SPAN-1 of U, of which all but the
-// last are in ua from the bulge's round before (loaded here if it is the
-// first); the column that the bulge leaves is stored (all if it is the last).
-template <class A, int NR>
-__device__ __forceinline__ void u_step(typename A::E* u, int wl, int c0, const typename A::Refl f,
-                                       typename A::E (&ua)[(A::W + kWave - 1) / kWave][A::SPAN], bool first,
-                                       bool last, int lane) {
-  using E = typename A::E;
-  constexpr int S = A::SPAN, LD = A::W + 1, RI = (A::W + kWave - 1) / kWave;
   if (first) {
 #pragma unroll
     for (int e = 0; e < RI; ++e)
 #pragma unroll
-      for (int q = 0; q + 1 < S; ++q) ua[e][q] = u[min(lane + kWave * e, wl - 1) + (c0 + q) * LD];
+      for (int q = 0; q + 1 < S; ++q) ua[e][q] = uc[min(lane + kWave * e, A::W - 1) + q * LD];
   }
 #pragma unroll
-  for (int e = 0; e < RI; ++e)
-    ua[e][S - 1] = NR == S ? u[min(lane + kWave * e, wl - 1) + (c0 + S - 1) * LD] : A::zero();
+  for (int e = 0; e < RI; ++e) {
+    const int i = min(lane + kWave * e, A::W - 1);
+#pragma unroll
+    for (int q = 0; q < S; ++q) y[e][q] = q < NR ? hc[i + q * LD] : A::zero();
+    ua[e][S - 1] = NR == S ? uc[i + (S - 1) * LD] : A::zero();
+  }
 #pragma unroll
   for (int e = 0; e < RI; ++e) {
-    A::cols(f, ua[e]);
-    const bool in = lane + kWave * e < wl;
-    E* p = u + lane + kWave * e + c0 * LD;
-    if (in) p[0] = ua[e][0];
-    if (last && in) {
 #pragma unroll
-      for (int q = 1; q < NR; ++q) p[q * LD] = ua[e][q];
+    for (int q = 0; q < NR; ++q) pin(y[e][q]);
+    if (NR == S) pin(ua[e][S - 1]);
+  }
+#pragma unroll
+  for (int e = 0; e < RI; ++e) {
+    const int i = lane + kWave * e;
+    A::cols(f, y[e]);
+    if (i <= r1) {
+#pragma unroll
+      for (int q = 0; q < NR; ++q) hc[i + q * LD] = y[e][q];
+    }
+    A::cols(f, ua[e]);
+    if (i < wl) {
+      uc[i] = ua[e][0];
+      if (last) {
+#pragma unroll
+        for (int q = 1; q < NR; ++q) uc[i + q * LD] = ua[e][q];
+      }
     }
 #pragma unroll
     for (int q = 0; q + 1 < S; ++q) ua[e][q] = ua[e][q + 1];
   }
 }
 
+// The rounds between a bulge's first and last: the same two halves without
+// any test.  A round is bound by instruction issue (one wave64 vector
+// instruction per SIMD and 2 ns, four waves to a SIMD), so everything that a
+// round could test is arranged to hold:
+//  * the row operation starts at column k itself, whose entries the first
+//    lane has, so the reflector's vector comes from there;
+//  * lanes past the last column work on the padding between h and u;
+//  * the column operation runs over all rows: below the bulge H is zero, and
+//    so is U (see rounds), and rows past the window are never written back;
+//  * RR and RC (column and row items per lane) are fixed per call.
+// rowb: byte offset of (k + 1, k + lane); colb: of (lane, k + 1).  (Float,
+// window of 128: with the tests a round took 0.61 us for one bulge and 1.08 us
+// for 16, here 0.32 and 0.75 us.)
+template <class A, int RR, int RC>
+__device__ __forceinline__ void steady_rounds(char* hb, char* ub, int& rowb, int& colb, int count,
+                                              typename A::E (&ua)[(A::W + kWave - 1) / kWave][A::SPAN],
+                                              int lane) {
+  using E = typename A::E;
+  constexpr int S = A::SPAN, W = A::W, LD = W + 1, B = sizeof(E), kPadB = W * LD * B;
+  auto at = [](char* p, int off) -> E& { return *reinterpret_cast<E*>(p + off); };
+#pragma clang loop unroll(disable)
+  for (; count > 0; --count) {
+    E y[RR][S], x[S], z[RC][S];
+    int ro[RR];
+#pragma unroll
+    for (int e = 0; e < RR; ++e) {
+      ro[e] = min(rowb + e * kWave * LD * B, kPadB);
+#pragma unroll
+      for (int q = 0; q < S; ++q) y[e][q] = at(hb, ro[e] + q * B);
+    }
+#pragma unroll
+    for (int q = 0; q < S; ++q) x[q] = bcast(y[0][q]);
+    E beta;
+    const typename A::Refl f = A::make(x, beta);
+#pragma unroll
+    for (int e = 0; e < RR; ++e) A::rows(f, y[e]);
+    if (lane == 0) {
+      y[0][0] = beta;
+#pragma unroll
+      for (int q = 1; q < S; ++q) y[0][q] = A::zero();
+    }
+#pragma unroll
+    for (int e = 0; e < RR; ++e)
+#pragma unroll
+      for (int q = 0; q < S; ++q) at(hb, ro[e] + q * B) = y[e][q];
+    __syncthreads();
+#pragma unroll
+    for (int e = 0; e < RC; ++e) {
+      if (kWave * (e + 1) > W && lane >= W - kWave * e) break;
+#pragma unroll
+      for (int q = 0; q < S; ++q) z[e][q] = at(hb, colb + (kWave * e + q * LD) * B);
+      ua[e][S - 1] = at(ub, colb + (kWave * e + (S - 1) * LD) * B);
+    }
+#pragma unroll
+    for (int e = 0; e < RC; ++e) {
+      if (kWave * (e + 1) > W && lane >= W - kWave * e) break;
+      A::cols(f, z[e]);
+#pragma unroll
+      for (int q = 0; q < S; ++q) at(hb, colb + (kWave * e + q * LD) * B) = z[e][q];
+      A::cols(f, ua[e]);
+      at(ub, colb + kWave * e * B) = ua[e][0];
+#pragma unroll
+      for (int q = 0; q + 1 < S; ++q) ua[e][q] = ua[e][q + 1];
+    }
+    rowb += (LD + 1) * B;
+    colb += LD * B;
+    __syncthreads();
+  }
+}
+
 // Rounds 0..R-1 of a chain of nb bulges on the LDS window h (order wl) with
 // its transformation u; lo and hi are the ends of the active block in window
-// coordinates (either may lie outside).  Bulge j enters at k = lo - 1 (its
-// first reflector comes from shift j) and leaves after k = hi - 2, where the
-// reflector has two rows.  Called by the whole workgroup; ends with a barrier.
-template <class A>
+// coordinates (either may lie outside).  Wave j has bulge j, which enters at
+// k = lo - 1 (its first reflector comes from shift j) and leaves after
+// k = hi - 2, where a reflector of the real route has two rows.  kFresh: u
+// starts as the identity.  A column of U then reaches S - 1 rows further down
+// with every bulge that has passed it, and one row per lane suffices until
+// row kWave is reached.  Called by the whole workgroup; ends with a barrier.
+template <class A, bool kFresh>
 __device__ __forceinline__ void rounds(typename A::E* h, typename A::E* u, int wl, int kbase, int R, int lo,
-                                       int hi, int nb, const typename A::Shift* sh, typename A::Refl* rf) {
+                                       int hi, int nb, const typename A::Shift* sh) {
   using E = typename A::E;
-  constexpr int S = A::SPAN, RI = (A::W + kWave - 1) / kWave;
-  const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x / kWave);
+  constexpr int S = A::SPAN, W = A::W, LD = W + 1, RI = (W + kWave - 1) / kWave, B = sizeof(E);
+  const int j = __builtin_amdgcn_readfirstlane((int)threadIdx.x / kWave);
   const int lane = threadIdx.x % kWave;
-  const int j = wave % kNb;
-  // rounds in which this wave's bulge moves, and in which its reflector is
-  // SPAN rows wide
+  // rounds [ra, rb) in which this wave's bulge moves
   const int k0 = kbase - S * j;
-  const int ra = max(0, lo - 1 - k0), rb = j < nb ? min(R, hi - 1 - k0) : 0;
-  if (wave < kNb) {
-#pragma clang loop unroll(disable)
-    for (int r = 0; r < R; ++r) {
-      const int k = k0 + r;
-      const bool live = r >= ra && r < rb;
-      const bool full = S == 2 || k < hi - 2;
-      if (live) {
-        if (full) row_step<A, S>(h, wl, k, lo, sh + j, rf + j, lane);
-        else row_step<A, 2>(h, wl, k, lo, sh + j, rf + j, lane);
-      }
+  const int ra = min(R, max(0, lo - 1 - k0)), rb = j < nb ? max(ra, min(R, hi - 1 - k0)) : ra;
+  E ua[RI][S];
+#pragma unroll
+  for (int e = 0; e < RI; ++e)
+#pragma unroll
+    for (int q = 0; q < S; ++q) ua[e][q] = A::zero();
+  auto idle = [](int n) {
+    for (; n > 0; --n) {
       __syncthreads();
-      if (live) {
-        const int r1 = min(min(k + S + 1, hi), wl - 1);
-        const typename A::Refl f = rf[j];
-        if (full) col_step<A, S>(h, k + 1, r1, f, lane);
-        else col_step<A, 2>(h, k + 1, r1, f, lane);
-      }
       __syncthreads();
     }
-  } else {
-    E ua[RI][S];
-#pragma clang loop unroll(disable)
-    for (int r = 0; r < R; ++r) {
-      const int k = k0 + r;
-      __syncthreads();
-      if (r >= ra && r < rb) {
-        const typename A::Refl f = rf[j];
-        if (S == 2 || k < hi - 2) u_step<A, S>(u, wl, k + 1, f, ua, r == ra, r == rb - 1, lane);
-        else u_step<A, 2>(u, wl, k + 1, f, ua, r == ra, r == rb - 1, lane);
-      }
-      __syncthreads();
+  };
+  // the bulge's first and last round in this call
+  auto single = [&](int r) {
+    const int k = k0 + r;
+    const bool full = S == 2 || k < hi - 2;
+    const typename A::Refl f = full ? row_step<A, S, RI>(h, wl, k, lo, sh + j, lane)
+                                    : row_step<A, 2, RI>(h, wl, k, lo, sh + j, lane);
+    __syncthreads();
+    const int r1 = min(min(k + S + 1, hi), wl - 1);
+    if (full) col_step<A, S, RI>(h, u, k + 1, r1, f, ua, r == ra, r == rb - 1, wl, lane);
+    else col_step<A, 2, RI>(h, u, k + 1, r1, f, ua, r == ra, r == rb - 1, wl, lane);
+    __syncthreads();
+  };
+  idle(ra);
+  if (rb > ra) single(ra);
+  if (rb > ra + 1) {
+    int k = k0 + ra + 1;
+    const int ke = k0 + rb - 1;
+    int rowb = (k + 1 + (k + lane) * LD) * B, colb = (lane + (k + 1) * LD) * B;
+    char *hb = reinterpret_cast<char*>(h), *ub = reinterpret_cast<char*>(u);
+    if constexpr (RI == 1) {
+      steady_rounds<A, 1, 1>(hb, ub, rowb, colb, ke - k, ua, lane);
+    } else {
+      // the row operation needs a second item per lane before k1, the column
+      // operation from k2 on
+      const int k1 = min(ke, max(k, wl - kWave)), k2 = min(ke, max(k, kFresh ? kWave - 1 - S - (S - 1) * j : k));
+      const int km = min(k1, k2), kx = max(k1, k2);
+      steady_rounds<A, 2, 1>(hb, ub, rowb, colb, km - k, ua, lane);
+      if (k1 > k2) steady_rounds<A, 2, 2>(hb, ub, rowb, colb, kx - km, ua, lane);
+      else steady_rounds<A, 1, 1>(hb, ub, rowb, colb, kx - km, ua, lane);
+      steady_rounds<A, 1, 2>(hb, ub, rowb, colb, ke - kx, ua, lane);
     }
+    single(rb - 1);
   }
+  idle(R - rb);
 }
 
 // Window load / store.  Entries below the band-th subdiagonal are zero.
@@ -412,21 +526,37 @@ __device__ __forceinline__ void win_load(typename A::E* h, typename A::E* u, con
   }
 }
 
-// U is written as W x W planes (real, then imaginary), zero outside m x m.
+// U is written for qr_apply_kernel's registers: its operand fragments one after
+// the other (32 columns; block of TM columns; group of KG rows; lane; four
+// rows), so that a wave reads each with consecutive 16-byte loads.  Planes
+// real, then imaginary; zero outside m x m.
 template <class A>
 __device__ __forceinline__ void win_store(const typename A::E* h, const typename A::E* u, typename A::T* H,
                                  int64_t ld, int s, int m, int band, typename A::T* U) {
-  constexpr int W = A::W;
+  using M = Mfma<typename A::T>;
+  constexpr int W = A::W, TM = M::TM, NB = 32 / TM, KG = kWave / TM * 4, G = W / KG;
   for (int x = threadIdx.x; x < W * W; x += kThreads) {
     const int i = x % W, j = x / W;
-    const bool in = i < m && j < m;
-    if (in)
+    if (i < m && j < m)
       A::store(H + (s + i) + (int64_t)(s + j) * ld, ld, i <= j + band ? h[i + j * (W + 1)] : A::zero());
-    A::store(U + x, 2 * W * W, in ? u[i + j * (W + 1)] : A::zero());
+  }
+  for (int x = threadIdx.x; x < W * W; x += kThreads) {
+    const int lane = x / 4 % kWave, f = x / (4 * kWave);  // fragment (32-column block, b, g)
+    const int i = f % G * KG + lane / TM * 4 + x % 4;
+    const int j = f / (G * NB) * 32 + f / G % NB * TM + lane % TM;
+    A::store(U + x, 2 * W * W, i < m && j < m ? u[i + j * (W + 1)] : A::zero());
   }
 }
 template <class A>
 constexpr int64_t u_elems() { return (int64_t)A::W * A::W * (A::kComplex ? 2 : 1); }
+
+// Bulges of a chain: at most one per wave, and few enough that a chain gains
+// at least half a window per step, so that windows kLag apart do not overlap.
+template <class A>
+constexpr int chain_bulges() {
+  static_assert(kLag == 2, "half a window per step");
+  return std::min(kNb, (A::W - 2) / (2 * A::SPAN));
+}
 
 // One window of a chain at one step of a batch.
 struct ChainWin {
@@ -449,15 +579,14 @@ __global__ __launch_bounds__(kThreads) void qr_chase_kernel(ChaseArgs<typename A
   constexpr int W = A::W;
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   E* h = reinterpret_cast<E*>(smem);
-  E* u = h + (W + 1) * W;
-  __shared__ typename A::Refl rf[kNb];
+  E* u = h + (W + 1) * W + kPad;
   __shared__ typename A::Shift sh[kNb];
   const ChainWin w = a.w[blockIdx.x];
   const int64_t ld = A::ldim(a.n);
   if (threadIdx.x < a.nb) sh[threadIdx.x] = reinterpret_cast<const typename A::Shift*>(a.shifts)[w.sh0 + threadIdx.x];
   win_load<A>(h, u, a.H, ld, w.s, w.wl, A::SPAN);
   __syncthreads();
-  rounds<A>(h, u, w.wl, w.kbase - w.s, w.R, a.lo - w.s, a.hi - w.s, a.nb, sh, rf);
+  rounds<A, true>(h, u, w.wl, w.kbase - w.s, w.R, a.lo - w.s, a.hi - w.s, a.nb, sh);
   win_store<A>(h, u, a.H, ld, w.s, w.wl, A::SPAN, a.U + blockIdx.x * u_elems<A>());
 }
 
@@ -567,8 +696,7 @@ __global__ __launch_bounds__(kThreads) void qr_small_kernel(int n, typename A::T
   static_assert(W <= 2 * kWave, "two ballots cover a block");
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   E* h = reinterpret_cast<E*>(smem);
-  E* u = h + (W + 1) * W;
-  __shared__ typename A::Refl rf[kNb];
+  E* u = h + (W + 1) * W + kPad;
   __shared__ typename A::Shift sh[kNb];
   const int b = blockIdx.x;
   if (b >= cnt[0]) return;
@@ -621,7 +749,7 @@ __global__ __launch_bounds__(kThreads) void qr_small_kernel(int n, typename A::T
       sh[q] = v;
     }
     __syncthreads();
-    rounds<A>(h, u, m, l - 1, hi - l + A::SPAN * (nb - 1), l, hi, nb, sh, rf);
+    rounds<A, false>(h, u, m, l - 1, hi - l + A::SPAN * (nb - 1), l, hi, nb, sh);
   }
   __syncthreads();
   if (!ok && threadIdx.x == 0) atomicOr(status, 1);
@@ -707,12 +835,13 @@ __global__ __launch_bounds__(kThreads) void qr_scan_kernel(int n, typename A::T*
 // The panel is staged in LDS, k-contiguous; wave v forms 32 of the W
 // outputs of every panel line on MFMA, its part of U held in registers.  The
 // operand whose index is the contiguous one of the output goes second, so the
-// stores are coalesced.  (n = 2048, one window of 128: 25 us on the vector
-// units with U copied to every workgroup's LDS, 8 us here.)
+// stores are coalesced.  (n = 2048: 25 us per step for one window on the
+// vector units with U copied to every workgroup's LDS; 22 us for up to 13
+// windows here.)
 struct WinRange { int s, wl; };
 template <typename T>
 struct ApplyArgs {
-  int n, cols;
+  int n;
   T* H;
   T* Z;
   const T* U;
@@ -721,7 +850,7 @@ struct ApplyArgs {
   WinRange w[kMaxChains];
 };
 
-template <class A>
+template <class A, bool kCols>
 __global__ __launch_bounds__(A::W / 32 * kWave) void qr_apply_kernel(ApplyArgs<typename A::T> a) {
   using T = typename A::T;
   using E = typename A::E;
@@ -739,7 +868,7 @@ __global__ __launch_bounds__(A::W / 32 * kWave) void qr_apply_kernel(ApplyArgs<t
   T* base;
   int nl;
   int64_t lstr, kstr;
-  if (!a.cols) {
+  if (!kCols) {
     const int c0 = s + wl + 32 * (int)blockIdx.x;
     nl = min(32, n - c0);
     base = a.H + s + (int64_t)c0 * ld;
@@ -765,7 +894,7 @@ __global__ __launch_bounds__(A::W / 32 * kWave) void qr_apply_kernel(ApplyArgs<t
     for (int b = 0; b < NB; ++b)
 #pragma unroll
       for (int g = 0; g < G; ++g) {
-        const T* q = U + p * W * W + (ib + b * TM + mn) * W + g * KG + 4 * kk;
+        const T* q = U + p * W * W + ((((ib / 32) * NB + b) * G + g) * kWave + lane) * 4;
 #pragma unroll
         for (int e = 0; e < 4; ++e) uf[p][b][g][e] = q[e];
       }
@@ -774,7 +903,7 @@ __global__ __launch_bounds__(A::W / 32 * kWave) void qr_apply_kernel(ApplyArgs<t
 #pragma unroll
   for (int e = 0; e < N; ++e) {
     const int x = t + NT * e;
-    const int c = a.cols ? x % 32 : x / W, k = a.cols ? x / 32 : x % W;
+    const int c = kCols ? x % 32 : x / W, k = kCols ? x / 32 : x % W;
     E v = A::zero();
     if (c < nl && k < wl) v = A::load(base + c * lstr + k * kstr, ld);
     if constexpr (A::kComplex) {
@@ -792,7 +921,7 @@ __global__ __launch_bounds__(A::W / 32 * kWave) void qr_apply_kernel(ApplyArgs<t
     for (int b = 0; b < NB; ++b)
 #pragma unroll
       for (int c = 0; c < NB; ++c) acc[p][b][c] = typename M::acc_t{};
-  const T sg = a.cols ? T(1) : T(-1);  // U or conj(U)
+  const T sg = kCols ? T(1) : T(-1);  // U or conj(U)
 #pragma unroll
   for (int g = 0; g < G; ++g)
 #pragma unroll
@@ -806,7 +935,7 @@ __global__ __launch_bounds__(A::W / 32 * kWave) void qr_apply_kernel(ApplyArgs<t
       for (int b = 0; b < NB; ++b)
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-          auto mac = [&](typename M::acc_t& d, T uv, T pv) { d = a.cols ? M::mma(uv, pv, d) : M::mma(pv, uv, d); };
+          auto mac = [&](typename M::acc_t& d, T uv, T pv) { d = kCols ? M::mma(uv, pv, d) : M::mma(pv, uv, d); };
           mac(acc[0][b][c], uf[0][b][g][e], pf[0][e]);
           if constexpr (A::kComplex) {
             const T ui = sg * uf[1][b][g][e];
@@ -822,8 +951,8 @@ __global__ __launch_bounds__(A::W / 32 * kWave) void qr_apply_kernel(ApplyArgs<t
     for (int c = 0; c < NB; ++c)
 #pragma unroll
       for (int r = 0; r < M::NACC; ++r) {
-        const int i = ib + b * TM + (a.cols ? M::c_row(lane, r) : M::c_col(lane, r));
-        const int l = c * TM + (a.cols ? M::c_col(lane, r) : M::c_row(lane, r));
+        const int i = ib + b * TM + (kCols ? M::c_row(lane, r) : M::c_col(lane, r));
+        const int l = c * TM + (kCols ? M::c_col(lane, r) : M::c_row(lane, r));
         if (i < wl && l < nl) {
           T* o = base + l * lstr + i * kstr;
           o[0] = acc[0][b][c][r];
@@ -833,16 +962,15 @@ __global__ __launch_bounds__(A::W / 32 * kWave) void qr_apply_kernel(ApplyArgs<t
 }
 
 template <class A>
-constexpr size_t win_lds() { return sizeof(typename A::E) * (size_t)(A::W + 1) * A::W * 2; }
+constexpr size_t win_lds() { return sizeof(typename A::E) * ((size_t)(A::W + 1) * A::W * 2 + kPad); }
 
 template <class A>
-void launch_apply(hipStream_t st, ApplyArgs<typename A::T>& a, int windows) {
+void launch_apply(hipStream_t st, const ApplyArgs<typename A::T>& a, int windows) {
   const int g = (int)ceil_div(a.n, 32);
-  for (int cols = 0; cols < 2; ++cols) {
-    a.cols = cols;
-    hipLaunchKernelGGL(qr_apply_kernel<A>, dim3(cols ? 2 * g : g, windows), dim3(A::W / 32 * kWave), 0, st, a);
-    MSQRT_LAUNCH_CHECK();
-  }
+  hipLaunchKernelGGL((qr_apply_kernel<A, false>), dim3(g, windows), dim3(A::W / 32 * kWave), 0, st, a);
+  MSQRT_LAUNCH_CHECK();
+  hipLaunchKernelGGL((qr_apply_kernel<A, true>), dim3(2 * g, windows), dim3(A::W / 32 * kWave), 0, st, a);
+  MSQRT_LAUNCH_CHECK();
 }
 
 // (Quasi-)triangular Schur form of the Hessenberg matrix H, Z <- Z U.
@@ -887,7 +1015,7 @@ bool schur_qr(hipStream_t st, int n, typename A::T* H, typename A::T* Z, HseqrWo
     lo = res[1];
     if (++batches > max_batches || stuck > 300) return false;  // no progress: give up
     const int total = A::batch_bulges(hi - lo + 1);
-    const int K = (int)ceil_div(total, kNb), nb = (int)ceil_div(total, K);
+    const int K = (int)ceil_div(total, chain_bulges<A>()), nb = (int)ceil_div(total, K);
     // the windows of one chain; bulge j sits at kbase - SPAN j
     std::vector<ChainWin> win;
     int s = lo, kb = lo - 1;
