@@ -623,7 +623,7 @@ void reduce(hipStream_t st, int n, T* H, T* Z, GehrdWork& w) {
       const unsigned nb = 2u * (unsigned)nbp - 1u;  // barriers of the launch
       base.gen += nb;
       base.top += (unsigned)std::min(G, 8) * nb;
-      for (int g = 0; g < 8; ++g) base.sub[g] += (unsigned)(G / 8 + (g < G % 8 ? 1 : 0)) * nb;
+      for (int g = 0; g < 8 && G > 8; ++g) base.sub[g] += (unsigned)(G / 8 + (g < G % 8 ? 1 : 0)) * nb;
     } else {
       hipLaunchKernelGGL(kern, dim3(1), dim3(kThreads), lds, st, pa);
       MSQRT_LAUNCH_CHECK();

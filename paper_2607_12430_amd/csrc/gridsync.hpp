@@ -7,7 +7,7 @@
 
 namespace msqrt {
 
-constexpr int kSyncThreads = 1024;  // workgroup size of the kernels that use this header
+constexpr int kSyncThreads = 1024;  // default workgroup size
 
 // Values exchanged between workgroups inside a launch (partial products and
 // sums) are written and read with agent-scope atomic stores and loads, which
@@ -84,7 +84,7 @@ constexpr int kBarWords = kBarSub + 8 * kBarSubStride;  // words of one entry's 
 
 // Counter values at the start of a launch.  All counters only grow within one
 // reduction, so a barrier needs no reset: the host adds what every launch
-// contributes.
+// contributes (nothing to the group counters when G <= 8, see grid_arrive).
 struct BarrierBase {
   unsigned gen;     // release word: barriers completed
   unsigned top;     // top counter
@@ -105,26 +105,26 @@ struct BarrierBase {
 // by the first lane of the last wave (kBarT), which has no row work, so the
 // atomics' round trips hold up no thread that has.  A spin limit keeps a
 // broken launch from hanging: it raises the sticky failure flag.
-constexpr int kBarT = kSyncThreads - kWave;
+template <int NT>
+constexpr int kBarT = NT - kWave;
 
 // Arrival; returns true in thread kBarT if this workgroup released barrier k.
+template <int NT = kSyncThreads>
 __device__ inline bool grid_arrive(unsigned* bar, const BarrierBase& base, unsigned sub_base, int blk,
                                    int G, int k) {
   __builtin_amdgcn_s_waitcnt(0);
   __syncthreads();
   // A launch of one workgroup per batch entry synchronises with itself only:
   // the wait above and the workgroup barrier make its stores visible to its
-  // own later loads.  (The trailing order only shrinks, so every later launch
-  // of the reduction has G = 1 too and no counter is read again.)
+  // own later loads.
   if (G == 1) return true;
   bool released = false;
-  if (threadIdx.x == kBarT) {
+  if (threadIdx.x == kBarT<NT>) {
     const unsigned g = (unsigned)blk & 7u;
     const unsigned gsz = (unsigned)G / 8u + (g < ((unsigned)G & 7u) ? 1u : 0u);
     const unsigned ng = G < 8 ? (unsigned)G : 8u;
     // with G <= 8 every group has one member, which is always its group's
-    // last arrival: its counter is skipped (later launches of the reduction
-    // have G <= 8 too, so the group counters are not read again)
+    // last arrival: its counter is skipped, here and in the host's bases
     const unsigned old =
         G <= 8 ? sub_base + gsz * (unsigned)k - 1u
                : __hip_atomic_fetch_add(&bar[kBarSub + kBarSubStride * g], 1u, __ATOMIC_RELAXED,
@@ -141,8 +141,9 @@ __device__ inline bool grid_arrive(unsigned* bar, const BarrierBase& base, unsig
 }
 
 // Wait for barrier k (released: what grid_arrive returned).
+template <int NT = kSyncThreads>
 __device__ inline void grid_wait(unsigned* bar, const BarrierBase& base, int k, bool released) {
-  if (threadIdx.x == kBarT && !released) {
+  if (threadIdx.x == kBarT<NT> && !released) {
     const unsigned gen = base.gen + (unsigned)k;
     unsigned spins = 0;
     while (cload(&bar[kBarRel]) < gen) {
@@ -159,9 +160,10 @@ __device__ inline void grid_wait(unsigned* bar, const BarrierBase& base, int k, 
   __syncthreads();
 }
 
+template <int NT = kSyncThreads>
 __device__ inline void grid_barrier(unsigned* bar, const BarrierBase& base, unsigned sub_base, int blk,
                                     int G, int k) {
-  grid_wait(bar, base, k, grid_arrive(bar, base, sub_base, blk, G, k));
+  grid_wait<NT>(bar, base, k, grid_arrive<NT>(bar, base, sub_base, blk, G, k));
 }
 
 }  // namespace msqrt

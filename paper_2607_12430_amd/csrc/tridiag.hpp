@@ -7,8 +7,8 @@
 namespace msqrt {
 
 struct SytrdWork {
-  DevBuf VW, WV, ypart, sp, vp, bar;
-  int nbar = 0;  // batch entries of the last reduction (error flags)
+  DevBuf ypart, colb, sp, bar;
+  int nbar = 0;  // batch entries whose grid barrier the last reduction used
 };
 
 struct StedcWork {
