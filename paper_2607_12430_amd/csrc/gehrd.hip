@@ -111,6 +111,7 @@ template <typename T, class F>
 struct PanelArgs {
   int n, p, nbp;
   int rbp, G;    // rows per workgroup (a power of two), workgroups
+  int nbw;       // columns of a full panel
   int wf_lds;    // the exchanged column fits LDS
   T* H;          // ld P n, imaginary plane n rows below
   T* V;          // P planes of n x kNb, ld n: this panel's reflectors
@@ -124,27 +125,29 @@ struct PanelArgs {
 };
 
 template <class F>
-size_t panel_lds(int rbp, int n, bool wf) {
-  const size_t e = (size_t)3 * rbp * kLd + 2 * kNb * kLd + kThreads + kNb * kLd + rbp + 4 * kNb +
+size_t panel_lds(int rbp, int n, bool wf, int nbw = kNb) {
+  const size_t e = (size_t)3 * rbp * (nbw + 1) + 2 * kNb * kLd + kThreads + kNb * kLd + rbp + 4 * kNb +
                    (wf ? (size_t)n + kPad : 0);
   return e * sizeof(typename F::E);
 }
 
 // KREG: elements of A's rows held in registers per thread (the rest is read
-// from L2 at every column).
-template <typename T, class F, int KREG>
+// from L2 at every column).  kW: columns of a panel, 0 = a.nbw of them (the
+// large blocks of rows of the largest matrices, where LDS has no room for kNb).
+template <typename T, class F, int KREG, int kW>
 __global__ __launch_bounds__(kThreads) void hess_panel_kernel(PanelArgs<T, F> a) {
   using E = typename F::E;
   const int n = a.n, p = a.p, rbp = a.rbp, G = a.G;
+  const int lv = (kW ? kW : a.nbw) + 1;  // LDS row stride of V, Y and A's columns
   const int64_t ldh = (int64_t)F::P * n;
   const int blk = blockIdx.x, r0 = blk * rbp;
   const int t = threadIdx.x, g16 = t >> 4, l = t & 15;
   const bool solo = G == 1;
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   E* Vl = reinterpret_cast<E*>(smem);  // [r][k]
-  E* Yl = Vl + rbp * kLd;
-  E* Ap = Yl + rbp * kLd;              // the panel's columns of A, own rows
-  E* Tl = Ap + rbp * kLd;              // [row][column]
+  E* Yl = Vl + rbp * lv;
+  E* Ap = Yl + rbp * lv;              // the panel's columns of A, own rows
+  E* Tl = Ap + rbp * lv;              // [row][column]
   E* PV = Tl + kNb * kLd;              // V(p + 1 + q, k)
   E* red = PV + kNb * kLd;
   E* wl = red + kThreads + kNb * kLd;  // own rows of the column
@@ -159,8 +162,8 @@ __global__ __launch_bounds__(kThreads) void hess_panel_kernel(PanelArgs<T, F> a)
     if (g == (blk & 7)) sub_base = a.bar_base.sub[g];
   int nbar = 0;
 
-  for (int x = t; x < rbp * kLd; x += kThreads) {
-    const int r = x / kLd, k = x % kLd;
+  for (int x = t; x < rbp * lv; x += kThreads) {
+    const int r = x / lv, k = x % lv;
     Vl[x] = Yl[x] = F::zero();
     Ap[x] = (r0 + r < n && k < a.nbp) ? F::load(a.H + r0 + r + (int64_t)(p + k) * ldh, n) : F::zero();
   }
@@ -206,9 +209,9 @@ __global__ __launch_bounds__(kThreads) void hess_panel_kernel(PanelArgs<T, F> a)
     // w = A(:, c) - Y V(c, :)^*
     for (int r = g16; r < rbp; r += kThreads / 16) {
       E s = F::zero();
-      for (int k = l; k < i; k += 16) s = F::add(s, F::mulc(PV[(i - 1) * kLd + k], Yl[r * kLd + k]));
+      for (int k = l; k < i; k += 16) s = F::add(s, F::mulc(PV[(i - 1) * kLd + k], Yl[r * lv + k]));
       s = F::sum16(s);
-      if (l == 0) wl[r] = F::sub(Ap[r * kLd + i], s);
+      if (l == 0) wl[r] = F::sub(Ap[r * lv + i], s);
     }
     __syncthreads();
     if (i > 0) {
@@ -216,7 +219,7 @@ __global__ __launch_bounds__(kThreads) void hess_panel_kernel(PanelArgs<T, F> a)
       if (t < kNb * 16) {
         E s = F::zero();
         if (g16 < i)
-          for (int r = l; r < rbp; r += 16) s = F::add(s, F::mulc(Vl[r * kLd + g16], wl[r]));
+          for (int r = l; r < rbp; r += 16) s = F::add(s, F::mulc(Vl[r * lv + g16], wl[r]));
         s = F::sum16(s);
         if (l == 0) {
           if (solo) us[g16] = s;
@@ -240,7 +243,7 @@ __global__ __launch_bounds__(kThreads) void hess_panel_kernel(PanelArgs<T, F> a)
       __syncthreads();
       for (int r = g16; r < rbp; r += kThreads / 16) {
         E s = F::zero();
-        for (int k = l; k < i; k += 16) s = F::add(s, F::mul(Vl[r * kLd + k], zs[k]));
+        for (int k = l; k < i; k += 16) s = F::add(s, F::mul(Vl[r * lv + k], zs[k]));
         s = F::sum16(s);
         if (l == 0) wl[r] = F::sub(wl[r], s);
       }
@@ -251,7 +254,7 @@ __global__ __launch_bounds__(kThreads) void hess_panel_kernel(PanelArgs<T, F> a)
       E s = F::zero();
       for (int r = l; r < rbp; r += 16)
         if (r0 + r >= c + 2) {
-          if (g16 < i) s = F::add(s, F::mulc(Vl[r * kLd + g16], wl[r]));
+          if (g16 < i) s = F::add(s, F::mulc(Vl[r * lv + g16], wl[r]));
           else if (g16 == kNb - 1) s = F::add(s, F::real(F::abs2(wl[r])));
         }
       s = F::sum16(s);
@@ -305,7 +308,7 @@ __global__ __launch_bounds__(kThreads) void hess_panel_kernel(PanelArgs<T, F> a)
         E v = F::zero();
         if (row == c + 1) v = F::real(T(1));
         else if (row > c + 1) v = F::mul(scal, wl[r]);
-        Vl[r * kLd + i] = v;
+        Vl[r * lv + i] = v;
         F::store(a.H + row + (int64_t)c * ldh, n,
                  row <= c ? wl[r] : (row == c + 1 ? F::corner(alpha, beta) : F::zero()));
       }
@@ -352,9 +355,9 @@ __global__ __launch_bounds__(kThreads) void hess_panel_kernel(PanelArgs<T, F> a)
       E s = F::zero();
       for (int q = l; q < CG; q += 16) s = F::add(s, red[q * rbp + r]);
       s = F::mul(scal, s);
-      for (int k = l; k < i; k += 16) s = F::sub(s, F::mul(Yl[r * kLd + k], vt[k]));
+      for (int k = l; k < i; k += 16) s = F::sub(s, F::mul(Yl[r * lv + k], vt[k]));
       s = F::sum16(s);
-      if (l == 0) Yl[r * kLd + i] = r0 + r < n ? F::mul(tau, s) : F::zero();
+      if (l == 0) Yl[r * lv + i] = r0 + r < n ? F::mul(tau, s) : F::zero();
     }
     __syncthreads();
   }
@@ -363,7 +366,7 @@ __global__ __launch_bounds__(kThreads) void hess_panel_kernel(PanelArgs<T, F> a)
   for (int x = t; x < rbp * kNb; x += kThreads) {
     const int r = x % rbp, k = x / rbp, row = r0 + r;
     if (row >= n) continue;
-    const E v = Vl[r * kLd + k], y = Yl[r * kLd + k];
+    const E v = k < lv - 1 ? Vl[r * lv + k] : F::zero(), y = k < lv - 1 ? Yl[r * lv + k] : F::zero();
     F::store(a.V + row + (int64_t)k * n, pl, v);
     F::store(a.YV + row + (int64_t)k * n, 2 * pl, y);
     F::store(a.YV + pl + row + (int64_t)k * n, 2 * pl, v);
@@ -557,32 +560,32 @@ void reduce(hipStream_t st, int n, T* H, T* Z, GehrdWork& w) {
   MSQRT_LAUNCH_CHECK();
   const int nref = n - 2;  // reflectors for columns 0 .. n-3
   if (nref <= 0) return;
-  auto kern = hess_panel_kernel<T, F, KREG>;
-  static int resident = 0;  // co-resident workgroups of the panel kernel at full LDS
-  if (resident == 0) {
-    MSQRT_HIP(hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kLdsMax));
-    int per_cu = 0, ncu = 0, dev = 0;
-    MSQRT_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, (const void*)kern, kThreads, kLdsMax));
-    MSQRT_HIP(hipGetDevice(&dev));
-    MSQRT_HIP(hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev));
-    resident = std::max(1, per_cu) * std::max(1, ncu);
-  }
+  // one workgroup per CU at full LDS
+  int ncu = 0, dev = 0;
+  MSQRT_HIP(hipGetDevice(&dev));
+  MSQRT_HIP(hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev));
   // Rows per workgroup: 16 (a quarter of a wave per row sum) until the grid
   // would exceed the co-resident workgroups; small matrices in one workgroup.
-  const int gmax = std::min(resident, kMaxG);
+  const int gmax = std::min(std::max(1, ncu), kMaxG);
   int rbp = 16;
   while (rbp < kSolo && rbp < n) rbp *= 2;
   if (n > rbp || panel_lds<F>(rbp, n, true) > kLdsMax) {
     rbp = 16;
-    while (rbp < kThreads && ceil_div(n, rbp) > gmax) rbp *= 2;
+    while (rbp < kThreads / 2 && ceil_div(n, rbp) > gmax) rbp *= 2;
   }
+  // Panels of kNb columns unless the rows per workgroup leave LDS too little
+  // room for them (complex double from n = 8193 on, float from 65537 on).
+  int nbw = kNb;
+  while (nbw > 2 && panel_lds<F>(rbp, n, false, nbw) > kLdsMax) nbw -= 2;
   const int G = (int)ceil_div(n, rbp);
-  if (G > gmax || panel_lds<F>(rbp, n, false) > kLdsMax)
+  if (G > gmax || panel_lds<F>(rbp, n, false, nbw) > kLdsMax)
     throw Error{MSQRT_ERR_UNSUPPORTED, "Hessenberg reduction: matrix too large"};
-  const bool wf_lds = panel_lds<F>(rbp, n, true) <= kLdsMax;
-  const size_t lds = panel_lds<F>(rbp, n, wf_lds);
+  const bool wf_lds = panel_lds<F>(rbp, n, true, nbw) <= kLdsMax;
+  const size_t lds = panel_lds<F>(rbp, n, wf_lds, nbw);
+  auto kern = nbw == kNb ? hess_panel_kernel<T, F, KREG, kNb> : hess_panel_kernel<T, F, KREG, 0>;
+  MSQRT_HIP(hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kLdsMax));
 
-  const int npan = (int)ceil_div(nref, kNb);
+  const int npan = (int)ceil_div(nref, nbw);
   const int64_t pl = (int64_t)n * kNb;  // one plane of a panel
   T* Vall = w.V.ensure<T>((int64_t)npan * P * pl);
   T* Tall = w.Tall.ensure<T>((int64_t)npan * P * kNb * kNb);
@@ -613,10 +616,10 @@ void reduce(hipStream_t st, int n, T* H, T* Z, GehrdWork& w) {
   w.W2.ensure<T>((int64_t)(256 + ceil_div(n + kNb, 32)) * 4 * P * 32 * kNb);
 
   for (int pi = 0; pi < npan; ++pi) {
-    const int p = pi * kNb, nbp = std::min(kNb, nref - p);
+    const int p = pi * nbw, nbp = std::min(nbw, nref - p);
     T* V = Vall + (int64_t)pi * P * pl;
     T* Tp = Tall + (int64_t)pi * P * kNb * kNb;
-    PanelArgs<T, F> pa{n, p, nbp, rbp, G, wf_lds ? 1 : 0, H, V, YV, Tp, ex, ex + n, ex + n + kMaxG * kNb, bar, base};
+    PanelArgs<T, F> pa{n, p, nbp, rbp, G, nbw, wf_lds ? 1 : 0, H, V, YV, Tp, ex, ex + n, ex + n + kMaxG * kNb, bar, base};
     if (G > 1) {
       void* args[] = {&pa};
       MSQRT_HIP(hipLaunchCooperativeKernel((const void*)kern, dim3(G), dim3(kThreads), args, lds, st));
@@ -638,7 +641,7 @@ void reduce(hipStream_t st, int n, T* H, T* Z, GehrdWork& w) {
   }
   // Z(p+1:, p+1:) -= V (T (V^* Z(p+1:, p+1:)))
   for (int pi = npan - 1; pi >= 0; --pi) {
-    const int p = pi * kNb, m = n - p - 1;
+    const int p = pi * nbw, m = n - p - 1;
     const T* V = Vall + (int64_t)pi * P * pl;
     T* Zs = Z + p + 1 + (int64_t)(p + 1) * ld;
     const int splits = vta(m, m, 0, V + p + 1, Zs, ld, n, Zs, n);

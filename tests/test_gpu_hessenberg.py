@@ -1,6 +1,6 @@
 """The Hessenberg reduction where its launch shape changes: one workgroup up to
-order 128, 16 rows per workgroup above, rows of A beyond the registers, and a
-column too long for LDS."""
+order 128, 16 rows per workgroup above, rows of A beyond the registers, a
+column too long for LDS, and rows that leave LDS too little for a full panel."""
 
 import numpy as np
 import pytest
@@ -10,7 +10,7 @@ pytestmark = pytest.mark.gpu
 
 @pytest.mark.parametrize("prec,n", [("fp32", 34), ("fp32", 127), ("fp32", 128), ("fp32", 129),
                                     ("fp32", 301), ("fp32", 1100), ("fp64", 98), ("fp64", 128),
-                                    ("fp64", 129), ("fp64", 600), ("fp64", 3008)])
+                                    ("fp64", 129), ("fp64", 600), ("fp64", 3008), ("fp64", 8200)])
 def test_complex_reduction(prec, n):
     import torch
     import paper_2607_12430_amd as msq
