@@ -24,6 +24,7 @@
 #include <string>
 
 #include <algorithm>
+#include <mutex>
 #include <type_traits>
 #include <vector>
 
@@ -105,12 +106,14 @@ struct EpiStages<Epi, std::void_t<decltype(Epi::kStaged)>> : std::integral_const
 // coalesced (32 consecutive rows per half-wave).  For a symmetric output the
 // mirror (j, i) is written from the wave's own LDS block st (32 x 33 out_t),
 // read in transposed order, so those stores are coalesced too instead of
-// touching 32 rows per store instruction.
+// touching 32 rows per store instruction.  Elements before (mo, no) belong to
+// another workgroup.
 constexpr int kStageLd = 33;
 
 template <class Epi, class Acc>
 __device__ inline void epi_block_staged(const GemmShape& s, const Epi& epi, int b, int gi0, int gj0,
-                                        const Acc& acc, typename Epi::out_t* st, int lane) {
+                                        const Acc& acc, typename Epi::out_t* st, int lane, int mo = 0,
+                                        int no = 0) {
   using O = typename Epi::out_t;
   using M = Mfma<float>;
   static_assert(M::TM == 32 && M::TN == 32 && M::NACC == 16, "32 x 32 accumulator blocks");
@@ -122,13 +125,13 @@ __device__ inline void epi_block_staged(const GemmShape& s, const Epi& epi, int 
 #pragma unroll
   for (int r = 0; r < M::NACC; ++r) {
     const int gj = gj0 + M::c_row(lane, r);
-    const bool ok = gi < s.M && gj < s.N && !(s.tri && gi < gj);
+    const bool ok = gi >= mo && gj >= no && gi < s.M && gj < s.N && !(s.tri && gi < gj);
     x0[r] = ok ? epi.load(b, gi, gj) : 0.0;
   }
 #pragma unroll
   for (int r = 0; r < M::NACC; ++r) {
     const int gj = gj0 + M::c_row(lane, r);
-    const bool ok = gi < s.M && gj < s.N && !(s.tri && gi < gj);
+    const bool ok = gi >= mo && gj >= no && gi < s.M && gj < s.N && !(s.tri && gi < gj);
     const O x = ok ? epi.value(b, gi, gj, acc[r], x0[r]) : O(0);
     if (ok) dst[gi + (int64_t)gj * ld] = x;
     if (s.tri) st[(lane % 32) * kStageLd + M::c_row(lane, r)] = x;
@@ -142,7 +145,7 @@ __device__ inline void epi_block_staged(const GemmShape& s, const Epi& epi, int 
   for (int q = 0; q < 16; ++q) {
     const int li = 2 * q + lane / 32, lj = lane % 32;
     const int mi = gi0 + li, mj = gj0 + lj;
-    if (mi < s.M && mj < s.N && mi > mj) dst[mj + (int64_t)mi * ld] = st[li * kStageLd + lj];
+    if (mi >= mo && mj >= no && mi < s.M && mj < s.N && mi > mj) dst[mj + (int64_t)mi * ld] = st[li * kStageLd + lj];
   }
   // the next block's writes to st follow these reads
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
@@ -948,11 +951,252 @@ inline int gemm_cu_count() {
 // share a function type, so they are told apart by address).
 template <class Kern>
 inline void gemm_lds_attr(Kern k, size_t bytes) {
+  static std::mutex mu;
   static std::vector<const void*> done;
+  std::lock_guard<std::mutex> lk(mu);
   const void* f = (const void*)k;
   if (std::find(done.begin(), done.end(), f) != done.end()) return;
   MSQRT_HIP(hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes));
   done.push_back(f);
+}
+
+// ---------------------------------------------------------------------------
+// Float and double kernel with 64 x 64 tiles, for products whose 128-tiles
+// leave CUs idle: such a launch lasts as long as one workgroup's chain of
+// slabs, and a quarter of the work per workgroup on four times the CUs
+// shortens that chain.  Four waves of 32 x 32; a slab is 256 bytes of k per
+// row (64 floats, 32 doubles).  Slabs are double-buffered in LDS and two more
+// are on their way in registers, so a load has two slabs of MFMAs to arrive.
+// Rows of the slab are not padded: 16-byte groups of a row are permuted by a
+// function of the row such that both the writes and the fragment reads of 16
+// consecutive lanes touch every bank once.
+// Global loads are 16 bytes in the operand's own unit-stride direction (4 x 4
+// or 2 x 4 blocks are transposed in registers when that is not k) and need no
+// alignment beyond the element's.  They need no bounds either: the last tile
+// of a row or column of tiles starts 64 before the end and skips the outputs
+// that the tile before it owns, the last slab likewise with zeros for the k
+// already summed; only operands smaller than a tile are read element by element.
+// Bound by the chain of slabs, 1.9 us each against 0.9 us of MFMA; float 512^3
+// in 18 us (128-tiles 49), double 31 (86); with bounds tests in the loads an
+// order of 500 took twice as long as 512, now it takes the same.
+typedef float f32v4u __attribute__((ext_vector_type(4), aligned(4)));
+typedef double f64v2u __attribute__((ext_vector_type(2), aligned(8)));
+
+template <typename T>
+struct Narrow {
+  static constexpr int NT = 64, V = 16 / (int)sizeof(T), KS = 16 * V;
+  static constexpr int RG = NT / V, KQ = GTHREADS / RG, KT = KS / KQ;  // row groups, k groups, k per thread
+  static constexpr int E = NT * KS / GTHREADS;
+  static constexpr size_t kLds = (size_t)2 * 2 * NT * KS * sizeof(T);
+  using vu = typename std::conditional<sizeof(T) == 4, f32v4u, f64v2u>::type;
+  __device__ static int at(int row, int group) {
+    const int f = row / V + (16 / V) * (row % V);
+    return row * KS + ((group ^ f) & 15) * V;
+  }
+};
+
+// Rows r0 .. r0 + 63 and k kb .. kb + KS - 1 of op(X); elements with k < klo
+// or k >= K are zeros, rows >= R are arbitrary elements of X.
+template <typename T, bool RC>
+__device__ __forceinline__ void narrow_load(const T* __restrict__ X, int64_t ld, int r0, int R, int kb, int klo,
+                                            int K, int t, T (&v)[Narrow<T>::E]) {
+  using N = Narrow<T>;
+  const bool rows = r0 + N::NT <= R, ks = kb + N::KS <= K, cut = kb < klo || !ks;
+  if constexpr (RC) {
+    const int r = r0 + N::V * (t % N::RG), k = kb + N::KT * (t / N::RG);
+    if (rows) {
+#pragma unroll
+      for (int e = 0; e < N::KT; ++e) {
+        const typename N::vu x = *reinterpret_cast<const typename N::vu*>(X + r + (int64_t)min(k + e, K - 1) * ld);
+#pragma unroll
+        for (int i = 0; i < N::V; ++i) v[e * N::V + i] = x[i];
+      }
+    } else {
+#pragma unroll
+      for (int e = 0; e < N::KT; ++e)
+#pragma unroll
+        for (int i = 0; i < N::V; ++i)
+          v[e * N::V + i] = X[min(r + i, R - 1) + (int64_t)min(k + e, K - 1) * ld];
+    }
+    if (cut) {
+#pragma unroll
+      for (int e = 0; e < N::KT; ++e)
+#pragma unroll
+        for (int i = 0; i < N::V; ++i)
+          if (k + e < klo || k + e >= K) v[e * N::V + i] = T(0);
+    }
+  } else {
+    const int k = kb + N::V * (t % 16), r = r0 + t / 16;
+    if (ks) {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const typename N::vu x =
+            *reinterpret_cast<const typename N::vu*>(X + k + (int64_t)min(r + 16 * e, R - 1) * ld);
+#pragma unroll
+        for (int i = 0; i < N::V; ++i) v[e * N::V + i] = x[i];
+      }
+    } else {
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+#pragma unroll
+        for (int i = 0; i < N::V; ++i)
+          v[e * N::V + i] = X[min(k + i, K - 1) + (int64_t)min(r + 16 * e, R - 1) * ld];
+    }
+    if (cut) {
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+#pragma unroll
+        for (int i = 0; i < N::V; ++i)
+          if (k + i < klo || k + i >= K) v[e * N::V + i] = T(0);
+    }
+  }
+}
+
+template <typename T, bool RC>
+__device__ __forceinline__ void narrow_store(T* Xs, int t, const T (&v)[Narrow<T>::E]) {
+  using N = Narrow<T>;
+  typedef T vec __attribute__((ext_vector_type(16 / sizeof(T))));
+  if constexpr (RC) {
+    const int r = N::V * (t % N::RG), g0 = N::KT / N::V * (t / N::RG);
+#pragma unroll
+    for (int i = 0; i < N::V; ++i)
+#pragma unroll
+      for (int g = 0; g < N::KT / N::V; ++g) {
+        vec x;
+#pragma unroll
+        for (int e = 0; e < N::V; ++e) x[e] = v[(g * N::V + e) * N::V + i];
+        *reinterpret_cast<vec*>(Xs + N::at(r + i, g0 + g)) = x;
+      }
+  } else {
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      vec x;
+#pragma unroll
+      for (int i = 0; i < N::V; ++i) x[i] = v[e * N::V + i];
+      *reinterpret_cast<vec*>(Xs + N::at(t / 16 + 16 * e, t % 16)) = x;
+    }
+  }
+}
+
+template <typename T, bool TA, bool TB, class Epi>
+__global__ __launch_bounds__(GTHREADS, 2) void gemm_narrow_kernel(GemmShape s, const T* __restrict__ A,
+                                                                  const T* __restrict__ B, Epi epi,
+                                                                  double* __restrict__ partials) {
+  using M = Mfma<T>;
+  using N = Narrow<T>;
+  typedef T vec __attribute__((ext_vector_type(16 / sizeof(T))));
+  constexpr int NBLK = 32 / M::TM, KL = kWave / M::TM, STEPS = 16 / KL;
+  extern __shared__ __attribute__((aligned(16))) unsigned char gemm_ldsn[];
+  __shared__ double red[GTHREADS / kWave];
+  T* const lds = reinterpret_cast<T*>(gemm_ldsn);
+  auto slab = [&](int buf, int op) { return lds + (buf * 2 + op) * N::NT * N::KS; };
+
+  int tm, tn;
+  if (!gemm_tile_coords(s, tm, tn)) return;
+  const int batch = blockIdx.y;
+  const int K = (batch == (int)gridDim.y - 1) ? s.K_last : s.K;
+  A += (int64_t)batch * s.sA;
+  B += (int64_t)batch * s.sB;
+  const int mo = tm * N::NT, no = tn * N::NT;  // first output owned
+  const int m0 = max(0, min(mo, s.M - N::NT)), n0 = max(0, min(no, s.N - N::NT));
+  const int t = threadIdx.x, lane = t % kWave, wave = t / kWave;
+  const int wm = wave % 2, wn = wave / 2;
+  constexpr bool ARC = !TA, BRC = TB;
+
+  typename M::acc_t acc[NBLK][NBLK];
+#pragma unroll
+  for (int i = 0; i < NBLK; ++i)
+#pragma unroll
+    for (int j = 0; j < NBLK; ++j)
+#pragma unroll
+      for (int r = 0; r < M::NACC; ++r) acc[i][j][r] = T(0);
+
+  struct Regs {
+    T a[N::E], b[N::E];
+  } r0, r1;
+  const int nslab = (K + N::KS - 1) / N::KS;
+  auto load = [&](int q, Regs& r) {
+    const int klo = q * N::KS, kb = max(0, min(klo, K - N::KS));
+    narrow_load<T, ARC>(A, s.lda, m0, s.M, kb, klo, K, t, r.a);
+    narrow_load<T, BRC>(B, s.ldb, n0, s.N, kb, klo, K, t, r.b);
+  };
+  auto store = [&](int buf, const Regs& r) {
+    narrow_store<T, ARC>(slab(buf, 0), t, r.a);
+    narrow_store<T, BRC>(slab(buf, 1), t, r.b);
+  };
+  if (nslab > 0) {
+    load(0, r0);
+    if (nslab > 1) load(1, r1);
+    store(0, r0);
+  }
+  __syncthreads();
+  const int h = lane / M::TM, fr = lane % M::TM;
+  // slab q, in LDS buffer `buf`: rl receives slab q + 2, rs holds slab q + 1
+  auto body = [&](int q, int buf, Regs& rl, const Regs& rs) {
+    if (q + 2 < nslab) load(q + 2, rl);
+    const T* As = slab(buf, 0);
+    const T* Bs = slab(buf, 1);
+    auto step = [&](int g) {  // KL groups of V consecutive k, one per lane group
+      vec av[NBLK], bv[NBLK];
+#pragma unroll
+      for (int i = 0; i < NBLK; ++i) {
+        av[i] = *reinterpret_cast<const vec*>(As + N::at(wm * 32 + i * M::TM + fr, KL * g + h));
+        bv[i] = *reinterpret_cast<const vec*>(Bs + N::at(wn * 32 + i * M::TM + fr, KL * g + h));
+      }
+      // B as the first operand: lanes run along the rows of C
+#pragma unroll
+      for (int c = 0; c < N::V; ++c)
+#pragma unroll
+        for (int i = 0; i < NBLK; ++i)
+#pragma unroll
+          for (int j = 0; j < NBLK; ++j) acc[i][j] = M::mma(bv[j][c], av[i][c], acc[i][j]);
+    };
+    constexpr int KG = KL * N::V;
+    if (K - q * N::KS >= N::KS) {
+#pragma unroll
+      for (int g = 0; g < STEPS; ++g) step(g);
+    } else if (K >= N::KS) {  // the k left are the last ones of the slab
+      for (int g = (N::KS - (K - q * N::KS)) / KG; g < STEPS; ++g) step(g);
+    } else {
+      for (int g = 0; g < (K + KG - 1) / KG; ++g) step(g);
+    }
+    if (q + 1 < nslab) store(buf ^ 1, rs);
+    __syncthreads();
+  };
+  for (int q = 0; q < nslab; q += 2) {
+    body(q, 0, r0, r1);
+    if (q + 1 < nslab) body(q + 1, 1, r1, r0);
+  }
+
+  if constexpr (sizeof(T) == 4 && EpiStages<Epi>::value) {
+    static_assert((size_t)(GTHREADS / kWave) * 32 * kStageLd * sizeof(typename Epi::out_t) <= N::kLds,
+                  "staging blocks fit the slab buffers");
+    if (!epi.live(batch)) return;
+    typename Epi::out_t* st = reinterpret_cast<typename Epi::out_t*>(gemm_ldsn) + wave * 32 * kStageLd;
+    epi_block_staged(s, epi, batch, m0 + wm * 32, n0 + wn * 32, acc[0][0], st, lane, mo, no);
+    return;
+  }
+  double part = 0.0;
+#pragma unroll
+  for (int i = 0; i < NBLK; ++i)
+#pragma unroll
+    for (int j = 0; j < NBLK; ++j)
+#pragma unroll
+      for (int r = 0; r < M::NACC; ++r) {
+        const int gi = m0 + wm * 32 + i * M::TM + M::c_col(lane, r);
+        const int gj = n0 + wn * 32 + j * M::TN + M::c_row(lane, r);
+        if (gi >= mo && gj >= no && gi < s.M && gj < s.N) {
+          if (s.tri && gi < gj) continue;
+          part += epi(batch, gi, gj, acc[i][j][r], s.tri && gi != gj);
+        }
+      }
+  if (Epi::kReduces) {
+    part = block_sum(part, red);
+    if (t == 0) {
+      const int id = (blockIdx.x % 8) * s.per_xcd + blockIdx.x / 8;
+      partials[(int64_t)batch * s.ntiles + id] = part;
+    }
+  }
 }
 
 // ---------------------------------------------------------------------------
@@ -1346,6 +1590,40 @@ int launch_gemm(hipStream_t st, bool ta, bool tb, const GemmShape& s, const T* A
       return s.ntiles;
     }
   }
+  // 64-tiles where the busiest CU gets at most three quarters of the work that
+  // 128-tiles (four units each) give it.  Measured 128 -> 64, microseconds:
+  // with one unit per CU against four, float 1000^3 90 -> 39, double
+  // 165 -> 67; two against four, float 1280^3 111 -> 64; three against four,
+  // float 1531^3 133 -> 130, double 246 -> 218, and nine against twelve, 64
+  // symmetric 512^3 204 -> 155.  With equal work the larger tile reads LDS
+  // half as often: four against four, float 2048^3 174 -> 189.
+  auto narrow = [&]() {
+    const int64_t ncu = gemm_cu_count();
+    const GemmShape w0 = make_shape(s.M, s.N, s.K, s.lda, s.ldb, s.sA, s.sB, s.tri != 0, Narrow<T>::NT);
+    const int64_t u128 = ceil_div((int64_t)s.ntiles * batch, ncu), u64 = ceil_div((int64_t)w0.ntiles * batch, ncu);
+    if (u64 <= 3 * u128) {
+      GemmShape w = w0;
+      w.K_last = s.K_last;
+      dim3 gn(8 * w.per_xcd, batch);
+      auto gon = [&](auto kern) {
+        gemm_lds_attr(kern, Narrow<T>::kLds);
+        hipLaunchKernelGGL(kern, gn, block, Narrow<T>::kLds, st, w, A, B, epi, partials);
+      };
+      if (!ta && !tb) gon(gemm_narrow_kernel<T, false, false, Epi>);
+      else if (ta && !tb) gon(gemm_narrow_kernel<T, true, false, Epi>);
+      else if (!ta && tb) gon(gemm_narrow_kernel<T, false, true, Epi>);
+      else gon(gemm_narrow_kernel<T, true, true, Epi>);
+      MSQRT_LAUNCH_CHECK();
+      if (tok >= 0) {
+        const double outs = w.tri ? 0.5 * (double)w.N * (w.N + 1) : (double)w.M * w.N;
+        const double kk = (double)w.K * (batch - 1) + w.K_last;
+        const std::string cls = std::string(sizeof(T) == 4 ? "gemm_f32:" : "gemm_f64:") + Epi::kName;
+        prof_end(tok, st, cls.c_str(), 2.0 * outs * kk, 0.0);
+      }
+      return w.ntiles;
+    }
+    return 0;
+  };
   if constexpr (std::is_same<T, float>::value) {
     const int64_t ncu = gemm_cu_count();
     if (s.tri && s.M >= kWideMin && s.K >= 256 && (int64_t)s.ntiles * batch > 2 * ncu) {
@@ -1401,6 +1679,7 @@ int launch_gemm(hipStream_t st, bool ta, bool tb, const GemmShape& s, const T* A
       }
       return w.ntiles;
     }
+    if (const int nt = narrow()) return nt;
     // more tiles than two workgroups per CU hold but no more than three:
     // the 16-deep variant runs them in one round
     const int64_t units = (int64_t)s.ntiles * batch;
@@ -1443,6 +1722,7 @@ int launch_gemm(hipStream_t st, bool ta, bool tb, const GemmShape& s, const T* A
       }
       return w.ntiles;
     }
+    if (const int nt = narrow()) return nt;
     auto go = [&](auto kern) {
       gemm_lds_attr(kern, kGemmF64Lds);
       hipLaunchKernelGGL(kern, grid, block, kGemmF64Lds, st, s, A, B, epi, partials);

@@ -433,7 +433,7 @@ msqrt_status refine_general(Factor* f, const double* A, int64_t lda, double* X, 
   T* M = f->ws1.ensure<T>(2 * nn);
   T* Wst = f->ws2.ensure<T>(2 * nn);
   T* Rt = f->gt.ensure<T>(2 * nn);
-  const int ntiles = (int)(ceil_div(n, 128) * ceil_div(n, 128));
+  const int ntiles = (int)residual_tiles(n);
   double* part = f->part.ensure<double>(2 * (int64_t)ntiles + 2 * kRedBlocks + 64);
   double* rn = f->rnorm.ensure<double>(2);
   double* sc2 = f->gsc.ensure<double>(2);
@@ -621,7 +621,7 @@ msqrt_status refine_root3(Factor* f, const double* A, int64_t lda, double* X, in
   T* M = f->ws1.ensure<T>(2 * nn);
   T* Wst = f->ws2.ensure<T>(2 * nn);
   T* Rt = f->gt.ensure<T>(2 * nn);
-  const int ntiles = (int)(ceil_div(n, 128) * ceil_div(n, 128));
+  const int ntiles = (int)residual_tiles(n);
   double* part = f->part.ensure<double>(2 * (int64_t)ntiles + 2 * kRedBlocks + 64);
   double* rn = f->rnorm.ensure<double>(2);
   double* sc2 = f->gsc.ensure<double>(2);
@@ -752,7 +752,7 @@ msqrt_status backward_general(Factor* f, const double* X, int64_t ldx, const dou
   T* M = f->ws1.ensure<T>(2 * nn);
   T* Wst = f->ws2.ensure<T>(2 * nn);
   T* Rt = f->gt.ensure<T>(2 * nn);
-  const int ntiles = (int)(ceil_div(n, 128) * ceil_div(n, 128));
+  const int ntiles = (int)residual_tiles(n);
   double* part = f->part.ensure<double>(2 * (int64_t)ntiles + 2 * kRedBlocks + 64);
   double* rn = f->rnorm.ensure<double>(2);
   double* one2 = f->gsc.ensure<double>(2);
@@ -941,7 +941,7 @@ msqrt_status refine_real(Factor* f, const double* A, int64_t lda, double* X, int
   T* M = f->ws1.ensure<T>(nn);
   T* Wm = f->ws2.ensure<T>(nn);
   T* Rt = f->gt.ensure<T>(nn);
-  const int ntiles = (int)(ceil_div(n, 128) * ceil_div(n, 128));
+  const int ntiles = (int)residual_tiles(n);
   double* part = f->part.ensure<double>((int64_t)ntiles + 2 * kRedBlocks + 64);
   double* rn = f->rnorm.ensure<double>(1);
   trsylv_reset(st, f->tw);
@@ -1035,7 +1035,7 @@ msqrt_status backward_real(Factor* f, const double* X, int64_t ldx, const double
   T* M = f->ws1.ensure<T>(nn);
   T* Wm = f->ws2.ensure<T>(nn);
   T* Rt = f->gt.ensure<T>(nn);
-  const int ntiles = (int)(ceil_div(n, 128) * ceil_div(n, 128));
+  const int ntiles = (int)residual_tiles(n);
   double* part = f->part.ensure<double>((int64_t)ntiles + 2 * kRedBlocks + 64);
   double* rn = f->rnorm.ensure<double>(1);
   double* one = f->gsc.ensure<double>(1);

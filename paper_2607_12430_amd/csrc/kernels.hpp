@@ -41,6 +41,10 @@ void launch_copy_f64(hipStream_t st, int n, const double* A, int64_t lda, int64_
 
 // ---- GEMMs (gemm.hip) -----------------------------------------------------
 
+// Most tiles per batch entry of a full n x n residual product (its smallest
+// tiles are 64 x 64).
+inline int64_t residual_tiles(int n) { return ceil_div(n, 64) * ceil_div(n, 64); }
+
 // C = alpha op(A) op(B)   (+ beta C)
 // split = true: BF16-split products (hi*hi + hi*lo + lo*hi, float accumulation)
 void gemm_store_f32(hipStream_t st, bool ta, bool tb, int M, int N, int K, const float* A,

@@ -85,9 +85,9 @@ void pool_free(void* p, size_t bytes) {
 // Refinement for HPD (real SPD) factors: Alg. 3 loop.  T is the factor
 // precision (float for FP32, double for FP64).
 
-// Tiles of the symmetric residual GEMM (128 x 128, lower triangle): sizes
-// the per-tile partial sums of ||R||_F.
-static int64_t residual_tiles(int n) { return ceil_div(n, 128) * (ceil_div(n, 128) + 1) / 2; }
+// Tiles of the symmetric residual GEMM (lower triangle of its smallest tiles):
+// sizes the per-tile partial sums of ||R||_F.
+static int64_t residual_tiles_sym(int n) { return ceil_div(n, 64) * (ceil_div(n, 64) + 1) / 2; }
 
 template <typename T>
 static msqrt_status refine_hpd(Factor* f, const double* A, int64_t lda, int64_t sA, double* X,
@@ -100,7 +100,7 @@ static msqrt_status refine_hpd(Factor* f, const double* A, int64_t lda, int64_t 
   const T* s = f->S.as<T>();
   T* W1 = ws ? (T*)ws->w1 : f->ws1.ensure<T>(nn * batch);
   T* W2 = ws ? (T*)ws->w2 : f->ws2.ensure<T>(nn * batch);
-  double* part = ws ? ws->part : f->part.ensure<double>(residual_tiles(n) * batch + 64);
+  double* part = ws ? ws->part : f->part.ensure<double>(residual_tiles_sym(n) * batch + 64);
   double* rn = ws ? ws->rn : f->rnorm.ensure<double>(batch);
   int* active = ws ? ws->flags : f->active.ensure<int>(batch);
   double* best = nullptr;
@@ -255,7 +255,7 @@ static msqrt_status backward_hpd(Factor* f, const double* X, int64_t ldx, const 
   double* T1 = Xs + nn * batch;
   T* W1 = f->ws1.ensure<T>(nn * batch);
   T* W2 = f->ws2.ensure<T>(nn * batch);
-  const int ntile = (int)(ceil_div(n, 128) * ceil_div(n, 128));
+  const int ntile = (int)residual_tiles(n);
   const int nt32 = (int)ceil_div(n, 32);
   double* part = f->part.ensure<double>((int64_t)std::max(ntile, nt32 * (nt32 + 1) / 2) * batch + 64);
   double* rn = f->rnorm.ensure<double>(2 * batch);
@@ -617,7 +617,7 @@ size_t carve_refine_ws(const Factor* f, unsigned char* base, RefineWs* ws) {
   const int64_t n = f->n, batch = f->batch, nn = n * n;
   const size_t es = f->prec == MSQRT_PREC_FP64 ? 8 : 4;
   const int64_t nt = ceil_div(n, 32);
-  const int64_t nparts = std::max<int64_t>(residual_tiles((int)n), nt * (nt + 1) / 2) * batch + 64;
+  const int64_t nparts = std::max<int64_t>(residual_tiles_sym((int)n), nt * (nt + 1) / 2) * batch + 64;
   auto up = [](size_t b) { return (b + 255) & ~(size_t)255; };
   size_t off = 0;
   auto take = [&](size_t bytes) {
