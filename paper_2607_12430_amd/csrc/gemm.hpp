@@ -987,6 +987,7 @@ struct Narrow {
   static constexpr int NT = 64, V = 16 / (int)sizeof(T), KS = 16 * V;
   static constexpr int RG = NT / V, KQ = GTHREADS / RG, KT = KS / KQ;  // row groups, k groups, k per thread
   static constexpr int E = NT * KS / GTHREADS;
+  static constexpr int NBLK = 32 / Mfma<T>::TM;  // MFMA blocks per side of a wave's 32 x 32
   static constexpr size_t kLds = (size_t)2 * 2 * NT * KS * sizeof(T);
   using vu = typename std::conditional<sizeof(T) == 4, f32v4u, f64v2u>::type;
   __device__ static int at(int row, int group) {
@@ -1078,32 +1079,21 @@ __device__ __forceinline__ void narrow_store(T* Xs, int t, const T (&v)[Narrow<T
   }
 }
 
-template <typename T, bool TA, bool TB, class Epi>
-__global__ __launch_bounds__(GTHREADS, 2) void gemm_narrow_kernel(GemmShape s, const T* __restrict__ A,
-                                                                  const T* __restrict__ B, Epi epi,
-                                                                  double* __restrict__ partials) {
+// acc = the 64 x 64 tile at (m0, n0) of op(A) op(B), op(A) R x K, op(B) K x C;
+// wave w holds rows 32 (w % 2) and columns 32 (w / 2) of it.  Ends with a
+// barrier, so lds (Narrow<T>::kLds bytes) is free again.
+template <typename T, bool TA, bool TB>
+__device__ __forceinline__ void narrow_product(const T* __restrict__ A, int64_t lda, const T* __restrict__ B,
+                                               int64_t ldb, int R, int C, int K, int m0, int n0, T* lds,
+                                               typename Mfma<T>::acc_t (&acc)[Narrow<T>::NBLK][Narrow<T>::NBLK]) {
   using M = Mfma<T>;
   using N = Narrow<T>;
   typedef T vec __attribute__((ext_vector_type(16 / sizeof(T))));
-  constexpr int NBLK = 32 / M::TM, KL = kWave / M::TM, STEPS = 16 / KL;
-  extern __shared__ __attribute__((aligned(16))) unsigned char gemm_ldsn[];
-  __shared__ double red[GTHREADS / kWave];
-  T* const lds = reinterpret_cast<T*>(gemm_ldsn);
+  constexpr int NBLK = N::NBLK, KL = kWave / M::TM, STEPS = 16 / KL;
+  constexpr bool ARC = !TA, BRC = TB;
   auto slab = [&](int buf, int op) { return lds + (buf * 2 + op) * N::NT * N::KS; };
-
-  int tm, tn;
-  if (!gemm_tile_coords(s, tm, tn)) return;
-  const int batch = blockIdx.y;
-  const int K = (batch == (int)gridDim.y - 1) ? s.K_last : s.K;
-  A += (int64_t)batch * s.sA;
-  B += (int64_t)batch * s.sB;
-  const int mo = tm * N::NT, no = tn * N::NT;  // first output owned
-  const int m0 = max(0, min(mo, s.M - N::NT)), n0 = max(0, min(no, s.N - N::NT));
   const int t = threadIdx.x, lane = t % kWave, wave = t / kWave;
   const int wm = wave % 2, wn = wave / 2;
-  constexpr bool ARC = !TA, BRC = TB;
-
-  typename M::acc_t acc[NBLK][NBLK];
 #pragma unroll
   for (int i = 0; i < NBLK; ++i)
 #pragma unroll
@@ -1117,8 +1107,8 @@ __global__ __launch_bounds__(GTHREADS, 2) void gemm_narrow_kernel(GemmShape s, c
   const int nslab = (K + N::KS - 1) / N::KS;
   auto load = [&](int q, Regs& r) {
     const int klo = q * N::KS, kb = max(0, min(klo, K - N::KS));
-    narrow_load<T, ARC>(A, s.lda, m0, s.M, kb, klo, K, t, r.a);
-    narrow_load<T, BRC>(B, s.ldb, n0, s.N, kb, klo, K, t, r.b);
+    narrow_load<T, ARC>(A, lda, m0, R, kb, klo, K, t, r.a);
+    narrow_load<T, BRC>(B, ldb, n0, C, kb, klo, K, t, r.b);
   };
   auto store = [&](int buf, const Regs& r) {
     narrow_store<T, ARC>(slab(buf, 0), t, r.a);
@@ -1167,6 +1157,28 @@ __global__ __launch_bounds__(GTHREADS, 2) void gemm_narrow_kernel(GemmShape s, c
     body(q, 0, r0, r1);
     if (q + 1 < nslab) body(q + 1, 1, r1, r0);
   }
+}
+
+template <typename T, bool TA, bool TB, class Epi>
+__global__ __launch_bounds__(GTHREADS, 2) void gemm_narrow_kernel(GemmShape s, const T* __restrict__ A,
+                                                                  const T* __restrict__ B, Epi epi,
+                                                                  double* __restrict__ partials) {
+  using M = Mfma<T>;
+  using N = Narrow<T>;
+  constexpr int NBLK = N::NBLK;
+  extern __shared__ __attribute__((aligned(16))) unsigned char gemm_ldsn[];
+  __shared__ double red[GTHREADS / kWave];
+  int tm, tn;
+  if (!gemm_tile_coords(s, tm, tn)) return;
+  const int batch = blockIdx.y;
+  const int K = (batch == (int)gridDim.y - 1) ? s.K_last : s.K;
+  const int mo = tm * N::NT, no = tn * N::NT;  // first output owned
+  const int m0 = max(0, min(mo, s.M - N::NT)), n0 = max(0, min(no, s.N - N::NT));
+  const int t = threadIdx.x, lane = t % kWave, wave = t / kWave;
+  const int wm = wave % 2, wn = wave / 2;
+  typename M::acc_t acc[NBLK][NBLK];
+  narrow_product<T, TA, TB>(A + (int64_t)batch * s.sA, s.lda, B + (int64_t)batch * s.sB, s.ldb, s.M, s.N, K, m0, n0,
+                            reinterpret_cast<T*>(gemm_ldsn), acc);
 
   if constexpr (sizeof(T) == 4 && EpiStages<Epi>::value) {
     static_assert((size_t)(GTHREADS / kWave) * 32 * kStageLd * sizeof(typename Epi::out_t) <= N::kLds,

@@ -3,9 +3,14 @@
 //
 // All scalar work (eigenvalues, secular roots, deflation) is float64 on the
 // device; the eigenvector matrices and the merge products use the factor
-// precision T on the MFMA GEMM.  Every merge of a level is processed by the
-// same launches: one workgroup per merge for the deflation scan, one wave per
-// secular root, one GEMM per merge for the eigenvector update.
+// precision T on MFMA products, the blocks of up to 32 rows in float64.  Every merge of a level is processed by the
+// same five launches: one workgroup per merge for the deflation scan, one wave
+// per secular root (and per 64 rows for the deflation rotations), per
+// recomputed z and per eigenvector, and the products of all merges.  The
+// recursion halves every block, so a kernel finds its block from a position
+// or a block number alone, and nothing crosses to or from the host between
+// levels.  (Block tables copied to the device and the rotation counts read
+// back at every level cost more host time than the small levels ran.)
 //
 // Merge of two solved halves (T1' = Q1 D1 Q1^T, T2' = Q2 D2 Q2^T) coupled by
 // beta:  T = diag(Q1, Q2) (D + rho z z^T) diag(Q1, Q2)^T with
@@ -18,6 +23,8 @@
 #include <cmath>
 #include <vector>
 
+#include "gemm.hpp"
+#include "gridsync.hpp"
 #include "kernels.hpp"
 #include "tridiag.hpp"
 
@@ -25,19 +32,74 @@ namespace msqrt {
 
 namespace {
 
-constexpr int kLeaf = 32;
+// Largest leaf.  A leaf's chain of rotations grows with its square (198 us at
+// 32), a level of merges costs about 40 us: order 64 takes 0.13 ms with leaves
+// of 16, 0.24 with 32; order 1000 0.56 and 0.76.
+// A float solve works on blocks of up to 2 kLeaf rows in float64: with the
+// merges to 32 rows in float, Z^T Z - I was 10 to 28% larger than with leaves
+// of 32.
+constexpr int kLeaf = 16;
 
-struct MergeDesc {
-  int s, n1, m;  // start, left size, total size
+// A block of the recursion: rows s .. s + m of the concatenated index space;
+// a merge (m > kLeaf) has halves of m / 2 and m - m / 2.
+struct Block {
+  int s, m, id;  // id: entry * 2^depth + path, -1 for no block
+  __host__ __device__ int n1() const { return m / 2; }
+  __host__ __device__ bool merge() const { return id >= 0 && m > kLeaf; }
 };
+
+// Block number id of `depth`.  A leaf met above that depth keeps its place
+// with the remaining path bits zero; other paths below it hold nothing.
+__host__ __device__ inline Block block_at(int n, int depth, int id) {
+  const int e = id >> depth, path = id & ((1 << depth) - 1);
+  Block b{e * n, n, id};
+  for (int i = depth - 1; i >= 0; --i) {
+    if (b.m <= kLeaf) {
+      if (path & ((2 << i) - 1)) b.id = -1;
+      return b;
+    }
+    const int h = b.m / 2;
+    if (path >> i & 1) {
+      b.s += h;
+      b.m -= h;
+    } else {
+      b.m = h;
+    }
+  }
+  return b;
+}
+
+// Block of `depth` that holds position p.
+__device__ inline Block block_of(int n, int depth, int p) {
+  const int e = p / n;
+  Block b{e * n, n, e};
+  for (int i = 0; i < depth; ++i) {
+    b.id <<= 1;
+    if (b.m <= kLeaf) continue;
+    const int h = b.m / 2;
+    if (p >= b.s + h) {
+      b.s += h;
+      b.m -= h;
+      b.id |= 1;
+    } else {
+      b.m = h;
+    }
+  }
+  return b;
+}
 
 // A batch of tridiagonal matrices of order n is solved as one matrix of
 // order batch * n whose off-diagonal vanishes at the entry boundaries: every
 // position s of the concatenated index space belongs to entry s / n, and no
 // leaf or merge straddles two entries.  The eigenvector matrices stay n x n
 // per entry (stride n * n); this is the offset of the diagonal block that
-// starts at position s.
-__host__ __device__ inline int64_t blk_off(int s, int n) {
+// starts at position s.  The float64 blocks of a float solve are kept in a
+// band of kBand rows instead (column c of the concatenated space at c * kBand;
+// blocks of at most kBand rows do not overlap).
+constexpr int kBand = 2 * kLeaf;
+template <bool kB>
+__device__ inline int64_t blk_off(int s, int n) {
+  if (kB) return (int64_t)s * (kBand + 1);
   const int e = s / n, sl = s - e * n;
   return (int64_t)e * n * n + sl + (int64_t)sl * n;
 }
@@ -65,43 +127,45 @@ struct Meta {
 };
 
 // ---------------------------------------------------------------------------
-// Tearing: for every split point q, d[q-1] -= |e[q-1]| and d[q] -= |e[q-1]|.
-
-__global__ void tear_kernel(int nsplit, const int* splits, double* d, const double* e) {
-  const int t = blockIdx.x * blockDim.x + threadIdx.x;
-  if (t >= nsplit) return;
-  const int q = splits[t];
-  const double b = fabs(e[q - 1]);
-  d[q - 1] -= b;
-  d[q] -= b;
-}
-
-// ---------------------------------------------------------------------------
 // Leaf eigensolver: implicit symmetric QR with Wilkinson shifts on a leaf of
-// size L <= 32.  One wave per leaf; every lane runs the scalar recurrence
+// size L <= kLeaf.  One wave per leaf; every lane runs the scalar recurrence
 // redundantly (identical values) and lane r applies the rotations to row r of
-// the eigenvector block.
+// the eigenvector block.  Bound by the dependent chain of one rotation after
+// the other, so the chain is kept short: 1/r from the reciprocal square root
+// estimate and one cubic Newton step (2^-66 before rounding; the leaf is
+// scaled by a power of two so that r^2 cannot overflow, and r^2 close to
+// underflow takes hypot), the rotated entries carried in registers, the next
+// ones read a step ahead: 150 ns per rotation, 310 with hypot, two divisions
+// and LDS reads in the chain.
 
-template <typename T>
-__global__ __launch_bounds__(64) void leaf_kernel(const int* leaf_start, const int* leaf_size,
-                                                  const double* dg, const double* eg, double* lam,
-                                                  T* Z, int n) {
-  __shared__ double d[kLeaf], e[kLeaf], Zl[kLeaf][kLeaf + 1];
-  const int lf = blockIdx.x, lane = threadIdx.x;
-  const int s = leaf_start[lf], L = leaf_size[lf];
-  if (lane < L) {
-    d[lane] = dg[s + lane];
-    e[lane] = (lane + 1 < L) ? eg[s + lane] : 0.0;
-    for (int c = 0; c < L; ++c) Zl[lane][c] = (c == lane) ? 1.0 : 0.0;
+template <typename T, bool kB>
+__global__ __launch_bounds__(64) void leaf_kernel(int depth, const double* dg, const double* eg,
+                                                  const int* exs, double* lam, T* Z, int n) {
+  __shared__ double d[kLeaf + 2], e[kLeaf + 2], Zl[kLeaf][kLeaf + 3];
+  const int lane = threadIdx.x;
+  const Block bl = block_at(n, depth, blockIdx.x);
+  if (bl.id < 0) return;
+  const int s = bl.s, L = bl.m;
+  const double d0 = lane < L ? dg[s + lane] : 0.0, e0 = lane + 1 < L ? eg[s + lane] : 0.0;
+  const double amax = wave_max(fmax(fabs(d0), fabs(e0)));
+  const int ex = amax > 0.0 && amax < INFINITY ? ilogb(amax) : 0;
+  if (lane < kLeaf + 2) {
+    d[lane] = ldexp(d0, -ex);
+    e[lane] = ldexp(e0, -ex);
   }
+  if (lane < L)
+    for (int c = 0; c < L; ++c) Zl[lane][c] = (c == lane) ? 1.0 : 0.0;
   __syncthreads();
   const double eps = 1.1102230246251565e-16;
-  static_assert(kLeaf <= kWave, "one lane per off-diagonal entry of a leaf");
+  static_assert(kLeaf + 2 <= kWave, "one lane per entry of a leaf");
+  const int row = min(lane, kLeaf - 1);
   int hi = L - 1, iters = 0;
   while (hi > 0 && iters < 60 * kLeaf) {
     // lo = 1 + the last negligible e[l] below hi (0 if none): every lane
-    // tests its own entry and a ballot finds the last one
-    const bool small = lane < hi && fabs(e[lane]) <= eps * (fabs(d[lane]) + fabs(d[lane + 1]));
+    // tests its own entry and a ballot finds the last one.  (The entries of
+    // the leaf are at most 2; without the absolute term a graded leaf with a
+    // zero diagonal never deflates, its shifts underflow.)
+    const bool small = lane < hi && fabs(e[lane]) <= eps * (fabs(d[lane]) + fabs(d[lane + 1])) + 1e-140;
     const unsigned long long sm = __ballot(small);
     const int lo = sm ? 64 - __clzll(sm) : 0;
     if (lo == hi) { --hi; continue; }
@@ -111,44 +175,45 @@ __global__ __launch_bounds__(64) void leaf_kernel(const int* leaf_start, const i
     const double den = dd + copysign(sqrt(dd * dd + b2), dd);
     const double mu = (den == 0.0) ? d[hi] : d[hi] - b2 / den;
     double x = d[lo] - mu, z = e[lo];
-    // d[k] and e[k] were written by the previous step and are carried in
-    // registers; d[k+1] and e[k+1] are not touched before step k
-    double cd = d[lo], ce = e[lo];
+    double cd = d[lo], ce = z, dk1 = d[lo + 1], ek1 = e[lo + 1];
+    double qa = Zl[row][lo], qb = Zl[row][lo + 1];
     for (int k = lo; k < hi; ++k) {
-      const double dk1 = d[k + 1];
-      const double ek1 = (k + 1 < hi) ? e[k + 1] : 0.0;
-      const double r = hypot(x, z);
-      const double c = (r == 0.0) ? 1.0 : x / r;
-      const double sn = (r == 0.0) ? 0.0 : z / r;
-      const double dk = cd, ek = ce;
-      const double ekm = (k > lo) ? r : 0.0;
-      const double nd0 = c * c * dk + 2.0 * c * sn * ek + sn * sn * dk1;
-      const double nd1 = sn * sn * dk - 2.0 * c * sn * ek + c * c * dk1;
-      const double ne = c * sn * (dk1 - dk) + (c * c - sn * sn) * ek;
-      double nx = 0.0, nz = 0.0, nek1 = 0.0;
-      if (k + 1 < hi) {
-        nx = ne;
-        nz = sn * ek1;
-        nek1 = c * ek1;
+      const double dk2 = d[k + 2], ek2 = e[k + 2], qn = Zl[row][k + 2];
+      const double g = fma(x, x, z * z);
+      double r, c, sn;
+      if (g > 1e-290) {
+        const double y0 = __builtin_amdgcn_rsq(g);
+        const double er = fma(-g * y0, y0, 1.0);
+        const double y = fma(y0 * er, fma(0.375, er, 0.5), y0);
+        r = g * y;
+        c = x * y;
+        sn = z * y;
+      } else {
+        r = hypot(x, z);
+        c = (r == 0.0) ? 1.0 : x / r;
+        sn = (r == 0.0) ? 0.0 : z / r;
       }
-      cd = nd1;
-      ce = nek1;
+      // [c s; -s c] [cd ce; ce dk1] [c -s; s c]
+      const double p = fma(sn, dk1 - cd, 2.0 * c * ce);
+      const double ne = fma(c, p, -ce);
       // Every lane computed the same scalars and writes them itself, so each
       // lane's later reads depend only on its own writes (no barrier).
-      if (k > lo) e[k - 1] = ekm;
-      d[k] = nd0;
-      d[k + 1] = nd1;
-      e[k] = ne;
-      if (k + 1 < hi) e[k + 1] = nek1;
-      if (lane < L) {
-        const double qa = Zl[lane][k], qb = Zl[lane][k + 1];
-        Zl[lane][k] = c * qa + sn * qb;
-        Zl[lane][k + 1] = -sn * qa + c * qb;
-      }
-      x = nx;
-      z = nz;
+      if (k > lo) e[k - 1] = r;
+      d[k] = fma(sn, p, cd);
+      cd = fma(-sn, p, dk1);
+      Zl[row][k] = c * qa + sn * qb;
+      qa = c * qb - sn * qa;
+      const bool more = k + 1 < hi;
+      x = ne;
+      z = more ? sn * ek1 : 0.0;
+      ce = more ? c * ek1 : ne;
+      dk1 = dk2;
+      ek1 = ek2;
+      qb = qn;
     }
-    if (fabs(e[hi - 1]) <= eps * (fabs(d[hi - 1]) + fabs(d[hi]))) e[hi - 1] = 0.0;
+    d[hi] = cd;
+    e[hi - 1] = ce;
+    Zl[row][hi] = qa;
   }
   __syncthreads();
   // Ascending order: rank of eigenvalue c (ties by index).
@@ -160,9 +225,9 @@ __global__ __launch_bounds__(64) void leaf_kernel(const int* leaf_start, const i
   }
   __syncthreads();
   if (lane < L) {
-    lam[s + rank[lane]] = d[lane];
-    T* Zb = Z + blk_off(s, n);
-    for (int c = 0; c < L; ++c) Zb[lane + (int64_t)rank[c] * n] = (T)Zl[lane][c];
+    lam[s + rank[lane]] = ldexp(d[lane], ex + (depth == 0 ? exs[blockIdx.x] : 0));
+    T* Zb = Z + blk_off<kB>(s, n);
+    for (int c = 0; c < L; ++c) Zb[lane + (int64_t)rank[c] * (kB ? kBand : n)] = (T)Zl[lane][c];
   }
 }
 
@@ -170,17 +235,18 @@ __global__ __launch_bounds__(64) void leaf_kernel(const int* leaf_start, const i
 // Merge preparation: z vector, merge of the two sorted halves, deflation scan.
 // One workgroup per merge.
 
-template <typename T>
-__global__ __launch_bounds__(256) void merge_prep_kernel(const MergeDesc* md, const double* eg,
-                                                         const double* lam, const T* Z, int n,
-                                                         Meta mt) {
-  const MergeDesc g = md[blockIdx.x];
-  const int s = g.s, n1 = g.n1, m = g.m, n2 = m - n1;
+template <typename T, bool kB>
+__global__ __launch_bounds__(256) void merge_prep_kernel(int depth, const double* eg, const double* lam,
+                                                         const T* Z, int n, Meta mt) {
+  const Block g = block_at(n, depth, blockIdx.x);
+  if (!g.merge()) return;
+  const int s = g.s, n1 = g.n1(), m = g.m, n2 = m - n1;
   const double beta = eg[s + n1 - 1];
   const double sgn = beta >= 0.0 ? 1.0 : -1.0;
   const double rho = 2.0 * fabs(beta);
   const double r2 = 0.7071067811865476;
-  const T* Zg = Z + blk_off(s, n);
+  const T* Zg = Z + blk_off<kB>(s, n);
+  const int ldz = kB ? kBand : n;
   __shared__ double red[4];
   // merge-path placement of the two ascending halves
   double dmax = 0.0, zmax = 0.0;
@@ -189,14 +255,14 @@ __global__ __launch_bounds__(256) void merge_prep_kernel(const MergeDesc* md, co
     int pos;
     if (i < n1) {
       di = lam[s + i];
-      zi = r2 * (double)Zg[(n1 - 1) + (int64_t)i * n];
+      zi = r2 * (double)Zg[(n1 - 1) + (int64_t)i * ldz];
       int lo = 0, hi = n2;  // count right values < di
       while (lo < hi) { const int mid = (lo + hi) / 2; if (lam[s + n1 + mid] < di) lo = mid + 1; else hi = mid; }
       pos = i + lo;
     } else {
       const int jr = i - n1;
       di = lam[s + i];
-      zi = sgn * r2 * (double)Zg[n1 + (int64_t)i * n];
+      zi = sgn * r2 * (double)Zg[n1 + (int64_t)i * ldz];
       int lo = 0, hi = n1;  // count left values <= di
       while (lo < hi) { const int mid = (lo + hi) / 2; if (lam[s + mid] <= di) lo = mid + 1; else hi = mid; }
       pos = jr + lo;
@@ -365,19 +431,14 @@ __global__ __launch_bounds__(256) void merge_prep_kernel(const MergeDesc* md, co
   }
 }
 
-// Deflation rotations on the rows of each merge block (one thread per row).
-template <typename T>
-__global__ void merge_rot_kernel(const MergeDesc* md, int nmerge_rows, const int* row_merge,
-                                 Meta mt, T* Z, int n) {
-  const int r = blockIdx.x * blockDim.x + threadIdx.x;
-  if (r >= nmerge_rows) return;
-  const int b = row_merge[r];
-  if (b < 0) return;
-  const MergeDesc g = md[b];
-  const int nr = mt.kcnt[3 * b + 2];
-  T* Zr = Z + blk_off(g.s, n) + (r - g.s);  // row r of the merge block
+// Deflation rotations on row p of its merge block.
+template <typename T, bool kB>
+__device__ inline void merge_rot(const Block& g, int p, const Meta& mt, T* Z, int n) {
+  const int nr = mt.kcnt[3 * g.id + 2];
+  T* Zr = Z + blk_off<kB>(g.s, n) + (p - g.s);
+  const int ldz = kB ? kBand : n;
   for (int q = 0; q < nr; ++q) {
-    const int64_t ca = (int64_t)mt.rota[g.s + q] * n, cb = (int64_t)mt.rotb[g.s + q] * n;
+    const int64_t ca = (int64_t)mt.rota[g.s + q] * ldz, cb = (int64_t)mt.rotb[g.s + q] * ldz;
     const double c = mt.rotc[g.s + q], sn = mt.rots[g.s + q];
     const double x = (double)Zr[ca], y = (double)Zr[cb];
     Zr[ca] = (T)(c * x + sn * y);
@@ -406,19 +467,27 @@ __device__ inline void secular_eval(const double* dl, const double* zl, int k, i
     if (i <= j) { psi += zl[i] * w; dpsi += w * w; }
     else { phi += zl[i] * w; dphi += w * w; }
   }
-  psi = wave_sum(psi);
-  phi = wave_sum(phi);
-  dpsi = wave_sum(dpsi);
-  dphi = wave_sum(dphi);
+  psi = wsum(psi);
+  phi = wsum(phi);
+  dpsi = wsum(dpsi);
+  dphi = wsum(dphi);
 }
 
-__global__ __launch_bounds__(64) void secular_kernel(const MergeDesc* md, const int* pos_merge,
-                                                     Meta mt, int n) {
+// Workgroups from N on apply the deflation rotations, 64 rows each.
+template <typename T, bool kB>
+__global__ __launch_bounds__(64) void secular_kernel(int depth, Meta mt, int n, int N, T* Z) {
   const int w = blockIdx.x;
   const int lane = threadIdx.x;
-  const int b = pos_merge[w];
-  if (b < 0) return;
-  const MergeDesc g = md[b];
+  if (w >= N) {
+    const int p = (w - N) * 64 + lane;
+    if (p >= N) return;
+    const Block g = block_of(n, depth, p);
+    if (g.merge()) merge_rot<T, kB>(g, p, mt, Z, n);
+    return;
+  }
+  const Block g = block_of(n, depth, w);
+  if (!g.merge()) return;
+  const int b = g.id;
   const int j = w - g.s;
   const int k = mt.kcnt[3 * b];
   if (j >= k) return;
@@ -448,7 +517,7 @@ __global__ __launch_bounds__(64) void secular_kernel(const MergeDesc* md, const 
     org = k - 1;
     double zz = 0.0;
     for (int i = lane; i < k; i += kWave) zz += zl[i] * zl[i];
-    zz = wave_sum(zz);
+    zz = wsum(zz);
     lo = 0.0;
     hi = rho * zz * (1.0 + 4.0 * eps) + 1e-300;
   }
@@ -514,12 +583,11 @@ __global__ __launch_bounds__(64) void secular_kernel(const MergeDesc* md, const 
 // Gu-Eisenstat: z_i recomputed from the computed roots so that the computed
 // eigenvectors are numerically orthogonal:
 //   zhat_i^2 = (lambda_i - d_i)/rho * prod_{j != i} (lambda_j - d_i)/(d_j - d_i).
-__global__ __launch_bounds__(64) void lowner_kernel(const MergeDesc* md, const int* pos_merge,
-                                                    Meta mt, int n) {
+__global__ __launch_bounds__(64) void lowner_kernel(int depth, Meta mt, int n) {
   const int p = blockIdx.x, lane = threadIdx.x;
-  const int b = pos_merge[p];
-  if (b < 0) return;
-  const MergeDesc g = md[b];
+  const Block g = block_of(n, depth, p);
+  if (!g.merge()) return;
+  const int b = g.id;
   const int i = p - g.s;
   const int k = mt.kcnt[3 * b];
   if (i >= k) return;
@@ -541,17 +609,17 @@ __global__ __launch_bounds__(64) void lowner_kernel(const MergeDesc* md, const i
 
 // Columns of M: secular eigenvectors (normalised) and unit vectors for the
 // deflated entries, at the rank of their eigenvalue; new eigenvalue array.
-template <typename T>
-__global__ __launch_bounds__(64) void vectors_kernel(const MergeDesc* md, const int* pos_merge,
-                                                     Meta mt, T* M, double* lam_new, int n) {
+template <typename T, bool kB>
+__global__ __launch_bounds__(64) void vectors_kernel(int depth, Meta mt, const int* exs, T* M, double* lam_new,
+                                                     int n) {
   const int w = blockIdx.x, lane = threadIdx.x;
-  const int b = pos_merge[w];
-  if (b < 0) return;
-  const MergeDesc g = md[b];
+  const Block g = block_of(n, depth, w);
+  if (!g.merge()) return;
+  const int b = g.id;
   const int q = w - g.s;
   const int k = mt.kcnt[3 * b], nd = mt.kcnt[3 * b + 1];
-  T* Mb = M + (int64_t)g.s * n;  // m x m, ld m
-  const int m = g.m;
+  T* Mb = M + (int64_t)g.s * (kB ? kBand : n);  // m x m, ld m
+  const int m = g.m, ex = depth == 0 ? exs[b] : 0;
   if (q < k) {
     const int j = q;
     const double* dl = mt.dl + g.s;
@@ -562,57 +630,116 @@ __global__ __launch_bounds__(64) void vectors_kernel(const MergeDesc* md, const 
       const double v = mt.zhat[g.s + i] / ((dl[i] - dorg) - tau);
       nrm += v * v;
     }
-    nrm = sqrt(wave_sum(nrm));
+    nrm = sqrt(wsum(nrm));
     // rank among deflated values (strictly smaller)
     int lo = 0, hi = nd;
     while (lo < hi) { const int mid = (lo + hi) / 2; if (mt.defd[g.s + mid] < lj) lo = mid + 1; else hi = mid; }
-    const int col = j + lo;
+    T* col = Mb + (int64_t)(j + lo) * m;
     for (int i = lane; i < k; i += kWave) {
       const double v = mt.zhat[g.s + i] / ((dl[i] - dorg) - tau) / nrm;
-      Mb[mt.cl[g.s + i] + (int64_t)col * m] = (T)v;
+      col[mt.cl[g.s + i]] = (T)v;
     }
-    if (lane == 0) lam_new[g.s + col] = lj;
+    for (int i = lane; i < nd; i += kWave) col[mt.defc[g.s + i]] = T(0);
+    if (lane == 0) lam_new[g.s + j + lo] = ldexp(lj, ex);
   } else if (q < k + nd) {
     const int t = q - k;
     const double v = mt.defd[g.s + t];
     int lo = 0, hi = k;  // roots <= v
     while (lo < hi) { const int mid = (lo + hi) / 2; if (mt.lamr[g.s + mid] <= v) lo = mid + 1; else hi = mid; }
-    const int col = t + lo;
-    if (lane == 0) {
-      Mb[mt.defc[g.s + t] + (int64_t)col * m] = T(1);
-      lam_new[g.s + col] = v;
+    T* col = Mb + (int64_t)(t + lo) * m;
+    const int one = mt.defc[g.s + t];
+    for (int i = lane; i < m; i += kWave) col[i] = T(i == one ? 1 : 0);
+    if (lane == 0) lam_new[g.s + t + lo] = ldexp(v, ex);
+  }
+}
+
+// The products C = A M of a level, A a merge's m x m block of eigenvectors:
+// 64 x 64 tiles of every merge in one launch (max_tiles^2 workgroups for
+// each block of the level).
+// Before the deflation rotations A = diag(Z1, Z2), and a merge that rotated
+// no columns keeps that form: tiles within one half then sum over that half
+// alone.  A leaf met at this level is copied.  One product launch per merge
+// (up to 48 of 10 us at order 1531, full length for batches) was bound by
+// launches and by the chain of one 128-tile.
+template <typename T, typename TO, bool kB>
+__global__ __launch_bounds__(GTHREADS, 2) void merge_gemm_kernel(int depth, int max_tiles, Meta mt, int n,
+                                                                 const T* __restrict__ Za, const T* __restrict__ Mm,
+                                                                 TO* __restrict__ Zb, const double* lamA,
+                                                                 double* lamB) {
+  using N = Narrow<T>;
+  using M = Mfma<T>;
+  extern __shared__ __attribute__((aligned(16))) unsigned char merge_lds[];
+  const unsigned per = (unsigned)(max_tiles * max_tiles);
+  const int tile = blockIdx.x % per;
+  const Block g = block_at(n, depth, blockIdx.x / per);
+  if (g.id < 0) return;
+  const int m = g.m, t = threadIdx.x;
+  const T* A = Za + blk_off<kB>(g.s, n);
+  const int ldz = kB ? kBand : n;
+  TO* C = Zb + blk_off<false>(g.s, n);
+  if (!g.merge()) {
+    if (tile > 0) return;
+    for (int x = t; x < m * m; x += GTHREADS) C[x % m + (int64_t)(x / m) * n] = (TO)A[x % m + (int64_t)(x / m) * ldz];
+    if (t < m) lamB[g.s + t] = lamA[g.s + t];
+    return;
+  }
+  const int tiles = (m + N::NT - 1) / N::NT;
+  if (tile >= tiles * tiles) return;
+  const int mo = tile % tiles * N::NT, no = tile / tiles * N::NT;
+  int k0 = 0, k1 = m;
+  if (mt.kcnt[3 * g.id + 2] == 0) {
+    if (min(mo + N::NT, m) <= g.n1()) k1 = g.n1();
+    else if (mo >= g.n1()) k0 = g.n1();
+  }
+  constexpr int NBLK = N::NBLK;
+  typename M::acc_t acc[NBLK][NBLK];
+  const int m0 = max(0, min(mo, m - N::NT)), n0 = max(0, min(no, m - N::NT));
+  narrow_product<T, false, false>(A + (int64_t)k0 * ldz, ldz, Mm + (int64_t)g.s * (kB ? kBand : n) + k0, m, m, m, k1 - k0, m0, n0,
+                                  reinterpret_cast<T*>(merge_lds), acc);
+  const int lane = t % kWave, wave = t / kWave;
+#pragma unroll
+  for (int i = 0; i < NBLK; ++i)
+#pragma unroll
+    for (int j = 0; j < NBLK; ++j)
+#pragma unroll
+      for (int r = 0; r < M::NACC; ++r) {
+        const int gi = m0 + wave % 2 * 32 + i * M::TM + M::c_col(lane, r);
+        const int gj = n0 + wave / 2 * 32 + j * M::TN + M::c_row(lane, r);
+        if (gi >= mo && gj >= no && gi < m && gj < m) C[gi + (int64_t)gj * n] = (TO)acc[i][j][r];
+      }
+}
+
+// Concatenated float64 copies of the batch's diagonals, torn at every split of
+// the recursion (d[q-1] -= |e[q-1]| and d[q] -= |e[q-1]| at split point q);
+// the coupling at the end of every entry is zero.  Every entry is scaled by a
+// power of two (2^-ex) to entries below 2: the merges compare the poles with
+// z, which has norm 1.  One workgroup per entry.
+template <typename T>
+__global__ __launch_bounds__(1024) void tear_kernel(int n, int depth, const T* d, const T* e, int64_t sD, double* dd,
+                                                    double* ee, int* exs) {
+  __shared__ double red[1024 / kWave];
+  d += blockIdx.x * sD;
+  e += blockIdx.x * sD;
+  dd += (int64_t)blockIdx.x * n;
+  ee += (int64_t)blockIdx.x * n;
+  double mx = 0.0;
+  for (int i = threadIdx.x; i < n; i += blockDim.x)
+    mx = fmax(mx, fmax(fabs((double)d[i]), i + 1 < n ? fabs((double)e[i]) : 0.0));
+  mx = block_max(mx, red);
+  const int ex = mx > 0.0 && mx < INFINITY ? ilogb(mx) : 0;
+  if (threadIdx.x == 0) exs[blockIdx.x] = ex;
+  for (int i = threadIdx.x; i < n; i += blockDim.x) {
+    double v = ldexp((double)d[i], -ex);
+    Block bl{0, n, 0};
+    for (int l = 0; l < depth && bl.m > kLeaf; ++l) {
+      const int q = bl.s + bl.m / 2;
+      if (i == q - 1 || i == q) v -= fabs(ldexp((double)e[q - 1], -ex));
+      if (i >= q) bl = {q, bl.m - bl.m / 2, 0};
+      else bl.m /= 2;
     }
+    dd[i] = v;
+    ee[i] = (i + 1 < n) ? ldexp((double)e[i], -ex) : 0.0;
   }
-}
-
-// Concatenated float64 copies of the batch's diagonals; the coupling at the
-// end of every entry is zero.
-template <typename T>
-__global__ void cast_tridiag(int n, const T* d, const T* e, int64_t sD, double* dd, double* ee) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  const int b = blockIdx.y;
-  if (i < n) {
-    dd[(int64_t)b * n + i] = (double)d[b * sD + i];
-    ee[(int64_t)b * n + i] = (i + 1 < n) ? (double)e[b * sD + i] : 0.0;
-  }
-}
-
-// Copies the diagonal block [r0, r0+sz) of entry blockIdx.y of Za (and its
-// eigenvalues) to Zb.
-template <typename T>
-__global__ void copy_block(int n, int r0, int sz, const T* Za, T* Zb, const double* la,
-                           double* lb) {
-  const int c = r0 + blockIdx.x;
-  const int64_t zo = (int64_t)blockIdx.y * n * n;
-  for (int i = threadIdx.x; i < sz; i += blockDim.x)
-    Zb[zo + (int64_t)(r0 + i) + (int64_t)c * n] = Za[zo + (int64_t)(r0 + i) + (int64_t)c * n];
-  if (threadIdx.x == 0) lb[(int64_t)blockIdx.y * n + c] = la[(int64_t)blockIdx.y * n + c];
-}
-
-template <typename T>
-__global__ void copy_mat(int64_t cnt, const T* a, T* b) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < cnt) b[i] = a[i];
 }
 
 }  // namespace
@@ -625,206 +752,93 @@ void stedc_batched(hipStream_t st, int n, int batch, const T* d, const T* e, int
   const int64_t N64 = (int64_t)n * batch;
   if (N64 > (int64_t)1 << 30 || nn * batch > ((int64_t)1 << 40))
     throw Error{MSQRT_ERR_UNSUPPORTED, "tridiagonal eigensolver: batch too large"};
+  const size_t prep_bytes = 2 * sizeof(double) + sizeof(int);  // LDS per row of a merge
+  if (n > kLeaf && n * prep_bytes > 140 * 1024)
+    throw Error{MSQRT_ERR_UNSUPPORTED, "tridiagonal eigensolver supports n <= 7000"};
   const int N = (int)N64;
-  double* dd = w.dd.ensure<double>(N);
-  double* ee = w.ee.ensure<double>(N);
-  hipLaunchKernelGGL(cast_tridiag<T>, dim3((unsigned)ceil_div(n, 256), (unsigned)batch), dim3(256), 0,
-                     st, n, d, e, sD, dd, ee);
-  MSQRT_LAUNCH_CHECK();
-
   // Static recursion tree of one entry: halve until the pieces are at most
   // kLeaf.  Every entry has the same tree, shifted by a multiple of n.
-  std::vector<std::vector<MergeDesc>> levels;  // levels[0] = leaves' parents ... top
-  std::vector<std::pair<int, int>> cur{{0, n}};
-  std::vector<std::vector<std::pair<int, int>>> tree{cur};
-  while (true) {
-    bool split = false;
-    std::vector<std::pair<int, int>> nxt;
-    for (auto& pr : tree.back()) {
-      if (pr.second > kLeaf) {
-        const int h = pr.second / 2;
-        nxt.push_back({pr.first, h});
-        nxt.push_back({pr.first + h, pr.second - h});
-        split = true;
-      } else {
-        nxt.push_back(pr);
-      }
-    }
-    if (!split) break;
-    tree.push_back(nxt);
-  }
-  // leaves = tree.back(); merges: for level L from deepest-1 up to 0, every
-  // node of tree[L] that was split.
-  const auto& leaves = tree.back();
-  std::vector<int> lst, lsz, splits;
-  for (int b = 0; b < batch; ++b)
-    for (auto& pr : leaves) { lst.push_back(b * n + pr.first); lsz.push_back(pr.second); }
-  // Nodes of a tree level that are not split are already solved leaves; they
-  // are carried unchanged through that level's merge step.
-  std::vector<std::vector<std::pair<int, int>>> carried;
-  for (size_t li = 0; li + 1 < tree.size(); ++li) {
-    std::vector<MergeDesc> lv;
-    std::vector<std::pair<int, int>> cv;
-    for (auto& pr : tree[li]) {
-      if (pr.second > kLeaf) {
-        const int h = pr.second / 2;
-        lv.push_back({pr.first, h, pr.second});
-        for (int b = 0; b < batch; ++b) splits.push_back(b * n + pr.first + h);
-      } else {
-        cv.push_back(pr);
-      }
-    }
-    levels.push_back(lv);
-    carried.push_back(cv);
-  }
-  std::reverse(levels.begin(), levels.end());  // bottom-up
-  std::reverse(carried.begin(), carried.end());
+  int depth = 0;
+  auto largest = [&](int dep) { return (int)ceil_div(n, (int64_t)1 << dep); };
+  while (largest(depth) > kLeaf) ++depth;
 
-  // device metadata
-  const int nl = (int)lst.size();
-  int* dmeta = w.meta.ensure<int>(2 * (int64_t)nl + (int64_t)splits.size() + 4 * N64 + 8);
-  int* dlst = dmeta;
-  int* dlsz = dmeta + nl;
-  int* dspl = dmeta + 2 * nl;
-  int* pos_merge = dspl + splits.size();
-  std::vector<int> hmeta(2 * nl + splits.size());
-  std::copy(lst.begin(), lst.end(), hmeta.begin());
-  std::copy(lsz.begin(), lsz.end(), hmeta.begin() + nl);
-  std::copy(splits.begin(), splits.end(), hmeta.begin() + 2 * nl);
-  MSQRT_HIP(hipMemcpyAsync(dmeta, hmeta.data(), sizeof(int) * hmeta.size(), hipMemcpyHostToDevice, st));
-  if (!splits.empty()) {
-    hipLaunchKernelGGL(tear_kernel, dim3((unsigned)ceil_div(splits.size(), 64)), dim3(64), 0, st,
-                       (int)splits.size(), dspl, dd, ee);
+  double* dd = w.dd.ensure<double>(N);
+  double* ee = w.ee.ensure<double>(N);
+  int* ib = w.rot.ensure<int>((int64_t)10 * N + 16);
+  int* exs = ib + 9 * (int64_t)N;
+  hipLaunchKernelGGL(tear_kernel<T>, dim3((unsigned)batch), dim3(1024), 0, st, n, depth, d, e, sD, dd, ee, exs);
+  MSQRT_LAUNCH_CHECK();
+  // the last level writes Z and lam
+  T* Z2 = w.Z2.ensure<T>(nn * batch);
+  double* lam2 = w.lam.ensure<double>(N);
+  T *Za = depth % 2 ? Z2 : Z, *Zb = depth % 2 ? Z : Z2;
+  double *lamA = depth % 2 ? lam2 : lam, *lamB = depth % 2 ? lam : lam2;
+  auto leaves = [&](auto* z, auto band) {
+    using TZ = std::remove_pointer_t<decltype(z)>;
+    hipLaunchKernelGGL((leaf_kernel<TZ, decltype(band)::value>), dim3((unsigned)batch << depth), dim3(64), 0, st,
+                       depth, dd, ee, exs, lamA, z, n);
     MSQRT_LAUNCH_CHECK();
+  };
+  if (depth == 0) {
+    leaves(Za, std::false_type());
+    return;
   }
-  T* Za = Z;
-  T* Zb = w.Z2.ensure<T>(nn * batch);
   MSQRT_HIP(hipMemsetAsync(Za, 0, sizeof(T) * nn * batch, st));
   MSQRT_HIP(hipMemsetAsync(Zb, 0, sizeof(T) * nn * batch, st));
-  double* lamA = lam;
-  double* lamB = w.lam.ensure<double>(N);
-  hipLaunchKernelGGL(leaf_kernel<T>, dim3(nl), dim3(64), 0, st, dlst, dlsz, dd, ee, lamA, Za, n);
-  MSQRT_LAUNCH_CHECK();
-  if (levels.empty()) return;
 
   // metadata buffers, indexed by concatenated position (per merge: by the
-  // merge's index in its level, entry-major)
+  // block number)
   Meta mt;
   double* fb = w.roots.ensure<double>((int64_t)12 * N + 16);
-  int* ib = w.rot.ensure<int>((int64_t)10 * N + 16);
   mt.dl = fb; mt.zl = fb + N; mt.defd = fb + 2 * N; mt.rotc = fb + 3 * N; mt.rots = fb + 4 * N;
   mt.tau = fb + 5 * N; mt.lamr = fb + 6 * N; mt.zhat = fb + 7 * N; mt.tmpd = fb + 8 * N;
   mt.tmpz = fb + 9 * N; mt.rho = fb + 10 * N;
   mt.cl = ib; mt.defc = ib + N; mt.rota = ib + 2 * N; mt.rotb = ib + 3 * N; mt.org = ib + 4 * N;
   mt.tmpc = ib + 5 * N; mt.kcnt = ib + 6 * N;
-  MergeDesc* dmd = (MergeDesc*)w.zhat.ensure<int>((int64_t)3 * N + 16);
   // M: the m x m secular eigenvector block of the merge at position s sits
   // at M + s * n (ld m)
   T* M = w.M.ensure<T>(nn * batch);
-
-  static bool prep_attr[2] = {false, false};
-  if (!prep_attr[sizeof(T) == 8]) {
-    MSQRT_HIP(hipFuncSetAttribute((const void*)merge_prep_kernel<T>,
-                                  hipFuncAttributeMaxDynamicSharedMemorySize, 140 * 1024));
-    prep_attr[sizeof(T) == 8] = true;
-  }
-  std::vector<int> posm(N);
-  std::vector<MergeDesc> all;
-  for (size_t L = 0; L < levels.size(); ++L) {
-    const auto& lv = levels[L];
-    const int nm1 = (int)lv.size();
-    const int nm = nm1 * batch;
-    all.clear();
-    for (int b = 0; b < batch; ++b)
-      for (auto g : lv) { g.s += b * n; all.push_back(g); }
-    std::fill(posm.begin(), posm.end(), -1);
-    for (int b = 0; b < nm; ++b)
-      for (int i = 0; i < all[b].m; ++i) posm[all[b].s + i] = b;
-    MSQRT_HIP(hipMemcpyAsync(dmd, all.data(), sizeof(MergeDesc) * nm, hipMemcpyHostToDevice, st));
-    MSQRT_HIP(hipMemcpyAsync(pos_merge, posm.data(), sizeof(int) * N, hipMemcpyHostToDevice, st));
-    int mmax = 0;
-    for (auto& g : lv) mmax = std::max(mmax, g.m);
-    const size_t prep_lds = (size_t)mmax * (2 * sizeof(double) + sizeof(int));
-    if (prep_lds > 140 * 1024) throw Error{MSQRT_ERR_UNSUPPORTED, "tridiagonal eigensolver supports n <= 7000"};
-    hipLaunchKernelGGL(merge_prep_kernel<T>, dim3(nm), dim3(256), prep_lds, st, dmd, ee, lamA, Za, n, mt);
+  // A level: from eigenvectors za (in a band or not) to zb.
+  auto level = [&](int dep, auto* za, auto* mm, auto* zb, auto band) {
+    using TZ = std::remove_pointer_t<decltype(za)>;
+    using TO = std::remove_pointer_t<decltype(zb)>;
+    constexpr bool kB = decltype(band)::value;
+    const unsigned nb = (unsigned)batch << dep;
+    const int mmax = largest(dep);
+    gemm_lds_attr(merge_prep_kernel<TZ, kB>, 140 * 1024);
+    hipLaunchKernelGGL((merge_prep_kernel<TZ, kB>), dim3(nb), dim3(256), mmax * prep_bytes, st, dep, ee, lamA,
+                       (const TZ*)za, n, mt);
     MSQRT_LAUNCH_CHECK();
-    hipLaunchKernelGGL(merge_rot_kernel<T>, dim3((unsigned)ceil_div(N, 256)), dim3(256), 0, st, dmd, N,
-                       pos_merge, mt, Za, n);
+    hipLaunchKernelGGL((secular_kernel<TZ, kB>), dim3((unsigned)(N + ceil_div(N, 64))), dim3(64), 0, st, dep, mt, n, N,
+                       za);
     MSQRT_LAUNCH_CHECK();
-    hipLaunchKernelGGL(secular_kernel, dim3(N), dim3(64), 0, st, dmd, pos_merge, mt, n);
+    hipLaunchKernelGGL(lowner_kernel, dim3(N), dim3(64), 0, st, dep, mt, n);
     MSQRT_LAUNCH_CHECK();
-    hipLaunchKernelGGL(lowner_kernel, dim3(N), dim3(64), 0, st, dmd, pos_merge, mt, n);
+    hipLaunchKernelGGL((vectors_kernel<TZ, kB>), dim3(N), dim3(64), 0, st, dep, mt, exs, mm, lamB, n);
     MSQRT_LAUNCH_CHECK();
-    MSQRT_HIP(hipMemsetAsync(M, 0, sizeof(T) * nn * batch, st));
-    hipLaunchKernelGGL(vectors_kernel<T>, dim3(N), dim3(64), 0, st, dmd, pos_merge, mt, M, lamB, n);
+    const int tiles = (int)ceil_div(mmax, Narrow<TZ>::NT);
+    gemm_lds_attr(merge_gemm_kernel<TZ, TO, kB>, Narrow<TZ>::kLds);
+    hipLaunchKernelGGL((merge_gemm_kernel<TZ, TO, kB>), dim3(nb * tiles * tiles), dim3(GTHREADS), Narrow<TZ>::kLds, st,
+                       dep, tiles, mt, n, (const TZ*)za, (const TZ*)mm, zb, (const double*)lamA, lamB);
     MSQRT_LAUNCH_CHECK();
-    // C = A M for each merge, A the merge's m x m block of eigenvectors, M its
-    // secular block.  Before the deflation rotations A = diag(Z1, Z2); a
-    // level whose merges rotated no pair of columns keeps that structure, and
-    // the product splits into Z1 M(0:n1, :) and Z2 M(n1:m, :) (half the
-    // flops).  For a single matrix the rotation counts come to the host once
-    // per level; after a rotation the level forms the full products.  (A
-    // batch nearly always has a rotation in some entry at every level, so it
-    // skips the read and its host synchronisation: for 64 x n = 512 the
-    // eigensolver measured 2.49 ms without the read and 2.67 ms with it.)
-    bool halves = false;
-    if (batch == 1) {
-      std::vector<int> kc(3 * (size_t)nm);
-      MSQRT_HIP(hipMemcpyAsync(kc.data(), mt.kcnt, sizeof(int) * kc.size(), hipMemcpyDeviceToHost, st));
-      MSQRT_HIP(hipStreamSynchronize(st));
-      halves = true;
-      for (int b = 0; b < nm && halves; ++b) halves = kc[3 * b + 2] == 0;
-    }
-    auto gemm = [&](int Mr, int Nc, int Kk, const T* A_, int64_t sA_, const T* B_, int ldb_, int64_t sB_,
-                    T* C_, int64_t sC_, int nb_) {
-      if (std::is_same<T, float>::value)
-        gemm_store_f32(st, false, false, Mr, Nc, Kk, (const float*)A_, n, sA_, (const float*)B_, ldb_, sB_,
-                       (float*)C_, n, sC_, 1.f, 0.f, nb_, false);
-      else
-        gemm_store_f64(st, false, false, Mr, Nc, Kk, (const double*)A_, n, sA_, (const double*)B_, ldb_,
-                       sB_, (double*)C_, n, sC_, 1.0, 0.0, nb_, false);
-    };
-    auto merge_product = [&](const MergeDesc& g, const T* Ablk, int64_t sA_, const T* Mb, int64_t sM_,
-                             T* Cblk, int64_t sC_, int nb_) {
-      if (halves) {
-        const int n1 = g.n1, n2 = g.m - g.n1;
-        if (n1 > 0) gemm(n1, g.m, n1, Ablk, sA_, Mb, g.m, sM_, Cblk, sC_, nb_);
-        if (n2 > 0)
-          gemm(n2, g.m, n2, Ablk + blk_off(n1, n), sA_, Mb + n1, g.m, sM_, Cblk + n1, sC_, nb_);
-      } else {
-        gemm(g.m, g.m, g.m, Ablk, sA_, Mb, g.m, sM_, Cblk, sC_, nb_);
-      }
-    };
-    // One product per merge of the level, batched over the entries; a single
-    // entry whose merges are equal and adjacent (n a power of two times the
-    // leaf size) takes the whole level as one batch instead.
-    bool uniform = batch == 1 && nm1 > 1;
-    for (int b = 1; b < nm1 && uniform; ++b)
-      uniform = lv[b].m == lv[0].m && lv[b].n1 == lv[0].n1 && lv[b].s == lv[0].s + b * lv[0].m;
-    if (uniform) {
-      const MergeDesc& g = lv[0];
-      const int64_t sBlk = (int64_t)g.m * (n + 1), sM = (int64_t)g.m * n;
-      merge_product(g, Za + blk_off(g.s, n), sBlk, M + (int64_t)g.s * n, sM, Zb + blk_off(g.s, n), sBlk, nm1);
-    }
-    for (int b = 0; b < nm1 && !uniform; ++b) {
-      const MergeDesc& g = lv[b];
-      merge_product(g, Za + blk_off(g.s, n), nn, M + (int64_t)g.s * n, nn, Zb + blk_off(g.s, n), nn, batch);
-    }
-    for (auto& pr : carried[L]) {
-      hipLaunchKernelGGL(copy_block<T>, dim3((unsigned)pr.second, (unsigned)batch), dim3(64), 0, st, n,
-                         pr.first, pr.second, (const T*)Za, Zb, (const double*)lamA, lamB);
-      MSQRT_LAUNCH_CHECK();
-    }
-    std::swap(Za, Zb);
     std::swap(lamA, lamB);
+  };
+  int dep = depth - 1;
+  if constexpr (sizeof(T) == 4) {
+    // the first level in float64, its result rounded to float
+    double* zd = w.band.ensure<double>((int64_t)2 * N * (kBand + 1));
+    MSQRT_HIP(hipMemsetAsync(zd, 0, sizeof(double) * N * (kBand + 1), st));
+    leaves(zd, std::true_type());
+    level(dep, zd, zd + (int64_t)N * (kBand + 1), Zb, std::true_type());
+    std::swap(Za, Zb);
+    --dep;
+  } else {
+    leaves(Za, std::false_type());
   }
-  if (Za != Z) {
-    const int64_t cnt = nn * batch;
-    hipLaunchKernelGGL(copy_mat<T>, dim3((unsigned)ceil_div(cnt, 256)), dim3(256), 0, st, cnt,
-                       (const T*)Za, Z);
-    MSQRT_LAUNCH_CHECK();
+  for (; dep >= 0; --dep) {
+    level(dep, Za, M, Zb, std::false_type());
+    std::swap(Za, Zb);
   }
-  if (lamA != lam) MSQRT_HIP(hipMemcpyAsync(lam, lamA, sizeof(double) * N, hipMemcpyDeviceToDevice, st));
 }
 
 template <typename T>

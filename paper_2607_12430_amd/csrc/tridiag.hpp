@@ -12,7 +12,7 @@ struct SytrdWork {
 };
 
 struct StedcWork {
-  DevBuf dd, ee, lam, Z2, M, meta, rot, roots, zhat, scal;
+  DevBuf dd, ee, lam, Z2, M, band, rot, roots;
 };
 
 struct OrmtrWork {
