@@ -1,6 +1,7 @@
 // Exchange between the co-resident workgroups of a cooperative launch: coherent
-// loads and stores, fixed-order wavefront sums by DPP, and a two-level grid
-// barrier (the panel kernels of the tridiagonal and Hessenberg reductions).
+// loads and stores, fixed-order wavefront sums by DPP, values tagged with the
+// step they belong to, and a two-level grid barrier (the panel kernels of the
+// tridiagonal and Hessenberg reductions).
 #pragma once
 
 #include "common.hpp"
@@ -74,6 +75,54 @@ __device__ inline V wsum(V v) {
   v += dpp_v<0x141>(v);  // row_half_mirror
   v += dpp_v<0x140>(v);  // row_mirror
   return (lane_of(v, 0) + lane_of(v, 16)) + (lane_of(v, 32) + lane_of(v, 48));
+}
+
+// Tagged exchange: a value goes out as 64-bit words of 32 bits of it and a
+// 32-bit tag (the number of the step it belongs to), each written and read
+// whole, so a reader that finds the tag has the value: the read is the wait,
+// and no store is waited for.  A step's words may be overwritten once every
+// workgroup is known to have finished reading them.
+typedef unsigned long long tword;
+template <typename T>
+constexpr int kTagW = (int)sizeof(T) / 4;  // words per value
+__device__ inline void tag_store(tword* p, float v, unsigned tag) {
+  cstore(p, (tword)tag << 32 | __float_as_uint(v));
+}
+__device__ inline void tag_store(tword* p, double v, unsigned tag) {
+  const unsigned long long b = (unsigned long long)__double_as_longlong(v);
+  cstore(p, (tword)tag << 32 | (unsigned)b);
+  cstore(p + 1, (tword)tag << 32 | (unsigned)(b >> 32));
+}
+template <typename T>
+__device__ inline T tag_value(const tword* w) {
+  if constexpr (sizeof(T) == 4) return __uint_as_float((unsigned)w[0]);
+  else return __longlong_as_double((long long)((unsigned long long)(unsigned)w[1] << 32 | (unsigned)w[0]));
+}
+// Word at a workgroup-uniform base plus a byte offset of the thread's own.
+__device__ inline tword tag_word(const tword* base, unsigned bytes) {
+  return cload(reinterpret_cast<const tword*>(reinterpret_cast<const char*>(base) + bytes));
+}
+// Reads the words load(0 .. N - 1) until all carry the tag in all lanes (a loop
+// that lanes leave one by one doubles its registers).  A spin limit keeps a
+// broken launch from hanging: it raises the sticky failure flag.
+template <int N, class Load>
+__device__ __forceinline__ void tag_load(tword (&w)[N], Load load, unsigned tag, unsigned* fail) {
+  unsigned spins = 0;
+  while (true) {
+    bool miss = false;
+#pragma unroll
+    for (int k = 0; k < N; ++k) w[k] = load(k);
+#pragma unroll
+    for (int k = 0; k < N; ++k) miss = miss || (unsigned)(w[k] >> 32) != tag;
+    if (__ballot(miss) == 0) return;
+    if ((++spins & 255u) == 0u) {
+      if (__ballot(cload(fail) != 0u) != 0) return;
+      if (spins > (1u << 21)) {
+        cstore(fail, 1u);
+        return;
+      }
+    }
+  }
 }
 
 // Grid barrier state of one batch entry (unsigned words): the top counter,

@@ -4,25 +4,36 @@
 // The trailing matrix lives in registers, one lower-triangular tile per
 // workgroup of a cooperative launch, and is updated there at every column
 // (A -= v w^T + w v^T, summed apart and flushed every kFlush
-// columns), with ONE grid barrier per column.  For column j with
+// columns), with ONE exchange per column.  For column j with
 // sub-column u (rows j+1..n-1) the reflector is v = (u - beta e1) c, c =
 // 1/(alpha - beta).  Everything the column needs from v is linear in v, so
-// before the barrier each workgroup forms its tile's share of the product
+// before the exchange each workgroup forms its tile's share of the product
 // with the *unnormalised* u (A u and, off the diagonal, A^T u), its share of
 // u^T A u and ||u||^2, and publishes column j+1 of its tile.  After the
-// barrier every workgroup finishes the scalars, y = A v, w = tau y -
+// exchange every workgroup finishes the scalars, y = A v, w = tau y -
 // (tau/2)(tau y^T v) v and the next column u' = A(:, j+1) - v w_{j+1} - w for
 // the rows of its tile, and updates the tile.  A launch reduces kLaunchCols
 // columns, then writes its tiles back; the next one cuts the smaller trailing
 // matrix anew.  The last kTailRows rows take one workgroup (sytrd_tail_kernel).
 //
-// What bounds it: the latency of a column, about 2 us for the barrier, 1 us
-// for the gather and the instructions of product, row work and update.
-// (A blocked panel that left the matrix alone for 32 columns and corrected
-// every column with V and W spent 9.3 us per column at n = 1531 and 9.8 at
-// n = 4096: its row corrections, V^T u, W^T u and their exchange cost more than
-// the update of the register tile.  Now 4.8 and 6.2 us, 14.3 -> 7.3 ms and
-// 40.2 -> 25.3 ms, with an X_0 that is 5 % closer to the root.)
+// The exchange.  Small tiles (kTag): every word carries its column number, so
+// the reads that gather it are the wait; the scalars from every workgroup
+// also say that all have read the words of the column before, whose buffer
+// the next column takes.  Words go out twice as wide and are read again until
+// they are there, so larger tiles, which read more, exchange plain values
+// around a grid barrier.  Measured with tags and with the barrier: n = 1000
+// 3.4 and 4.2 ms, n = 1531 6.3 and 7.2 (64-row tiles); n = 4096, whose first
+// launches have 192- and 128-row tiles, 26.3 and 23.7.  Each workgroup's
+// scalars have a 64-byte line of their own: packed together they took 0.4 ms
+// longer at n = 1000.
+//
+// What bounds it: the latency of a column, 4.3 us at n = 1531, of which the
+// exchange is about half and the instructions of product, row work and update
+// the rest.  (A blocked panel that left the matrix alone for 32 columns and
+// corrected every column with V and W spent 9.3 us per column at n = 1531 and
+// 9.8 at n = 4096: its row corrections, V^T u, W^T u and their exchange cost
+// more than the update of the register tile.  Now 4.3 and 5.8 us, 14.3 -> 6.3
+// ms and 40.2 -> 23.7 ms, with an X_0 that is 5 % closer to the root.)
 #include <algorithm>
 #include <vector>
 
@@ -39,7 +50,7 @@ constexpr int kTRMax = 22;    // max tiles per dimension: 253 workgroups, one pe
 constexpr int kGMax = kTRMax * (kTRMax + 1) / 2;
 constexpr int kMaxTs = 256;   // largest tile
 constexpr int kMaxN = kTRMax * 192 + 1;  // largest order
-constexpr int kLaunchCols = 128;  // n = 4096: 27.6, 26.0, 25.3, 25.0 ms for 32, 64, 128, 256 (without kDelta)
+constexpr int kLaunchCols = 128;  // n = 4096: 27.6, 26.0, 25.3, 25.0 ms for 32, 64, 128, 256 (without kDelta and tags)
 constexpr int kFlush = 32;    // columns between flushes of the accumulated updates
 
 // How the panel kernel is built for tiles of 64 RPL rows: threads, and whether
@@ -47,17 +58,17 @@ constexpr int kFlush = 32;    // columns between flushes of the accumulated upda
 // per column instead of one per kFlush columns doubled the error of X_0 at
 // n = 4096 (kappa = 1e4: 1.9e-6 to 4.0e-6; 15 % at n = 500), so the updates
 // are summed apart wherever the registers hold both: 1024 threads have 128
-// registers each, 512 have 256.
+// registers each, 512 have 256.  kTag: the exchange is by tagged words.
 template <typename T, int RPL>
 struct Tile;
-template <> struct Tile<float, 1> { static constexpr int NT = 1024; static constexpr bool kDelta = true; };
-template <> struct Tile<float, 2> { static constexpr int NT = 1024; static constexpr bool kDelta = true; };
-template <> struct Tile<float, 3> { static constexpr int NT = 512; static constexpr bool kDelta = true; };
-template <> struct Tile<float, 4> { static constexpr int NT = 1024; static constexpr bool kDelta = false; };
-template <> struct Tile<double, 1> { static constexpr int NT = 1024; static constexpr bool kDelta = true; };
-template <> struct Tile<double, 2> { static constexpr int NT = 512; static constexpr bool kDelta = true; };
-template <> struct Tile<double, 3> { static constexpr int NT = 512; static constexpr bool kDelta = false; };
-template <> struct Tile<double, 4> { static constexpr int NT = 1024; static constexpr bool kDelta = false; };
+template <> struct Tile<float, 1> { static constexpr int NT = 1024; static constexpr bool kDelta = true; static constexpr bool kTag = true; };
+template <> struct Tile<float, 2> { static constexpr int NT = 1024; static constexpr bool kDelta = true; static constexpr bool kTag = false; };
+template <> struct Tile<float, 3> { static constexpr int NT = 512; static constexpr bool kDelta = true; static constexpr bool kTag = false; };
+template <> struct Tile<float, 4> { static constexpr int NT = 1024; static constexpr bool kDelta = false; static constexpr bool kTag = false; };
+template <> struct Tile<double, 1> { static constexpr int NT = 1024; static constexpr bool kDelta = true; static constexpr bool kTag = true; };
+template <> struct Tile<double, 2> { static constexpr int NT = 512; static constexpr bool kDelta = true; static constexpr bool kTag = false; };
+template <> struct Tile<double, 3> { static constexpr int NT = 512; static constexpr bool kDelta = false; static constexpr bool kTag = false; };
+template <> struct Tile<double, 4> { static constexpr int NT = 1024; static constexpr bool kDelta = false; static constexpr bool kTag = false; };
 
 template <typename T>
 struct PanelArgs {
@@ -67,13 +78,29 @@ struct PanelArgs {
   T* d;
   T* e;
   T* tau;
-  T* ypart;      // [2][TR][n] partial products
-  T* colb;       // [2][n] column j + 1, then [2] alpha
-  double* sp;    // [2][G][8] per wave of the rows of I: u^T A u, then ||u||^2
-  unsigned* bar;
+  // the exchanged words (tag: column + 1) of batch entry 0; sX per entry
+  tword* x;
+  unsigned* bar;  // barrier words of batch entry 0; the failure flag is among them
   BarrierBase bar_base;
   // batch entry b = blockIdx.y: every pointer above advances by b strides
-  int64_t sA, sD, sYP, sCB, sSP, sBar;
+  int64_t sA, sD, sX;
+};
+
+// The exchanged words of one entry, two buffers (column parity): partial
+// products [TR][n], column j + 1 [n], alpha; u^T A u per workgroup and wave of
+// the rows of I, ||u||^2 per diagonal workgroup and wave.
+template <typename T>
+struct Exchange {
+  static constexpr int W = kTagW<T>;
+  int64_t yp, cl, al, s0, s1, size;  // offsets in a buffer
+  __host__ __device__ Exchange(int n, int TR) {
+    yp = 0;
+    cl = (int64_t)TR * n * W;
+    al = cl + (int64_t)n * W;
+    s0 = al + W;
+    s1 = s0 + (int64_t)TR * (TR + 1) / 2 * 8;  // up to 4 doubles of 2 words
+    size = s1 + (int64_t)TR * 8;
+  }
 };
 
 // a + b after the halves (the rows of 16 lanes) of the wave have been exchanged:
@@ -127,10 +154,10 @@ __global__ __launch_bounds__((Tile<T, RPL>::NT)) void sytrd_panel_kernel(PanelAr
   constexpr bool kDelta = Tile<T, RPL>::kDelta;
   constexpr int TS = kWave * RPL, CW = TS / NW, CQ = CW / 4;  // tile size, columns per wave and lane row
   // Row work of a column: rows of I on threads [0, TS), rows of K on
-  // [NT / 2, NT / 2 + TS); the partial sums of the scalars beside or on the
-  // rows of I; the pivot row on kPivT.
-  constexpr int kKT = NT / 2, kScT = NT == 1024 ? 256 : 0, kPivT = NT == 1024 ? 768 : NT - 1;
-  static_assert(TS <= kKT && kKT + TS <= kPivT && kScT + kGMax <= kKT, "thread ranges");
+  // [NT / 2, NT / 2 + TS); the partial sums of the scalars of kScN workgroups
+  // per thread on the waves between them; the pivot row on kPivT.
+  constexpr int kKT = NT / 2, kScN = NT == 1024 ? 1 : 2, kPivT = NT == 1024 ? 768 : NT - 1;
+  static_assert(NT == 1024 ? TS <= 256 : NT == 512 && TS <= 192, "thread ranges");
   const int n = a.n, TR = a.TR, G = TR * (TR + 1) / 2;
   // workgroup (x, y) = (tile, batch entry); both ids and all that is derived
   // from them are scalar
@@ -140,10 +167,8 @@ __global__ __launch_bounds__((Tile<T, RPL>::NT)) void sytrd_panel_kernel(PanelAr
     a.d += bz * a.sD;
     a.e += bz * a.sD;
     a.tau += bz * a.sD;
-    a.ypart += bz * a.sYP;
-    a.colb += bz * a.sCB;
-    a.sp += bz * a.sSP;
-    a.bar += bz * a.sBar;
+    a.x += bz * a.sX;
+    a.bar += bz * kBarWords;
   }
   const int blk = blockIdx.x;
   // tile (bi, bj) of the lower triangle, row-major: bi (bi + 1) / 2 <= blk
@@ -155,6 +180,11 @@ __global__ __launch_bounds__((Tile<T, RPL>::NT)) void sytrd_panel_kernel(PanelAr
 #pragma unroll
   for (int g = 0; g < 8; ++g)
     if (g == (blk & 7)) sub_base = a.bar_base.sub[g];
+  unsigned* const fail = a.bar + kBarFail;
+  const Exchange<T> ex(n, TR);
+  constexpr int W = Exchange<T>::W;
+  constexpr bool kTag = Tile<T, RPL>::kTag;
+  constexpr int kCh = sizeof(T) == 8 ? 6 : 8;  // partial products read at a time
   const int p = a.p;
   const int I0 = p + bi * a.ts, nI = max(0, min(n - I0, a.ts));
   const int K0 = p + bj * a.ts, nK = max(0, min(n - K0, a.ts));
@@ -185,12 +215,17 @@ __global__ __launch_bounds__((Tile<T, RPL>::NT)) void sytrd_panel_kernel(PanelAr
   if (tid < TS) uI[tid] = (rowI && I0 + tid > p) ? A[I0 + tid + (unsigned)p * ld] : T(0);
   if (tid >= kKT && tid - kKT < TS) uK[tid - kKT] = (tid - kKT < nK && K0 + tid - kKT > p) ? A[K0 + tid - kKT + (unsigned)p * ld] : T(0);
   if (p == 0 && blk == 0 && tid == 0) a.d[0] = A[0];
+  if (tid < 8) red[tid / 4][tid % 4] = 0.0;
   __syncthreads();
 
   for (int jj = 0; jj < a.nc; ++jj) {
     const int j = p + jj, buf = jj & 1;
-    T* yp = a.ypart + (unsigned)(buf * TR) * n;
-    T* cl = a.colb + buf * n;
+    const unsigned tag = (unsigned)j + 1u;
+    tword* const xb = a.x + buf * ex.size;
+    tword* const yp = xb + ex.yp;
+    tword* const cl = xb + ex.cl;
+    T* const yv = reinterpret_cast<T*>(yp);  // the same without tags
+    T* const cv = reinterpret_cast<T*>(cl);
     // column j + 1 as it is before this column's update
     const int kc = j + 1 - K0 - cb;
     if (kc >= 0 && kc < CW && j + 1 - K0 < nK) {
@@ -200,7 +235,10 @@ __global__ __launch_bounds__((Tile<T, RPL>::NT)) void sytrd_panel_kernel(PanelAr
 #pragma unroll
           for (int q = 0; q < RPL; ++q) {
             const int r = lane + q * kWave;
-            if (r < nI && I0 + r >= j + 1) cstore(cl + I0 + r, entry(c, q));
+            if (r < nI && I0 + r >= j + 1) {
+              if constexpr (kTag) tag_store(cl + (unsigned)(I0 + r) * W, entry(c, q), tag);
+              else cstore(cv + I0 + r, entry(c, q));
+            }
           }
         }
     }
@@ -241,61 +279,116 @@ __global__ __launch_bounds__((Tile<T, RPL>::NT)) void sytrd_panel_kernel(PanelAr
       }
     }
     __syncthreads();
+    double s0 = 0.0, s1 = 0.0;
     if (tid < TS) {
       T z = T(0);
 #pragma unroll
       for (int w = 0; w < NW; ++w) z += zred[w][tid];
       const double u = (double)uI[tid];
-      if (rowI) cstore(yp + (unsigned)bj * n + I0 + tid, z);
-      double s0 = wsum(u * (double)z);
-      const double s1 = diag ? wsum(I0 + tid >= j + 2 ? u * u : 0.0) : 0.0;
+      if (rowI) {
+        if constexpr (kTag) tag_store(yp + ((unsigned)bj * n + I0 + tid) * W, z, tag);
+        else cstore(yv + (unsigned)bj * n + I0 + tid, z);
+      }
+      s0 = wsum(u * (double)z);
+      s1 = diag ? wsum(I0 + tid >= j + 2 ? u * u : 0.0) : 0.0;
       if (offdiag) s0 *= 2.0;
+      if (diag && rowI && I0 + tid == j + 1) tag_store(xb + ex.al, uI[tid], tag);
       if (lane == 0) {
-        double* sp = a.sp + ((unsigned)buf * G + blk) * 8 + wave;
-        cstore(sp, s0);
-        cstore(sp + 4, s1);
+        tword* const p0 = xb + ex.s0 + 8 * blk + 2 * wave;
+        tword* const p1 = xb + ex.s1 + 8 * bi + 2 * wave;
+        if constexpr (kTag) {
+          tag_store(p0, s0, tag);
+          if (diag) tag_store(p1, s1, tag);
+        } else {
+          cstore(reinterpret_cast<double*>(p0), s0);
+          if (diag) cstore(reinterpret_cast<double*>(p1), s1);
+        }
       }
-      if (diag && rowI && I0 + tid == j + 1) cstore(a.colb + 2 * n + buf, uI[tid]);
     } else if (rowK) {
-      cstore(yp + (unsigned)bi * n + K0 + (tid - kKT), zK[tid - kKT]);
+      if constexpr (kTag) tag_store(yp + ((unsigned)bi * n + K0 + (tid - kKT)) * W, zK[tid - kKT], tag);
+      else cstore(yv + (unsigned)bi * n + K0 + (tid - kKT), zK[tid - kKT]);
     }
-    grid_barrier<NT>(a.bar, a.bar_base, sub_base, blk, G, jj + 1);
-    // gather: all loads of a thread are in flight together
-    auto rowsum = [&](int i) -> T {
-      T t[kTRMax];
-#pragma unroll
-      for (int b = 0; b < kTRMax; ++b) t[b] = (b < TR) ? cload(yp + (unsigned)b * n + i) : T(0);
-      T z = T(0);
-#pragma unroll
-      for (int b = 0; b < kTRMax; ++b) z += t[b];
-      return z;
-    };
-    double g[8];
-    const bool sums = tid >= kScT && tid < kScT + 256;
-    if (sums) {
-      const int b = tid - kScT;
-#pragma unroll
-      for (int w = 0; w < 8; ++w) g[w] = (b < G && (w & 3) < RPL) ? cload(a.sp + ((unsigned)buf * G + b) * 8 + w) : 0.0;
-    }
-    T y = T(0), a1 = T(0);
-    const int row = rowI ? I0 + tid : (rowK ? K0 + tid - kKT : 0);
+    if constexpr (!kTag) grid_barrier<NT>(a.bar, a.bar_base, sub_base, blk, G, jj + 1);
+    // gather: all words of a thread are in flight together
+    const bool pivot = tid == kPivT;
+    const bool sums = NT == 1024 ? tid >= 256 && tid < 512 : (tid & 255) >= 192;
+    const int swave = NT == 1024 ? wave - 4 : wave / 4, sidx = swave * kWave + lane;
+    const int row = pivot ? j + 1 : rowI ? I0 + tid : (rowK ? K0 + tid - kKT : 0);
     const bool live = (rowI || rowK) && row >= j + 1;
-    if (live) {
-      a1 = cload(cl + row);
-      y = rowsum(row);
-    }
-    if (sums) {
-      const double s0 = wsum((g[0] + g[1]) + (g[2] + g[3])), s1 = wsum((g[4] + g[5]) + (g[6] + g[7]));
-      if (lane == 0) {
-        red[0][wave - kScT / kWave] = s0;
-        red[1][wave - kScT / kWave] = s1;
+    T y = T(0), a1 = T(0);
+    if (kTag && (live || pivot)) {
+      const unsigned stride = 8u * W * (unsigned)n;
+      unsigned ro = 8u * W * (unsigned)row;
+      asm volatile("" : "+v"(ro));  // the words' offsets are not kept over the columns
+      {
+        tword w[kCh * W + W];
+        auto load = [&](int k) {
+          if (k >= kCh * W) return tag_word(cl, ro + 8u * (k - kCh * W));
+          return k / W < TR ? tag_word(yp, ro + (unsigned)(k / W) * stride + 8u * (k % W)) : (tword)tag << 32;
+        };
+        tag_load(w, load, tag, fail);
+#pragma unroll
+        for (int b = 0; b < kCh; ++b) y += tag_value<T>(w + b * W);
+        a1 = tag_value<T>(w + kCh * W);
+      }
+      for (int b0 = kCh; b0 < TR; b0 += kCh) {
+        tword w[kCh * W];
+        auto load = [&](int k) {
+          return b0 + k / W < TR ? tag_word(yp, ro + (unsigned)(b0 + k / W) * stride + 8u * (k % W)) : (tword)tag << 32;
+        };
+        tag_load(w, load, tag, fail);
+#pragma unroll
+        for (int b = 0; b < kCh; ++b) y += tag_value<T>(w + b * W);
       }
     }
-    if (tid == kPivT) {
-      const T al = cload(a.colb + 2 * n + buf), a11 = cload(cl + j + 1);
-      piv[1] = rowsum(j + 1);
-      piv[0] = al;
-      piv[2] = a11;
+    if constexpr (!kTag) {
+      if (live || pivot) {
+        T t[kTRMax];
+#pragma unroll
+        for (int b = 0; b < kTRMax; ++b) t[b] = b < TR ? cload(yv + (unsigned)b * n + row) : T(0);
+        a1 = cload(cv + row);
+#pragma unroll
+        for (int b = 0; b < kTRMax; ++b) y += t[b];
+      }
+    }
+    if (sums) {
+      // the waves' sums of workgroup b (s0) and of diagonal workgroup b (s1)
+      auto gather = [&](const tword* base, int b) {
+        double g[RPL], s = 0.0;
+        if constexpr (kTag) {
+          tword w[2 * RPL];
+          tag_load(w, [&](int k) { return tag_word(base, 64u * b + 8u * k); }, tag, fail);
+#pragma unroll
+          for (int q = 0; q < RPL; ++q) g[q] = tag_value<double>(w + 2 * q);
+        } else {
+#pragma unroll
+          for (int q = 0; q < RPL; ++q) g[q] = cload(reinterpret_cast<const double*>(base + 8 * b + 2 * q));
+        }
+#pragma unroll
+        for (int q = 0; q < RPL; ++q) s += g[q];
+        return s;
+      };
+      s0 = s1 = 0.0;
+#pragma unroll
+      for (int h = 0; h < kScN; ++h) {
+        const int b = sidx + h * (kGMax / kScN + 1);
+        if (b < G && !pivot) s0 += gather(xb + ex.s0, b);
+      }
+      if (sidx < TR && !pivot) s1 = gather(xb + ex.s1, sidx);
+      s0 = wsum(s0);
+      s1 = wsum(s1);
+      if (lane == 0) {
+        red[0][swave] = s0;
+        red[1][swave] = s1;
+      }
+    }
+    if (pivot) {
+      tword w[W];
+      auto load = [&](int k) { return tag_word(xb + ex.al, 8u * k); };
+      tag_load(w, load, tag, fail);
+      piv[0] = tag_value<T>(w);
+      piv[1] = y;
+      piv[2] = a1;
     }
     __syncthreads();
     // v, w and the next u on the rows of the tile (the same values for a row
@@ -580,18 +673,17 @@ void sytrd_batched(hipStream_t st, int n, int batch, T* A, int64_t sA, T* d, T* 
   }
   if (n > sytrd_max_n())
     throw Error{MSQRT_ERR_UNSUPPORTED, "tridiagonal reduction supports n <= 4225 in this build"};
-  w.nbar = n > kTailRows<T> ? batch : 0;  // entries whose grid barrier is used
+  w.nbar = n > kTailRows<T> ? batch : 0;  // entries that exchange words
   if (w.nbar == 0) {
     launch_tail<T>(st, n, 0, batch, A, sA, d, e, tau, sD);
     return;
   }
-  const int64_t sYP = (int64_t)2 * kTRMax * n, sCB = 2 * (int64_t)n + 2, sSP = (int64_t)2 * kGMax * 8,
-                sBar = kBarWords;
-  T* ypart = w.ypart.ensure<T>(sYP * batch);
-  T* colb = w.colb.ensure<T>(sCB * batch);
-  double* sp = w.sp.ensure<double>(sSP * batch);
-  unsigned* bar = w.bar.ensure<unsigned>(sBar * batch);
-  MSQRT_HIP(hipMemsetAsync(bar, 0, sizeof(unsigned) * (size_t)(sBar * batch), st));
+  const int64_t sX = 2 * Exchange<T>(n, kTRMax).size;
+  tword* x = w.x.ensure<tword>(sX * batch);
+  unsigned* bar = w.bar.ensure<unsigned>((int64_t)kBarWords * batch);
+  // no word carries a tag yet
+  MSQRT_HIP(hipMemsetAsync(x, 0, sizeof(tword) * (size_t)(sX * batch), st));
+  MSQRT_HIP(hipMemsetAsync(bar, 0, sizeof(unsigned) * (size_t)kBarWords * batch, st));
   BarrierBase bar_base{};
   int p = 0;
   while (n - p > kTailRows<T>) {
@@ -600,7 +692,8 @@ void sytrd_batched(hipStream_t st, int n, int batch, T* A, int64_t sA, T* d, T* 
     // 4.15 ms with 64 rows, 4.4 with 128, 5.1 with 192, 5.5 with 256) but
     // needs more workgroups; a batch that is not co-resident takes several
     // launches, each as long as one (64 x 512: 2.1 ms with 256 rows in one
-    // launch, 2.8 with 192 in two, 4.1 with 128 in three).
+    // launch, 2.8 with 192 in two, 4.1 with 128 in three, all with the
+    // barrier; with tags the 64-row tiles took 3.4 ms at n = 1000).
     int best = 0, TR = 0, chunk = 0;
     double cost = 0.0;
     for (int rpl = 1; rpl <= 4; ++rpl) {
@@ -621,9 +714,8 @@ void sytrd_batched(hipStream_t st, int n, int batch, T* A, int64_t sA, T* d, T* 
     const int G = TR * (TR + 1) / 2, ts = (int)ceil_div(m, TR);
     const int tok = prof_begin(st);
     for (int b0 = 0; b0 < batch; b0 += chunk) {
-      PanelArgs<T> pa{n,           p,          nc,         TR,         ts,         A + b0 * sA, d + b0 * sD,
-                      e + b0 * sD, tau + b0 * sD, ypart + b0 * sYP, colb + b0 * sCB, sp + b0 * sSP,
-                      bar + b0 * sBar, bar_base, sA, sD, sYP, sCB, sSP, sBar};
+      PanelArgs<T> pa{n,  p,  nc, TR, ts, A + b0 * sA, d + b0 * sD, e + b0 * sD, tau + b0 * sD,
+                      x + b0 * sX, bar + (int64_t)b0 * kBarWords, bar_base, sA, sD, sX};
       void* args[] = {&pa};
       const int nt = best == 1 ? Tile<T, 1>::NT : best == 2 ? Tile<T, 2>::NT : best == 3 ? Tile<T, 3>::NT : Tile<T, 4>::NT;
       const void* kern = best == 1 ? (const void*)sytrd_panel_kernel<T, 1>
@@ -632,10 +724,13 @@ void sytrd_batched(hipStream_t st, int n, int batch, T* A, int64_t sA, T* d, T* 
                                      : (const void*)sytrd_panel_kernel<T, 4>;
       MSQRT_HIP(hipLaunchCooperativeKernel(kern, dim3(G, std::min(chunk, batch - b0)), dim3(nt), args, 0, st));
     }
-    bar_base.gen += (unsigned)nc;
-    bar_base.top += (unsigned)std::min(G, 8) * (unsigned)nc;
-    if (G > 8)  // with fewer workgroups the barrier skips the group counters
-      for (int g = 0; g < 8; ++g) bar_base.sub[g] += (unsigned)(G / 8 + (g < G % 8 ? 1 : 0)) * (unsigned)nc;
+    const bool tag = best == 1 ? Tile<T, 1>::kTag : best == 2 ? Tile<T, 2>::kTag : best == 3 ? Tile<T, 3>::kTag : Tile<T, 4>::kTag;
+    if (!tag) {
+      bar_base.gen += (unsigned)nc;
+      bar_base.top += (unsigned)std::min(G, 8) * (unsigned)nc;
+      if (G > 8)  // with fewer workgroups the barrier skips the group counters
+        for (int g = 0; g < 8; ++g) bar_base.sub[g] += (unsigned)(G / 8 + (g < G % 8 ? 1 : 0)) * (unsigned)nc;
+    }
     if (tok >= 0) {
       // algorithmic traffic: one read of the symmetric trailing matrix (lower
       // triangle) per column for its product with the reflector

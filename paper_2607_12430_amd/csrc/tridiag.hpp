@@ -7,8 +7,8 @@
 namespace msqrt {
 
 struct SytrdWork {
-  DevBuf ypart, colb, sp, bar;
-  int nbar = 0;  // batch entries whose grid barrier the last reduction used
+  DevBuf x, bar;
+  int nbar = 0;  // batch entries whose workgroups exchanged words in the last reduction
 };
 
 struct StedcWork {
@@ -38,12 +38,12 @@ template <typename T>
 void sytrd(hipStream_t st, int n, T* A, T* d, T* e, T* tau, SytrdWork& w);
 // The same for `batch` matrices A + b sA; entry b's d, e, tau start at
 // d + b sD, e + b sD, tau + b sD.  As many entries as fit co-resident share
-// one cooperative launch per panel (each with its own grid barrier), and
+// one cooperative launch per panel (each with its own exchanged words), and
 // the trailing updates are one batched GEMM.
 template <typename T>
 void sytrd_batched(hipStream_t st, int n, int batch, T* A, int64_t sA, T* d, T* e, T* tau,
                    int64_t sD, SytrdWork& w);
-// True if a grid barrier of the last reduction timed out (synchronous).
+// True if a wait of the last reduction timed out (synchronous).
 bool sytrd_failed(SytrdWork& w);
 
 // Eigen-decomposition of the symmetric tridiagonal (d, e): lam ascending
