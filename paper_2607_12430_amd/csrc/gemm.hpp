@@ -981,6 +981,8 @@ inline void gemm_lds_attr(Kern k, size_t bytes) {
 // order of 500 took twice as long as 512, now it takes the same.
 typedef float f32v4u __attribute__((ext_vector_type(4), aligned(4)));
 typedef double f64v2u __attribute__((ext_vector_type(2), aligned(8)));
+typedef __bf16 bf16x4_t __attribute__((ext_vector_type(4)));
+typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
 
 template <typename T>
 struct Narrow {
@@ -1053,10 +1055,30 @@ __device__ __forceinline__ void narrow_load(const T* __restrict__ X, int64_t ld,
   }
 }
 
-template <typename T, bool RC>
+// kSplit (float): a row holds the bf16 high parts of its 64 k in groups 0 - 7
+// and the low parts in groups 8 - 15.
+template <typename T, bool RC, bool kSplit>
 __device__ __forceinline__ void narrow_store(T* Xs, int t, const T (&v)[Narrow<T>::E]) {
   using N = Narrow<T>;
   typedef T vec __attribute__((ext_vector_type(16 / sizeof(T))));
+  if constexpr (kSplit) {
+    // four consecutive k of four rows (RC: v[k][row], else v[row][k])
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int row = RC ? 4 * (t % 16) + i : t / 16 + 16 * i, k = 4 * (RC ? t / 16 : t % 16);
+      bf16x4_t h, l;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const float x = RC ? v[4 * e + i] : v[4 * i + e];
+        const __bf16 xh = (__bf16)x;
+        h[e] = xh;
+        l[e] = (__bf16)(x - (float)xh);
+      }
+      *(reinterpret_cast<bf16x4_t*>(Xs + N::at(row, k / 8)) + (k / 4) % 2) = h;
+      *(reinterpret_cast<bf16x4_t*>(Xs + N::at(row, 8 + k / 8)) + (k / 4) % 2) = l;
+    }
+    return;
+  }
   if constexpr (RC) {
     const int r = N::V * (t % N::RG), g0 = N::KT / N::V * (t / N::RG);
 #pragma unroll
@@ -1081,15 +1103,17 @@ __device__ __forceinline__ void narrow_store(T* Xs, int t, const T (&v)[Narrow<T
 
 // acc = the 64 x 64 tile at (m0, n0) of op(A) op(B), op(A) R x K, op(B) K x C;
 // wave w holds rows 32 (w % 2) and columns 32 (w / 2) of it.  Ends with a
-// barrier, so lds (Narrow<T>::kLds bytes) is free again.
-template <typename T, bool TA, bool TB>
+// barrier, so lds (Narrow<T>::kLds bytes) is free again.  kSplit: float
+// operands as sums of two bf16 (see the BF16-split kernel below).
+template <typename T, bool TA, bool TB, bool kSplit = false>
 __device__ __forceinline__ void narrow_product(const T* __restrict__ A, int64_t lda, const T* __restrict__ B,
                                                int64_t ldb, int R, int C, int K, int m0, int n0, T* lds,
                                                typename Mfma<T>::acc_t (&acc)[Narrow<T>::NBLK][Narrow<T>::NBLK]) {
   using M = Mfma<T>;
   using N = Narrow<T>;
   typedef T vec __attribute__((ext_vector_type(16 / sizeof(T))));
-  constexpr int NBLK = N::NBLK, KL = kWave / M::TM, STEPS = 16 / KL;
+  constexpr int NBLK = N::NBLK, KL = kWave / M::TM;
+  constexpr int KG = kSplit ? 16 : KL * N::V, STEPS = N::KS / KG;  // k per step
   constexpr bool ARC = !TA, BRC = TB;
   auto slab = [&](int buf, int op) { return lds + (buf * 2 + op) * N::NT * N::KS; };
   const int t = threadIdx.x, lane = t % kWave, wave = t / kWave;
@@ -1111,8 +1135,8 @@ __device__ __forceinline__ void narrow_product(const T* __restrict__ A, int64_t 
     narrow_load<T, BRC>(B, ldb, n0, C, kb, klo, K, t, r.b);
   };
   auto store = [&](int buf, const Regs& r) {
-    narrow_store<T, ARC>(slab(buf, 0), t, r.a);
-    narrow_store<T, BRC>(slab(buf, 1), t, r.b);
+    narrow_store<T, ARC, kSplit>(slab(buf, 0), t, r.a);
+    narrow_store<T, BRC, kSplit>(slab(buf, 1), t, r.b);
   };
   if (nslab > 0) {
     load(0, r0);
@@ -1126,7 +1150,18 @@ __device__ __forceinline__ void narrow_product(const T* __restrict__ A, int64_t 
     if (q + 2 < nslab) load(q + 2, rl);
     const T* As = slab(buf, 0);
     const T* Bs = slab(buf, 1);
-    auto step = [&](int g) {  // KL groups of V consecutive k, one per lane group
+    auto step = [&](int g) {  // KL groups of consecutive k, one per lane group
+      if constexpr (kSplit) {
+        const int ra = wm * 32 + fr, rb = wn * 32 + fr, gk = 2 * g + h;
+        const bf16x8_t ah = *reinterpret_cast<const bf16x8_t*>(As + N::at(ra, gk));
+        const bf16x8_t al = *reinterpret_cast<const bf16x8_t*>(As + N::at(ra, 8 + gk));
+        const bf16x8_t bh = *reinterpret_cast<const bf16x8_t*>(Bs + N::at(rb, gk));
+        const bf16x8_t bl = *reinterpret_cast<const bf16x8_t*>(Bs + N::at(rb, 8 + gk));
+        acc[0][0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bh, al, acc[0][0], 0, 0, 0);
+        acc[0][0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bl, ah, acc[0][0], 0, 0, 0);
+        acc[0][0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bh, ah, acc[0][0], 0, 0, 0);
+        return;
+      }
       vec av[NBLK], bv[NBLK];
 #pragma unroll
       for (int i = 0; i < NBLK; ++i) {
@@ -1141,7 +1176,6 @@ __device__ __forceinline__ void narrow_product(const T* __restrict__ A, int64_t 
 #pragma unroll
           for (int j = 0; j < NBLK; ++j) acc[i][j] = M::mma(bv[j][c], av[i][c], acc[i][j]);
     };
-    constexpr int KG = KL * N::V;
     if (K - q * N::KS >= N::KS) {
 #pragma unroll
       for (int g = 0; g < STEPS; ++g) step(g);
@@ -1159,7 +1193,7 @@ __device__ __forceinline__ void narrow_product(const T* __restrict__ A, int64_t 
   }
 }
 
-template <typename T, bool TA, bool TB, class Epi>
+template <typename T, bool TA, bool TB, class Epi, bool kSplit = false>
 __global__ __launch_bounds__(GTHREADS, 2) void gemm_narrow_kernel(GemmShape s, const T* __restrict__ A,
                                                                   const T* __restrict__ B, Epi epi,
                                                                   double* __restrict__ partials) {
@@ -1177,7 +1211,7 @@ __global__ __launch_bounds__(GTHREADS, 2) void gemm_narrow_kernel(GemmShape s, c
   const int t = threadIdx.x, lane = t % kWave, wave = t / kWave;
   const int wm = wave % 2, wn = wave / 2;
   typename M::acc_t acc[NBLK][NBLK];
-  narrow_product<T, TA, TB>(A + (int64_t)batch * s.sA, s.lda, B + (int64_t)batch * s.sB, s.ldb, s.M, s.N, K, m0, n0,
+  narrow_product<T, TA, TB, kSplit>(A + (int64_t)batch * s.sA, s.lda, B + (int64_t)batch * s.sB, s.ldb, s.M, s.N, K, m0, n0,
                             reinterpret_cast<T*>(gemm_ldsn), acc);
 
   if constexpr (sizeof(T) == 4 && EpiStages<Epi>::value) {
@@ -1221,7 +1255,6 @@ __global__ __launch_bounds__(GTHREADS, 2) void gemm_narrow_kernel(GemmShape s, c
 // LDS holds the hi and lo parts k-contiguous so that every lane reads its 8
 // consecutive k values with one 16-byte load.
 
-typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
 typedef float f32x16_t __attribute__((ext_vector_type(16)));
 
 constexpr int SBK = 32;              // K-slab of the split kernel
@@ -1586,8 +1619,48 @@ int launch_gemm(hipStream_t st, bool ta, bool tb, const GemmShape& s, const T* A
   if (s.M <= 0 || s.N <= 0 || batch <= 0) return 0;
   dim3 grid(8 * s.per_xcd, batch), block(GTHREADS);
   const int tok = prof_begin(st);
+  // 64-tiles where the busiest CU gets at most three quarters of the work that
+  // 128-tiles (four units each) give it.  Measured 128 -> 64, microseconds:
+  // with one unit per CU against four, float 1000^3 90 -> 39, double
+  // 165 -> 67; two against four, float 1280^3 111 -> 64; three against four,
+  // float 1531^3 133 -> 130, double 246 -> 218, and nine against twelve, 64
+  // symmetric 512^3 204 -> 155.  With equal work the larger tile reads LDS
+  // half as often: four against four, float 2048^3 174 -> 189.  The BF16-split
+  // product is bound by loads and LDS writes in either tile, and 64-tiles hide
+  // them better: four against four, 2048^3 160 -> 99, and 114 -> 43 for the
+  // symmetric 1531^3; only from sixteen against sixteen on the larger tile is
+  // level (4096^3 NT 719 -> 706, NN 618 -> 667).
+  auto narrow = [&](auto sp) {
+    constexpr bool kSplit = decltype(sp)::value;
+    const int64_t ncu = gemm_cu_count();
+    const GemmShape w0 = make_shape(s.M, s.N, s.K, s.lda, s.ldb, s.sA, s.sB, s.tri != 0, Narrow<T>::NT);
+    const int64_t u128 = ceil_div((int64_t)s.ntiles * batch, ncu), u64 = ceil_div((int64_t)w0.ntiles * batch, ncu);
+    if (kSplit ? u64 < 4 * u128 || u128 < 4 : u64 <= 3 * u128) {
+      GemmShape w = w0;
+      w.K_last = s.K_last;
+      dim3 gn(8 * w.per_xcd, batch);
+      auto gon = [&](auto kern) {
+        gemm_lds_attr(kern, Narrow<T>::kLds);
+        hipLaunchKernelGGL(kern, gn, block, Narrow<T>::kLds, st, w, A, B, epi, partials);
+      };
+      if (!ta && !tb) gon(gemm_narrow_kernel<T, false, false, Epi, kSplit>);
+      else if (ta && !tb) gon(gemm_narrow_kernel<T, true, false, Epi, kSplit>);
+      else if (!ta && tb) gon(gemm_narrow_kernel<T, false, true, Epi, kSplit>);
+      else gon(gemm_narrow_kernel<T, true, true, Epi, kSplit>);
+      MSQRT_LAUNCH_CHECK();
+      if (tok >= 0) {
+        const double outs = w.tri ? 0.5 * (double)w.N * (w.N + 1) : (double)w.M * w.N;
+        const double kk = (double)w.K * (batch - 1) + w.K_last;
+        const std::string cls = std::string(kSplit ? "gemm_bf16x3:" : sizeof(T) == 4 ? "gemm_f32:" : "gemm_f64:") + Epi::kName;
+        prof_end(tok, st, cls.c_str(), 2.0 * outs * kk, 0.0);
+      }
+      return w.ntiles;
+    }
+    return 0;
+  };
   if (split) {
     if constexpr (std::is_same<T, float>::value) {
+      if (const int nt = narrow(std::true_type())) return nt;
       if (!ta && !tb) hipLaunchKernelGGL((gemm_split_kernel<false, false, Epi>), grid, block, 0, st, s, A, B, epi, partials);
       else if (ta && !tb) hipLaunchKernelGGL((gemm_split_kernel<true, false, Epi>), grid, block, 0, st, s, A, B, epi, partials);
       else if (!ta && tb) hipLaunchKernelGGL((gemm_split_kernel<false, true, Epi>), grid, block, 0, st, s, A, B, epi, partials);
@@ -1602,40 +1675,6 @@ int launch_gemm(hipStream_t st, bool ta, bool tb, const GemmShape& s, const T* A
       return s.ntiles;
     }
   }
-  // 64-tiles where the busiest CU gets at most three quarters of the work that
-  // 128-tiles (four units each) give it.  Measured 128 -> 64, microseconds:
-  // with one unit per CU against four, float 1000^3 90 -> 39, double
-  // 165 -> 67; two against four, float 1280^3 111 -> 64; three against four,
-  // float 1531^3 133 -> 130, double 246 -> 218, and nine against twelve, 64
-  // symmetric 512^3 204 -> 155.  With equal work the larger tile reads LDS
-  // half as often: four against four, float 2048^3 174 -> 189.
-  auto narrow = [&]() {
-    const int64_t ncu = gemm_cu_count();
-    const GemmShape w0 = make_shape(s.M, s.N, s.K, s.lda, s.ldb, s.sA, s.sB, s.tri != 0, Narrow<T>::NT);
-    const int64_t u128 = ceil_div((int64_t)s.ntiles * batch, ncu), u64 = ceil_div((int64_t)w0.ntiles * batch, ncu);
-    if (u64 <= 3 * u128) {
-      GemmShape w = w0;
-      w.K_last = s.K_last;
-      dim3 gn(8 * w.per_xcd, batch);
-      auto gon = [&](auto kern) {
-        gemm_lds_attr(kern, Narrow<T>::kLds);
-        hipLaunchKernelGGL(kern, gn, block, Narrow<T>::kLds, st, w, A, B, epi, partials);
-      };
-      if (!ta && !tb) gon(gemm_narrow_kernel<T, false, false, Epi>);
-      else if (ta && !tb) gon(gemm_narrow_kernel<T, true, false, Epi>);
-      else if (!ta && tb) gon(gemm_narrow_kernel<T, false, true, Epi>);
-      else gon(gemm_narrow_kernel<T, true, true, Epi>);
-      MSQRT_LAUNCH_CHECK();
-      if (tok >= 0) {
-        const double outs = w.tri ? 0.5 * (double)w.N * (w.N + 1) : (double)w.M * w.N;
-        const double kk = (double)w.K * (batch - 1) + w.K_last;
-        const std::string cls = std::string(sizeof(T) == 4 ? "gemm_f32:" : "gemm_f64:") + Epi::kName;
-        prof_end(tok, st, cls.c_str(), 2.0 * outs * kk, 0.0);
-      }
-      return w.ntiles;
-    }
-    return 0;
-  };
   if constexpr (std::is_same<T, float>::value) {
     const int64_t ncu = gemm_cu_count();
     if (s.tri && s.M >= kWideMin && s.K >= 256 && (int64_t)s.ntiles * batch > 2 * ncu) {
@@ -1691,7 +1730,7 @@ int launch_gemm(hipStream_t st, bool ta, bool tb, const GemmShape& s, const T* A
       }
       return w.ntiles;
     }
-    if (const int nt = narrow()) return nt;
+    if (const int nt = narrow(std::false_type())) return nt;
     // more tiles than two workgroups per CU hold but no more than three:
     // the 16-deep variant runs them in one round
     const int64_t units = (int64_t)s.ntiles * batch;
@@ -1734,7 +1773,7 @@ int launch_gemm(hipStream_t st, bool ta, bool tb, const GemmShape& s, const T* A
       }
       return w.ntiles;
     }
-    if (const int nt = narrow()) return nt;
+    if (const int nt = narrow(std::false_type())) return nt;
     auto go = [&](auto kern) {
       gemm_lds_attr(kern, kGemmF64Lds);
       hipLaunchKernelGGL(kern, grid, block, kGemmF64Lds, st, s, A, B, epi, partials);

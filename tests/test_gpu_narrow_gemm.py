@@ -37,3 +37,29 @@ def test_symmetric_output(prec, n, k):
     c = msq.test_syrk(a, prec=prec).astype(np.float64)
     a64 = a.astype(np.float64)
     assert np.array_equal(c, a64 @ a64.T)
+
+
+@pytest.mark.parametrize("ta,tb", [(False, False), (True, False), (False, True), (True, True)])
+@pytest.mark.parametrize("m,n,k", [(1, 1, 1), (63, 65, 7), (64, 64, 64), (65, 63, 65), (200, 333, 17),
+                                   (257, 190, 72), (1000, 501, 191)])
+def test_bf16_split(ta, tb, m, n, k):
+    import torch
+    import paper_2607_12430_amd as msq
+    rng = np.random.default_rng(m + 3 * n + 7 * k + 11 * ta + 13 * tb)
+    a = rng.standard_normal((k, m) if ta else (m, k)).astype(np.float32)
+    b = rng.standard_normal((n, k) if tb else (k, n)).astype(np.float32)
+    a64 = a.astype(np.float64).T if ta else a.astype(np.float64)
+    b64 = b.astype(np.float64).T if tb else b.astype(np.float64)
+    def parts(x):
+        t = torch.from_numpy(np.ascontiguousarray(x.astype(np.float32)))
+        hi = t.to(torch.bfloat16).float()
+        return hi.double().numpy(), (t - hi).to(torch.bfloat16).double().numpy()
+
+    ah, al = parts(a64)
+    bh, bl = parts(b64)
+    ref = ah @ bh + ah @ bl + al @ bh
+    scale = np.abs(a64) @ np.abs(b64)
+    print(f"[narrow gemm] split {m} {n} {k} {ta} {tb}", flush=True)
+    c = msq.test_gemm_f32(a, b, split=True, ta=ta, tb=tb).astype(np.float64)
+    # what the split product is in exact arithmetic, summed in float
+    assert np.all(np.abs(c - ref) <= 4.0 * 3 * k * 2.0 ** -24 * scale)
