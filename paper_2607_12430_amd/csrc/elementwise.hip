@@ -161,6 +161,22 @@ int launch_validate(hipStream_t st, int n, const double* A, int64_t lda, int64_t
   return nblk;
 }
 
+struct ScalesArg {
+  double v[kScalesByValue];
+};
+__global__ void set_scales_kernel(ScalesArg a, int count, double* d) {
+#pragma unroll
+  for (int i = 0; i < kScalesByValue; ++i)
+    if ((int)threadIdx.x == i && i < count) d[i] = a.v[i];
+}
+
+void launch_set_scales(hipStream_t st, int count, const double* h, double* d) {
+  ScalesArg a{};
+  for (int i = 0; i < count; ++i) a.v[i] = h[i];
+  hipLaunchKernelGGL(set_scales_kernel, dim3(1), dim3(64), 0, st, a, count, d);
+  MSQRT_LAUNCH_CHECK();
+}
+
 void launch_embed_complex(hipStream_t st, int n, const double* A, int64_t lda, int64_t sA,
                           double* E, int64_t sE, int batch) {
   if (n <= 0) return;

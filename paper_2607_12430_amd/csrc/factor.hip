@@ -121,6 +121,7 @@ msqrt_status build_factor(Factor* f, const msqrt_options& o, const double* A, in
   } else {
     const bool want_sym_check = o.structure != MSQRT_STRUCT_GENERAL;
     flags = analyse_input(f, A, lda, sA, want_sym_check, st);
+    f->upload_scales(st);
     if (!want_sym_check) flags |= 2;
   }
   if (tm) tm->end();

@@ -6,6 +6,7 @@
 
 #include "../../include/msqrt.h"
 #include "common.hpp"
+#include "kernels.hpp"
 
 namespace msqrt {
 
@@ -102,6 +103,10 @@ struct Factor {
       if ((int64_t)anorm.size() > i) anorm_scaled[i] = anorm[i] * h[i];
     }
     double* d = scales.ensure<double>(3 * b);
+    if (3 * b <= kScalesByValue) {  // as kernel arguments: nothing to wait for
+      launch_set_scales(st, (int)(3 * b), h.data(), d);
+      return;
+    }
     MSQRT_HIP(hipMemcpyAsync(d, h.data(), sizeof(double) * 3 * b, hipMemcpyHostToDevice, st));
     MSQRT_HIP(hipStreamSynchronize(st));
   }
@@ -115,14 +120,17 @@ struct Factor {
 struct PhaseTimer {
   hipStream_t st;
   msqrt_info* info;
-  struct Pending { int phase; hipEvent_t a, b; };
+  struct Pending { int phase; hipEvent_t a, b; bool shared; };  // shared: b starts the next phase
   std::vector<Pending> pend;
   std::vector<hipEvent_t> pool;
   int cur = -1;
   hipEvent_t cur_ev = nullptr;
   PhaseTimer(hipStream_t s, msqrt_info* i) : st(s), info(i) {}
   ~PhaseTimer() {
-    for (auto& p : pend) { pool.push_back(p.a); pool.push_back(p.b); }
+    for (auto& p : pend) {
+      pool.push_back(p.a);
+      if (!p.shared) pool.push_back(p.b);
+    }
     for (auto e : pool) hipEventDestroy(e);
     if (cur_ev) hipEventDestroy(cur_ev);
   }
@@ -134,16 +142,18 @@ struct PhaseTimer {
   }
   void begin(int phase) {
     if (!info) return;
-    end();
+    hipEvent_t e = ev();
+    MSQRT_HIP(hipEventRecord(e, st));
+    // one event ends the phase before and starts this one
+    if (cur >= 0) pend.push_back({cur, cur_ev, e, true});
     cur = phase;
-    cur_ev = ev();
-    MSQRT_HIP(hipEventRecord(cur_ev, st));
+    cur_ev = e;
   }
   void end() {
     if (!info || cur < 0) return;
     hipEvent_t e = ev();
     MSQRT_HIP(hipEventRecord(e, st));
-    pend.push_back({cur, cur_ev, e});
+    pend.push_back({cur, cur_ev, e, false});
     cur = -1;
     cur_ev = nullptr;
   }
@@ -155,7 +165,7 @@ struct PhaseTimer {
       if (hipEventElapsedTime(&ms, p.a, p.b) == hipSuccess && p.phase >= 0 && p.phase < 12)
         info->t_ms[p.phase] += ms;
       pool.push_back(p.a);
-      pool.push_back(p.b);
+      if (!p.shared) pool.push_back(p.b);
     }
     pend.clear();
   }
@@ -212,12 +222,10 @@ struct RefineWs {
   int* flags = nullptr;
 };
 
+// X (may be null): a second matrix checked along with A, its flags in *xflags.
 int analyse_input(Factor* f, const double* A, int64_t lda, int64_t sA, bool check_sym,
-                  hipStream_t st, const RefineWs* ws = nullptr);
-// Finiteness (bit0) and exact symmetry failures (bit1) of a batch of n x n
-// matrices with the factor's n and batch; the factor's scales are untouched.
-int validate_flags(Factor* f, const double* M, int64_t ld, int64_t sM, hipStream_t st,
-                   const RefineWs* ws = nullptr);
+                  hipStream_t st, const RefineWs* ws = nullptr,
+                  const double* X = nullptr, int64_t ldx = 0, int64_t sX = 0, int* xflags = nullptr);
 
 // Factorisation of the scaled input into f (Q, S, structure, prec).
 msqrt_status build_factor(Factor* f, const msqrt_options& o, const double* A, int64_t lda,

@@ -41,6 +41,10 @@ void launch_copy_f64(hipStream_t st, int n, const double* A, int64_t lda, int64_
 
 // ---- GEMMs (gemm.hip) -----------------------------------------------------
 
+// d[i] = h[i] for i < count <= kScalesByValue, passed by value.
+constexpr int kScalesByValue = 48;
+void launch_set_scales(hipStream_t st, int count, const double* h, double* d);
+
 // Most tiles per batch entry of a full n x n residual product (its smallest
 // tiles are 64 x 64).
 inline int64_t residual_tiles(int n) { return ceil_div(n, 64) * ceil_div(n, 64); }

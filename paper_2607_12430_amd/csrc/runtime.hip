@@ -396,53 +396,47 @@ msqrt_status backward(Factor* f, const double* X, int64_t ldx, const double* Gba
   return backward_general<float>(f, X, ldx, Gbar, ldgb, G, ldg, maxit, tol, st, info, tm);
 }
 
-// Finiteness (bit 0) and exact symmetry failures (bit 1) of a batch of
-// matrices, without touching the factor's scales.
-int validate_flags(Factor* f, const double* M, int64_t ld, int64_t sM, hipStream_t st,
-                   const RefineWs* ws) {
-  const int n = (int)f->n, batch = (int)f->batch;
-  const int nt = (int)ceil_div(n, 32);
-  int* flags = ws ? ws->flags : f->active.ensure<int>(batch);
-  double* part = ws ? ws->part : f->part.ensure<double>((int64_t)nt * (nt + 1) / 2 * batch + 64);
-  launch_fill_i32(st, flags, batch, 0);
-  launch_validate(st, n, M, ld, sM, batch, 1, flags, part);
-  std::vector<int> hf(batch);
-  MSQRT_HIP(hipMemcpyAsync(hf.data(), flags, sizeof(int) * batch, hipMemcpyDeviceToHost, st));
-  MSQRT_HIP(hipStreamSynchronize(st));
-  int agg = 0;
-  for (int b = 0; b < batch; ++b) agg |= hf[b];
-  return agg;
-}
-
 // Computes ||A_b||_F and the scale exponents k_b = round(log4(||A_b||_F / sqrt(n)))
 // into the factor; also validates finiteness / symmetry.  Returns flags.
 int analyse_input(Factor* f, const double* A, int64_t lda, int64_t sA, bool check_sym,
-                  hipStream_t st, const RefineWs* ws) {
+                  hipStream_t st, const RefineWs* ws, const double* X, int64_t ldx, int64_t sX, int* xflags) {
   const int n = (int)f->n, batch = (int)f->batch;
   const int nt = (int)ceil_div(n, 32);
   const int nblk = nt * (nt + 1) / 2;
-  int* flags = ws ? ws->flags : f->active.ensure<int>(batch);
   double* part = ws ? ws->part : f->part.ensure<double>((int64_t)nblk * batch + 64);
-  double* rn = ws ? ws->rn : f->rnorm.ensure<double>(batch);
-  launch_fill_i32(st, flags, batch, 0);
+  // norms and flags side by side, for one copy to the host
+  double* rn = ws ? ws->rn : f->rnorm.ensure<double>(2 * (int64_t)batch);
+  int* flags = ws ? ws->flags : (int*)(rn + batch);
+  std::vector<double> hn(2 * batch);
+  int* hf = (int*)(hn.data() + batch);
+  launch_fill_i32(st, flags, ws ? batch : 2 * batch, 0);
   launch_validate(st, n, A, lda, sA, batch, check_sym ? 1 : 0, flags, part);
   launch_reduce_sqrt(st, part, nblk, batch, rn);
-  std::vector<int> hf(batch);
-  std::vector<double> hn(batch);
-  MSQRT_HIP(hipMemcpyAsync(hf.data(), flags, sizeof(int) * batch, hipMemcpyDeviceToHost, st));
-  MSQRT_HIP(hipMemcpyAsync(hn.data(), rn, sizeof(double) * batch, hipMemcpyDeviceToHost, st));
+  if (ws) {
+    MSQRT_HIP(hipMemcpyAsync(hf, flags, sizeof(int) * batch, hipMemcpyDeviceToHost, st));
+    MSQRT_HIP(hipMemcpyAsync(hn.data(), rn, sizeof(double) * batch, hipMemcpyDeviceToHost, st));
+    if (X) {
+      launch_fill_i32(st, flags, batch, 0);
+      launch_validate(st, n, X, ldx, sX, batch, 1, flags, part);
+      MSQRT_HIP(hipMemcpyAsync(hf + batch, flags, sizeof(int) * batch, hipMemcpyDeviceToHost, st));
+    }
+  } else {
+    if (X) launch_validate(st, n, X, ldx, sX, batch, 1, flags + batch, part);
+    MSQRT_HIP(hipMemcpyAsync(hn.data(), rn, 2 * sizeof(double) * batch, hipMemcpyDeviceToHost, st));
+  }
   MSQRT_HIP(hipStreamSynchronize(st));
   int agg = 0;
   f->kexp.assign(batch, 0);
   f->anorm.assign(batch, 0.0);
+  if (X) *xflags = 0;
   for (int b = 0; b < batch; ++b) {
     agg |= hf[b];
+    if (X) *xflags |= hf[batch + b];
     f->anorm[b] = hn[b];
     int k = 0;
     if (hn[b] > 0 && std::isfinite(hn[b])) k = (int)std::lround(std::log(hn[b] / std::sqrt((double)n)) / std::log(4.0));
     f->kexp[b] = k;
   }
-  f->upload_scales(st);
   return agg;
 }
 
@@ -560,6 +554,7 @@ msqrt_status msqrt_factor_wrap(msqrt_prec prec, msqrt_struct structure, msqrt_dt
   f->kexp.assign(1, 0);
   f->anorm.assign(1, 0.0);
   f->upload_scales(nullptr);
+  MSQRT_HIP(hipStreamSynchronize(nullptr));  // the factor may be used on any stream
   MSQRT_HIP(hipDeviceSynchronize());
   *out = reinterpret_cast<msqrt_factor_t>(f.release());
   return MSQRT_OK;
@@ -662,9 +657,10 @@ msqrt_status refine_call(Factor* f, const void* dA, int64_t lda, int64_t strideA
       // An HPD factor refines a symmetric A from a symmetric X: the residual
       // is formed as A - X X^T from the lower triangle, which equals A - X^2
       // only for exactly symmetric A and X.
-      flags = analyse_input(f, (const double*)dA, lda, strideA, true, stream, ws);
-      if (!init_from_factor && !(flags & 3))
-        flags |= validate_flags(f, (const double*)dX, ldx, strideX, stream, ws);
+      int xflags = 0;
+      flags = analyse_input(f, (const double*)dA, lda, strideA, true, stream, ws,
+                            init_from_factor ? nullptr : (const double*)dX, ldx, strideX, &xflags);
+      if (!init_from_factor && !(flags & 3)) flags |= xflags;
     }
     f->kexp = k;
     f->upload_scales(stream);
