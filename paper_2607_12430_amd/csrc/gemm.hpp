@@ -1629,13 +1629,15 @@ int launch_gemm(hipStream_t st, bool ta, bool tb, const GemmShape& s, const T* A
   // product is bound by loads and LDS writes in either tile, and 64-tiles hide
   // them better: four against four, 2048^3 160 -> 99, and 114 -> 43 for the
   // symmetric 1531^3; only from sixteen against sixteen on the larger tile is
-  // level (4096^3 NT 719 -> 706, NN 618 -> 667).
+  // level (4096^3 NT 719 -> 706, NN 618 -> 667), and with A transposed from
+  // three 128-tiles per CU on (symmetric 4096^3 374 -> 453).
   auto narrow = [&](auto sp) {
     constexpr bool kSplit = decltype(sp)::value;
     const int64_t ncu = gemm_cu_count();
     const GemmShape w0 = make_shape(s.M, s.N, s.K, s.lda, s.ldb, s.sA, s.sB, s.tri != 0, Narrow<T>::NT);
     const int64_t u128 = ceil_div((int64_t)s.ntiles * batch, ncu), u64 = ceil_div((int64_t)w0.ntiles * batch, ncu);
-    if (kSplit ? u64 < 4 * u128 || u128 < 4 : u64 <= 3 * u128) {
+    const bool fewer = kSplit ? (u64 < 4 * u128 || u128 < 4) && !(ta && !tb && u128 >= 3) : u64 <= 3 * u128;
+    if (fewer) {
       GemmShape w = w0;
       w.K_last = s.K_last;
       dim3 gn(8 * w.per_xcd, batch);

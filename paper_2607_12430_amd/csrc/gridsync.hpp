@@ -117,7 +117,7 @@ __device__ __forceinline__ void tag_load(tword (&w)[N], Load load, unsigned tag,
     if (__ballot(miss) == 0) return;
     if ((++spins & 255u) == 0u) {
       if (__ballot(cload(fail) != 0u) != 0) return;
-      if (spins > (1u << 21)) {
+      if (spins > (1u << 24)) {
         cstore(fail, 1u);
         return;
       }
