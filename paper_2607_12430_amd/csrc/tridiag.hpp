@@ -38,8 +38,7 @@ template <typename T>
 void sytrd(hipStream_t st, int n, T* A, T* d, T* e, T* tau, SytrdWork& w);
 // The same for `batch` matrices A + b sA; entry b's d, e, tau start at
 // d + b sD, e + b sD, tau + b sD.  As many entries as fit co-resident share
-// one cooperative launch per panel (each with its own exchanged words), and
-// the trailing updates are one batched GEMM.
+// one cooperative launch, each with its own exchanged words.
 template <typename T>
 void sytrd_batched(hipStream_t st, int n, int batch, T* A, int64_t sA, T* d, T* e, T* tau,
                    int64_t sD, SytrdWork& w);
