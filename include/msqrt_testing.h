@@ -20,6 +20,10 @@ extern "C" {
 msqrt_status msqrt_test_sytrd(msqrt_prec prec, int64_t n, const void* A, void* d, void* e,
                               void* tau);
 
+/* Upper half of a 64-bit word by which the tridiagonal reduction marks it as
+ * written for `column` (no device work). */
+uint32_t msqrt_test_sytrd_tag(int64_t column);
+
 /* Two-stage tridiagonalisation A = Q T Q^T (dense -> band -> tridiagonal) of
  * the symmetric n x n column-major A (n <= 4104): the diagonal d (n) and
  * off-diagonal e (n-1) of T, and Q (n x n column-major) formed by the

@@ -248,6 +248,8 @@ extern "C" msqrt_status msqrt_test_sytrd(msqrt_prec prec, int64_t n, const void*
   }
 }
 
+extern "C" uint32_t msqrt_test_sytrd_tag(int64_t column) { return sytrd_tag((int)column); }
+
 extern "C" msqrt_status msqrt_test_sy2tr(msqrt_prec prec, int64_t n, const void* A, void* d,
                                          void* e, void* Q) {
   try {

@@ -78,11 +78,18 @@ __device__ inline V wsum(V v) {
 }
 
 // Tagged exchange: a value goes out as 64-bit words of 32 bits of it and a
-// 32-bit tag (the number of the step it belongs to), each written and read
-// whole, so a reader that finds the tag has the value: the read is the wait,
-// and no store is waited for.  A step's words may be overwritten once every
-// workgroup is known to have finished reading them.
+// 32-bit tag (of the step it belongs to), each written and read whole, so a
+// reader that finds the tag has the value: the read is the wait, and no store is
+// waited for.  A step's words may be overwritten once every workgroup is known
+// to have finished reading them.
+// The same memory may hold plain floats or doubles from an earlier launch, and
+// any finite bit pattern can be one of those (small step numbers are denormal
+// floats, which the tails of a kernel matrix have).  A tag is therefore the
+// upper half of a NaN, in float as in double, with the step in the payload: no
+// finite value and no NaN that arithmetic produces looks like a written word.
 typedef unsigned long long tword;
+constexpr unsigned kTagSteps = 1u << 19;  // the quiet bit of a double's NaN stays clear
+__host__ __device__ constexpr unsigned step_tag(unsigned step) { return 0xFFF00000u + 1u + step; }
 template <typename T>
 constexpr int kTagW = (int)sizeof(T) / 4;  // words per value
 __device__ inline void tag_store(tword* p, float v, unsigned tag) {

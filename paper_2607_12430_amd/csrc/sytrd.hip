@@ -78,7 +78,7 @@ struct PanelArgs {
   T* d;
   T* e;
   T* tau;
-  // the exchanged words (tag: column + 1) of batch entry 0; sX per entry
+  // the exchanged words (tag: the column's) of batch entry 0; sX per entry
   tword* x;
   unsigned* bar;  // barrier words of batch entry 0; the failure flag is among them
   BarrierBase bar_base;
@@ -220,7 +220,7 @@ __global__ __launch_bounds__((Tile<T, RPL>::NT)) void sytrd_panel_kernel(PanelAr
 
   for (int jj = 0; jj < a.nc; ++jj) {
     const int j = p + jj, buf = jj & 1;
-    const unsigned tag = (unsigned)j + 1u;
+    const unsigned tag = step_tag((unsigned)j);
     tword* const xb = a.x + buf * ex.size;
     tword* const yp = xb + ex.yp;
     tword* const cl = xb + ex.cl;
@@ -661,6 +661,8 @@ __global__ void copy_diag(const T* A, T* d, int64_t sA, int64_t sD) {
 
 int sytrd_max_n() { return kMaxN; }
 static_assert((int64_t)kMaxN * kMaxN < (int64_t(1) << 31), "the kernels' 32-bit offsets cover an n x n matrix");
+static_assert(kMaxN < (int)kTagSteps - 1, "one tag per column");
+unsigned sytrd_tag(int column) { return step_tag((unsigned)column); }
 
 template <typename T>
 void sytrd_batched(hipStream_t st, int n, int batch, T* A, int64_t sA, T* d, T* e, T* tau,

@@ -42,6 +42,8 @@ void sytrd(hipStream_t st, int n, T* A, T* d, T* e, T* tau, SytrdWork& w);
 template <typename T>
 void sytrd_batched(hipStream_t st, int n, int batch, T* A, int64_t sA, T* d, T* e, T* tau,
                    int64_t sD, SytrdWork& w);
+// Tag of the words exchanged for a column.
+unsigned sytrd_tag(int column);
 // True if a wait of the last reduction timed out (synchronous).
 bool sytrd_failed(SytrdWork& w);
 
