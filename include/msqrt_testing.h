@@ -51,6 +51,13 @@ msqrt_status msqrt_test_gehrd(msqrt_prec prec, int64_t n, const double* A, doubl
  * the shifted QR algorithm); T upper triangular. */
 msqrt_status msqrt_test_schur(msqrt_prec prec, int64_t n, const double* A, double* T, double* Q);
 
+/* The elementary transformations of the shifted QR for nv vectors `in` (host,
+ * 4 doubles each, rounded to the precision prec), 4 doubles each to `out`.
+ * cplx = 0: the reflector I - (tau + tl) v v^T, v = (1, w1, w2), that maps in[0..2] to
+ * a multiple of e_1: tau, tl, w1, w2.  cplx = 1: the rotation (1 + h) [c s; -conj(s) c]
+ * that maps (in[0] + i in[1], in[2] + i in[3]) likewise: c, Re s, Im s, h. */
+msqrt_status msqrt_test_qr_step(msqrt_prec prec, int cplx, int64_t nv, const double* in, double* out);
+
 /* Principal square root S of the upper triangular T (Eq. (subst), blocked);
  * NO_PRINCIPAL if a diagonal entry lies on or next to R<=0. */
 msqrt_status msqrt_test_trsqrt(msqrt_prec prec, int64_t n, const double* T, double* S);

@@ -316,6 +316,17 @@ def test_schur(a, prec="fp32"):
     return t, q
 
 
+def test_qr_step(x, cplx, prec="fp32"):
+    """Test hook: the QR's reflectors (tau, tl, w1, w2) or rotations (c, Re s,
+    Im s, h) for the rows of x (nv x 4)."""
+    import numpy as np
+    x = np.ascontiguousarray(x, np.float64)
+    out = np.zeros((x.shape[0], 4))
+    check(lib().msqrt_test_qr_step(_lib.PREC_NAMES[prec], 1 if cplx else 0, x.shape[0], _dp(x), _dp(out)),
+          "msqrt_test_qr_step")
+    return out
+
+
 def test_trsqrt(t, prec="fp32"):
     """Test hook: principal square root of an upper triangular matrix."""
     import numpy as np

@@ -34,7 +34,7 @@ EXPORTED = [
     "msqrt_release_cached",
     "msqrt_factor_wrap", "msqrt_factor_export", "msqrt_test_sytrd", "msqrt_test_sy2tr",
     "msqrt_test_sytrd_tag", "msqrt_test_stedc",
-    "msqrt_test_gehrd", "msqrt_test_schur", "msqrt_test_trsqrt", "msqrt_test_trsyl",
+    "msqrt_test_gehrd", "msqrt_test_schur", "msqrt_test_qr_step", "msqrt_test_trsqrt", "msqrt_test_trsyl",
     "msqrt_test_trcbrt", "msqrt_rootm",
     "msqrt_test_gemm_f32", "msqrt_test_syrk", "msqrt_features", "msqrt_mlp_forward", "msqrt_mlp_grad",
     "msqrt_mlp_adam", "msqrt_selector_set", "msqrt_selector_load", "msqrt_selector_clear",
@@ -135,6 +135,7 @@ def lib():
     dp = ctypes.POINTER(ctypes.c_double)
     L.msqrt_test_gehrd.argtypes = [ci, i64, dp, dp, dp]
     L.msqrt_test_schur.argtypes = [ci, i64, dp, dp, dp]
+    L.msqrt_test_qr_step.argtypes = [ci, ci, i64, dp, dp]
     L.msqrt_test_trsqrt.argtypes = [ci, i64, dp, dp]
     L.msqrt_test_trcbrt.argtypes = [ci, i64, dp, dp]
     L.msqrt_rootm.argtypes = [ctypes.POINTER(Options), ci, ci, i64, vp, i64, vp, i64, vp,
@@ -156,7 +157,8 @@ def lib():
     for name in ("msqrt_factor", "msqrt_refine", "msqrt_refine_noalloc", "msqrt_sqrtm",
                  "msqrt_sqrtm_backward",
                  "msqrt_factor_wrap", "msqrt_factor_export", "msqrt_test_sytrd",
-                 "msqrt_test_stedc", "msqrt_test_gehrd", "msqrt_test_schur", "msqrt_test_trsqrt",
+                 "msqrt_test_stedc", "msqrt_test_gehrd", "msqrt_test_schur", "msqrt_test_qr_step",
+                 "msqrt_test_trsqrt",
                  "msqrt_test_trcbrt", "msqrt_rootm",
                  "msqrt_test_trsyl", "msqrt_test_gemm_f32", "msqrt_test_syrk", "msqrt_features",
                  "msqrt_mlp_forward", "msqrt_mlp_grad", "msqrt_mlp_adam", "msqrt_selector_set",

@@ -7,6 +7,7 @@
 
 #include "../../include/msqrt_testing.h"
 #include "kernels.hpp"
+#include "qrchain.hpp"
 #include "schur.hpp"
 
 using namespace msqrt;
@@ -65,6 +66,45 @@ msqrt_status gehrd_impl(int n, const double* A, double* H, double* Q, bool schur
   MSQRT_HIP(hipDeviceSynchronize());
   from_stacked_host<T>(n, n, download(dH, 2 * (size_t)n * n), H);
   from_stacked_host<T>(n, n, download(dQ, 2 * (size_t)n * n), Q);
+  return MSQRT_OK;
+}
+
+template <typename T>
+__global__ void qr_step_kernel(int nv, int cplx, const double* in, double* out) {
+  const int i = blockIdx.x * blockDim.x + threadIdx.x;
+  if (i >= nv) return;
+  const double* x = in + 4 * (int64_t)i;
+  double* o = out + 4 * (int64_t)i;
+  if (cplx) {
+    using A = qr::CplxRoute<T>;
+    const cx<T> v[2] = {{(T)x[0], (T)x[1]}, {(T)x[2], (T)x[3]}};
+    cx<T> beta;
+    const typename A::Refl f = A::make(v, beta);
+    o[0] = f.c;
+    o[1] = f.s.r;
+    o[2] = f.s.i;
+    o[3] = f.h;
+  } else {
+    using A = qr::RealRoute<T>;
+    const T v[3] = {(T)x[0], (T)x[1], (T)x[2]};
+    T beta;
+    const typename A::Refl f = A::make(v, beta);
+    o[0] = f.tau;
+    o[1] = f.tl;
+    o[2] = f.w1;
+    o[3] = f.w2;
+  }
+}
+
+template <typename T>
+msqrt_status qr_step_impl(int nv, int cplx, const double* in, double* out) {
+  DevBuf ib, ob;
+  double* di = upload(ib, std::vector<double>(in, in + 4 * (size_t)nv));
+  double* dout = ob.ensure<double>(4 * (int64_t)nv);
+  hipLaunchKernelGGL(qr_step_kernel<T>, dim3((unsigned)ceil_div(nv, 256)), dim3(256), 0, nullptr, nv, cplx, di, dout);
+  MSQRT_LAUNCH_CHECK();
+  MSQRT_HIP(hipDeviceSynchronize());
+  MSQRT_HIP(hipMemcpy(out, dout, sizeof(double) * 4 * (size_t)nv, hipMemcpyDeviceToHost));
   return MSQRT_OK;
 }
 
@@ -155,6 +195,15 @@ extern "C" msqrt_status msqrt_test_schur(msqrt_prec prec, int64_t n, const doubl
   return guarded([&] {
     if (prec == MSQRT_PREC_FP64) return gehrd_impl<double>((int)n, A, T, Q, true);
     if (prec == MSQRT_PREC_FP32) return gehrd_impl<float>((int)n, A, T, Q, true);
+    return MSQRT_ERR_INVALID_ARG;
+  });
+}
+
+extern "C" msqrt_status msqrt_test_qr_step(msqrt_prec prec, int cplx, int64_t nv, const double* in, double* out) {
+  if (nv < 1 || !in || !out || nv > (1 << 24)) return MSQRT_ERR_INVALID_ARG;
+  return guarded([&] {
+    if (prec == MSQRT_PREC_FP64) return qr_step_impl<double>((int)nv, cplx, in, out);
+    if (prec == MSQRT_PREC_FP32) return qr_step_impl<float>((int)nv, cplx, in, out);
     return MSQRT_ERR_INVALID_ARG;
   });
 }
