@@ -2,9 +2,9 @@
 // spectral decomposition used by Alg. 3).
 //
 // The trailing matrix lives in registers, one lower-triangular tile per
-// workgroup of a cooperative launch, and is updated there at every column
-// (A -= v w^T + w v^T, summed apart and flushed every kFlush
-// columns), with ONE exchange per column.  For column j with
+// workgroup of a cooperative launch, and is updated there (A -= v w^T + w v^T,
+// summed apart and rounded into the tile once per kFlush or kLazy columns, see
+// Tile), with ONE exchange per column.  For column j with
 // sub-column u (rows j+1..n-1) the reflector is v = (u - beta e1) c, c =
 // 1/(alpha - beta).  Everything the column needs from v is linear in v, so
 // before the exchange each workgroup forms its tile's share of the product
@@ -48,17 +48,23 @@ namespace {
 
 constexpr int kTRMax = 22;    // max tiles per dimension: 253 workgroups, one per CU
 constexpr int kGMax = kTRMax * (kTRMax + 1) / 2;
-constexpr int kMaxTs = 256;   // largest tile
 constexpr int kMaxN = kTRMax * 192 + 1;  // largest order
 constexpr int kLaunchCols = 128;  // n = 4096: 27.6, 26.0, 25.3, 25.0 ms for 32, 64, 128, 256 (without kDelta and tags)
 constexpr int kFlush = 32;    // columns between flushes of the accumulated updates
 
-// How the panel kernel is built for tiles of 64 RPL rows: threads, and whether
-// a tile is held as matrix + accumulated updates.  One rounding of the matrix
-// per column instead of one per kFlush columns doubled the error of X_0 at
-// n = 4096 (kappa = 1e4: 1.9e-6 to 4.0e-6; 15 % at n = 500), so the updates
-// are summed apart wherever the registers hold both: 1024 threads have 128
-// registers each, 512 have 256.  kTag: the exchange is by tagged words.
+// How the panel kernel is built for tiles of 64 RPL rows: threads, and how a
+// tile's updates are kept from rounding it at every column (which doubled the
+// error of X_0 at n = 4096, kappa = 1e4: 1.9e-6 to 4.0e-6).  kDelta: they are
+// summed in registers beside the tile, where those hold both: 1024 threads have
+// 128 registers each, 512 have 256.  Otherwise the last up to kLazy columns'
+// v and w wait in LDS, the product and the published column are corrected by
+// them, and the tile is updated once for all of them.  (With one rounding per
+// column in these tiles X_0 was 16 % worse for 64 x 512 and, in double, 9 % at
+// n = 4096 than with panels of 32 columns, and the gradient of 64 x 512 1.7
+// times; now they are 0.90, 1.00 and 0.78 of it.  It costs 0.25 ms of the 64 x
+// 512 reduction, 2.04 -> 2.29, and 1.6 of 28.5 ms at n = 4096 in double.)
+// kTag: the exchange is by tagged words.
+constexpr int kLazy = 8;
 template <typename T, int RPL>
 struct Tile;
 template <> struct Tile<float, 1> { static constexpr int NT = 1024; static constexpr bool kDelta = true; static constexpr bool kTag = true; };
@@ -152,6 +158,7 @@ template <typename T, int RPL>
 __global__ __launch_bounds__((Tile<T, RPL>::NT)) void sytrd_panel_kernel(PanelArgs<T> a) {
   constexpr int NT = Tile<T, RPL>::NT, NW = NT / kWave;
   constexpr bool kDelta = Tile<T, RPL>::kDelta;
+  constexpr int PB = kDelta ? 1 : kLazy;  // columns of v and w in LDS
   constexpr int TS = kWave * RPL, CW = TS / NW, CQ = CW / 4;  // tile size, columns per wave and lane row
   // Row work of a column: rows of I on threads [0, TS), rows of K on
   // [NT / 2, NT / 2 + TS); the partial sums of the scalars of kScN workgroups
@@ -192,8 +199,8 @@ __global__ __launch_bounds__((Tile<T, RPL>::NT)) void sytrd_panel_kernel(PanelAr
   const int wave = __builtin_amdgcn_readfirstlane(tid / kWave), cb = wave * CW;
   const unsigned ld = (unsigned)n;  // n^2 < 2^31: 32-bit offsets
   T* A = a.A;
-  __shared__ __attribute__((aligned(16))) T uI[TS], uK[TS], vI[TS], wI[TS], vK[TS], wK[TS];
-  __shared__ T zred[NW][TS], zK[TS];
+  __shared__ __attribute__((aligned(16))) T uI[TS], uK[TS], vw[PB][4][TS];  // vw: v and w of the rows of I, of K
+  __shared__ T zred[NW][TS], zK[TS], dots[4][PB];
   __shared__ double red[2][4];
   __shared__ T piv[3];  // alpha, y_{j+1}, A(j+1, j+1)
   const bool rowI = tid < nI, rowK = offdiag && tid >= kKT && tid - kKT < nK;
@@ -218,240 +225,310 @@ __global__ __launch_bounds__((Tile<T, RPL>::NT)) void sytrd_panel_kernel(PanelAr
   if (tid < 8) red[tid / 4][tid % 4] = 0.0;
   __syncthreads();
 
-  for (int jj = 0; jj < a.nc; ++jj) {
-    const int j = p + jj, buf = jj & 1;
-    const unsigned tag = step_tag((unsigned)j);
-    tword* const xb = a.x + buf * ex.size;
-    tword* const yp = xb + ex.yp;
-    tword* const cl = xb + ex.cl;
-    T* const yv = reinterpret_cast<T*>(yp);  // the same without tags
-    T* const cv = reinterpret_cast<T*>(cl);
-    // column j + 1 as it is before this column's update
-    const int kc = j + 1 - K0 - cb;
-    if (kc >= 0 && kc < CW && j + 1 - K0 < nK) {
+  // kGroup columns, then the update of the tile that they left
+  constexpr int kGroup = kDelta ? kFlush : kLazy;
+#pragma clang loop unroll(disable)
+  for (int g0 = 0; g0 < a.nc; g0 += kGroup) {
+    const int g1 = min(g0 + kGroup, a.nc);
+#pragma clang loop unroll(disable)
+    for (int jj = g0; jj < g1; ++jj) {
+      const int j = p + jj, buf = jj & 1;
+      const unsigned tag = step_tag((unsigned)j);
+      tword* const xb = a.x + buf * ex.size;
+      tword* const yp = xb + ex.yp;
+      tword* const cl = xb + ex.cl;
+      T* const yv = reinterpret_cast<T*>(yp);  // the same without tags
+      T* const cv = reinterpret_cast<T*>(cl);
+      const int sl = kDelta ? 0 : jj - g0;  // slot of this column; the slots before it wait
+      // column j + 1 as it is before this column's update
+      const int kc = j + 1 - K0 - cb;
+      if (kc >= 0 && kc < CW && j + 1 - K0 < nK) {
+        T wait[RPL] = {};
+        if constexpr (!kDelta) {
+#pragma clang loop unroll(disable)
+          for (int t = 0; t < sl; ++t) {
+            const T vc = vw[t][2][cb + kc], wc = vw[t][3][cb + kc];
 #pragma unroll
-      for (int c = 0; c < CW; ++c)
-        if (c == kc) {
+            for (int q = 0; q < RPL; ++q) wait[q] += vw[t][0][lane + q * kWave] * wc + vw[t][1][lane + q * kWave] * vc;
+          }
+        }
+#pragma unroll
+        for (int c = 0; c < CW; ++c)
+          if (c == kc) {
+#pragma unroll
+            for (int q = 0; q < RPL; ++q) {
+              const int r = lane + q * kWave;
+              if (r < nI && I0 + r >= j + 1) {
+                if constexpr (kTag) tag_store(cl + (unsigned)(I0 + r) * W, entry(c, q), tag);
+                else cstore(cv + I0 + r, kDelta ? entry(c, q) : v[c][q] - wait[q]);
+              }
+            }
+          }
+      }
+      // sums by which the waiting columns correct the products below: w_K^T u_K,
+      // v_K^T u_K, w_I^T u_I, v_I^T u_I
+      if constexpr (!kDelta) {
+        for (int x = wave; x < (offdiag ? 4 : 2) * sl; x += NW) {
+          const int kind = x / sl, t = x % sl;
+          const T* a1 = vw[t][3 - kind];
+          const T* a2 = kind < 2 ? uK : uI;
+          T d = T(0);
+#pragma unroll
+          for (int q = 0; q < RPL; ++q) d += a1[lane + q * kWave] * a2[lane + q * kWave];
+          d = wsum(d);
+          if (lane == 0) dots[kind][t] = d;
+        }
+      }
+      // partial products: rows (one sum per wave), columns off the diagonal
+      {
+        T zi[RPL], ui[RPL], zk[CW];
+#pragma unroll
+        for (int q = 0; q < RPL; ++q) {
+          zi[q] = T(0);
+          ui[q] = uI[lane + q * kWave];
+        }
+#pragma unroll
+        for (int c = 0; c < CW; ++c) {
+          const T uk = uK[cb + c];
+          zk[c] = T(0);
 #pragma unroll
           for (int q = 0; q < RPL; ++q) {
-            const int r = lane + q * kWave;
-            if (r < nI && I0 + r >= j + 1) {
-              if constexpr (kTag) tag_store(cl + (unsigned)(I0 + r) * W, entry(c, q), tag);
-              else cstore(cv + I0 + r, entry(c, q));
+            const T x = entry(c, q);
+            zi[q] += x * uk;
+            zk[c] += x * ui[q];
+          }
+        }
+#pragma unroll
+        for (int q = 0; q < RPL; ++q) zred[wave][lane + q * kWave] = zi[q];
+        if (offdiag) {
+          // column sums over the 64 lanes by halving exchanges: lane row R ends
+          // with columns CQ R .. CQ R + CQ - 1
+          T z2[CW / 2], z4[CQ];
+#pragma unroll
+          for (int c = 0; c < CW / 2; ++c) z2[c] = swap_add32(zk[c], zk[c + CW / 2]);
+#pragma unroll
+          for (int c = 0; c < CQ; ++c) z4[c] = rsum16(swap_add16(z2[c], z2[c + CQ]));
+          const int l16 = lane & 15;
+          T z = z4[0];
+#pragma unroll
+          for (int c = 1; c < CQ; ++c) z = l16 == c ? z4[c] : z;
+          if (l16 < CQ) zK[cb + CQ * (lane >> 4) + l16] = z;
+        }
+      }
+      __syncthreads();
+      double s0 = 0.0, s1 = 0.0;
+      if (tid < TS) {
+        T z = T(0);
+#pragma unroll
+        for (int w = 0; w < NW; ++w) z += zred[w][tid];
+        if constexpr (!kDelta) {
+          T wait = T(0);
+#pragma clang loop unroll(disable)
+          for (int t = 0; t < sl; ++t) wait += vw[t][0][tid] * dots[0][t] + vw[t][1][tid] * dots[1][t];
+          z -= wait;
+        }
+        const double u = (double)uI[tid];
+        if (rowI) {
+          if constexpr (kTag) tag_store(yp + ((unsigned)bj * n + I0 + tid) * W, z, tag);
+          else cstore(yv + (unsigned)bj * n + I0 + tid, z);
+        }
+        s0 = wsum(u * (double)z);
+        s1 = diag ? wsum(I0 + tid >= j + 2 ? u * u : 0.0) : 0.0;
+        if (offdiag) s0 *= 2.0;
+        if (diag && rowI && I0 + tid == j + 1) tag_store(xb + ex.al, uI[tid], tag);
+        if (lane == 0) {
+          tword* const p0 = xb + ex.s0 + 8 * blk + 2 * wave;
+          tword* const p1 = xb + ex.s1 + 8 * bi + 2 * wave;
+          if constexpr (kTag) {
+            tag_store(p0, s0, tag);
+            if (diag) tag_store(p1, s1, tag);
+          } else {
+            cstore(reinterpret_cast<double*>(p0), s0);
+            if (diag) cstore(reinterpret_cast<double*>(p1), s1);
+          }
+        }
+      } else if (rowK) {
+        const int r = tid - kKT;
+        T z = zK[r];
+        if constexpr (!kDelta) {
+          T wait = T(0);
+#pragma clang loop unroll(disable)
+          for (int t = 0; t < sl; ++t) wait += vw[t][2][r] * dots[2][t] + vw[t][3][r] * dots[3][t];
+          z -= wait;
+        }
+        if constexpr (kTag) tag_store(yp + ((unsigned)bi * n + K0 + r) * W, z, tag);
+        else cstore(yv + (unsigned)bi * n + K0 + r, z);
+      }
+      if constexpr (!kTag) grid_barrier<NT>(a.bar, a.bar_base, sub_base, blk, G, jj + 1);
+      // gather: all words of a thread are in flight together
+      const bool pivot = tid == kPivT;
+      const bool sums = NT == 1024 ? tid >= 256 && tid < 512 : (tid & 255) >= 192;
+      const int swave = NT == 1024 ? wave - 4 : wave / 4, sidx = swave * kWave + lane;
+      const int row = pivot ? j + 1 : rowI ? I0 + tid : (rowK ? K0 + tid - kKT : 0);
+      const bool live = (rowI || rowK) && row >= j + 1;
+      T y = T(0), a1 = T(0);
+      if (kTag && (live || pivot)) {
+        const unsigned stride = 8u * W * (unsigned)n;
+        unsigned ro = 8u * W * (unsigned)row;
+        asm volatile("" : "+v"(ro));  // the words' offsets are not kept over the columns
+        {
+          tword w[kCh * W + W];
+          auto load = [&](int k) {
+            if (k >= kCh * W) return tag_word(cl, ro + 8u * (k - kCh * W));
+            return k / W < TR ? tag_word(yp, ro + (unsigned)(k / W) * stride + 8u * (k % W)) : (tword)tag << 32;
+          };
+          tag_load(w, load, tag, fail);
+#pragma unroll
+          for (int b = 0; b < kCh; ++b) y += tag_value<T>(w + b * W);
+          a1 = tag_value<T>(w + kCh * W);
+        }
+        for (int b0 = kCh; b0 < TR; b0 += kCh) {
+          tword w[kCh * W];
+          auto load = [&](int k) {
+            return b0 + k / W < TR ? tag_word(yp, ro + (unsigned)(b0 + k / W) * stride + 8u * (k % W)) : (tword)tag << 32;
+          };
+          tag_load(w, load, tag, fail);
+#pragma unroll
+          for (int b = 0; b < kCh; ++b) y += tag_value<T>(w + b * W);
+        }
+      }
+      if constexpr (!kTag) {
+        if (live || pivot) {
+          T t[kTRMax];
+#pragma unroll
+          for (int b = 0; b < kTRMax; ++b) t[b] = b < TR ? cload(yv + (unsigned)b * n + row) : T(0);
+          a1 = cload(cv + row);
+#pragma unroll
+          for (int b = 0; b < kTRMax; ++b) y += t[b];
+        }
+      }
+      if (sums) {
+        // the waves' sums of workgroup b (s0) and of diagonal workgroup b (s1)
+        auto gather = [&](const tword* base, int b) {
+          double g[RPL], s = 0.0;
+          if constexpr (kTag) {
+            tword w[2 * RPL];
+            tag_load(w, [&](int k) { return tag_word(base, 64u * b + 8u * k); }, tag, fail);
+#pragma unroll
+            for (int q = 0; q < RPL; ++q) g[q] = tag_value<double>(w + 2 * q);
+          } else {
+#pragma unroll
+            for (int q = 0; q < RPL; ++q) g[q] = cload(reinterpret_cast<const double*>(base + 8 * b + 2 * q));
+          }
+#pragma unroll
+          for (int q = 0; q < RPL; ++q) s += g[q];
+          return s;
+        };
+        s0 = s1 = 0.0;
+#pragma unroll
+        for (int h = 0; h < kScN; ++h) {
+          const int b = sidx + h * (kGMax / kScN + 1);
+          if (b < G && !pivot) s0 += gather(xb + ex.s0, b);
+        }
+        if (sidx < TR && !pivot) s1 = gather(xb + ex.s1, sidx);
+        s0 = wsum(s0);
+        s1 = wsum(s1);
+        if (lane == 0) {
+          red[0][swave] = s0;
+          red[1][swave] = s1;
+        }
+      }
+      if (pivot) {
+        tword w[W];
+        auto load = [&](int k) { return tag_word(xb + ex.al, 8u * k); };
+        tag_load(w, load, tag, fail);
+        piv[0] = tag_value<T>(w);
+        piv[1] = y;
+        piv[2] = a1;
+      }
+      __syncthreads();
+      // v, w and the next u on the rows of the tile (the same values for a row
+      // in every workgroup that has it)
+      if (tid < TS || (offdiag && tid >= kKT && tid - kKT < TS)) {
+        const bool isI = tid < TS;
+        const int r = isI ? tid : tid - kKT;
+        const Reflector f((double)piv[0], (red[1][0] + red[1][1]) + (red[1][2] + red[1][3]),
+                          (red[0][0] + red[0][1]) + (red[0][2] + red[0][3]), (double)piv[1], (double)piv[2]);
+        const T w1 = (T)f.w((double)piv[1], (double)piv[2], 1.0);
+        T vr = T(0), wr = T(0), un = T(0);
+        if (live) {
+          const double vd = row == j + 1 ? 1.0 : f.c * (double)(isI ? uI[r] : uK[r]);
+          vr = (T)vd;
+          wr = (T)f.w((double)y, (double)a1, vd);
+          un = a1 - (vr * w1 + wr);
+          if (diag) {
+            A[row + (unsigned)j * ld] = vr;
+            if (row == j + 1) {
+              a.d[j + 1] = un;
+              a.e[j] = (T)f.beta;
+              a.tau[j] = (T)f.tau;
             }
           }
         }
-    }
-    // partial products: rows (one sum per wave), columns off the diagonal
-    {
-      T zi[RPL], ui[RPL], zk[CW];
-#pragma unroll
-      for (int q = 0; q < RPL; ++q) {
-        zi[q] = T(0);
-        ui[q] = uI[lane + q * kWave];
+        if (row == j + 1) un = T(0);
+        if (isI) {
+          vw[sl][0][r] = vr;
+          vw[sl][1][r] = wr;
+          uI[r] = un;
+        }
+        if (diag || !isI) {
+          vw[sl][2][r] = vr;
+          vw[sl][3][r] = wr;
+          uK[r] = un;
+        }
       }
-#pragma unroll
-      for (int c = 0; c < CW; ++c) {
-        const T uk = uK[cb + c];
-        zk[c] = T(0);
+      __syncthreads();
+      if constexpr (kDelta) {
+        T vr[RPL], wr[RPL];
 #pragma unroll
         for (int q = 0; q < RPL; ++q) {
-          const T x = entry(c, q);
-          zi[q] += x * uk;
-          zk[c] += x * ui[q];
-        }
-      }
-#pragma unroll
-      for (int q = 0; q < RPL; ++q) zred[wave][lane + q * kWave] = zi[q];
-      if (offdiag) {
-        // column sums over the 64 lanes by halving exchanges: lane row R ends
-        // with columns CQ R .. CQ R + CQ - 1
-        T z2[CW / 2], z4[CQ];
-#pragma unroll
-        for (int c = 0; c < CW / 2; ++c) z2[c] = swap_add32(zk[c], zk[c + CW / 2]);
-#pragma unroll
-        for (int c = 0; c < CQ; ++c) z4[c] = rsum16(swap_add16(z2[c], z2[c + CQ]));
-        const int l16 = lane & 15;
-        T z = z4[0];
-#pragma unroll
-        for (int c = 1; c < CQ; ++c) z = l16 == c ? z4[c] : z;
-        if (l16 < CQ) zK[cb + CQ * (lane >> 4) + l16] = z;
-      }
-    }
-    __syncthreads();
-    double s0 = 0.0, s1 = 0.0;
-    if (tid < TS) {
-      T z = T(0);
-#pragma unroll
-      for (int w = 0; w < NW; ++w) z += zred[w][tid];
-      const double u = (double)uI[tid];
-      if (rowI) {
-        if constexpr (kTag) tag_store(yp + ((unsigned)bj * n + I0 + tid) * W, z, tag);
-        else cstore(yv + (unsigned)bj * n + I0 + tid, z);
-      }
-      s0 = wsum(u * (double)z);
-      s1 = diag ? wsum(I0 + tid >= j + 2 ? u * u : 0.0) : 0.0;
-      if (offdiag) s0 *= 2.0;
-      if (diag && rowI && I0 + tid == j + 1) tag_store(xb + ex.al, uI[tid], tag);
-      if (lane == 0) {
-        tword* const p0 = xb + ex.s0 + 8 * blk + 2 * wave;
-        tword* const p1 = xb + ex.s1 + 8 * bi + 2 * wave;
-        if constexpr (kTag) {
-          tag_store(p0, s0, tag);
-          if (diag) tag_store(p1, s1, tag);
-        } else {
-          cstore(reinterpret_cast<double*>(p0), s0);
-          if (diag) cstore(reinterpret_cast<double*>(p1), s1);
-        }
-      }
-    } else if (rowK) {
-      if constexpr (kTag) tag_store(yp + ((unsigned)bi * n + K0 + (tid - kKT)) * W, zK[tid - kKT], tag);
-      else cstore(yv + (unsigned)bi * n + K0 + (tid - kKT), zK[tid - kKT]);
-    }
-    if constexpr (!kTag) grid_barrier<NT>(a.bar, a.bar_base, sub_base, blk, G, jj + 1);
-    // gather: all words of a thread are in flight together
-    const bool pivot = tid == kPivT;
-    const bool sums = NT == 1024 ? tid >= 256 && tid < 512 : (tid & 255) >= 192;
-    const int swave = NT == 1024 ? wave - 4 : wave / 4, sidx = swave * kWave + lane;
-    const int row = pivot ? j + 1 : rowI ? I0 + tid : (rowK ? K0 + tid - kKT : 0);
-    const bool live = (rowI || rowK) && row >= j + 1;
-    T y = T(0), a1 = T(0);
-    if (kTag && (live || pivot)) {
-      const unsigned stride = 8u * W * (unsigned)n;
-      unsigned ro = 8u * W * (unsigned)row;
-      asm volatile("" : "+v"(ro));  // the words' offsets are not kept over the columns
-      {
-        tword w[kCh * W + W];
-        auto load = [&](int k) {
-          if (k >= kCh * W) return tag_word(cl, ro + 8u * (k - kCh * W));
-          return k / W < TR ? tag_word(yp, ro + (unsigned)(k / W) * stride + 8u * (k % W)) : (tword)tag << 32;
-        };
-        tag_load(w, load, tag, fail);
-#pragma unroll
-        for (int b = 0; b < kCh; ++b) y += tag_value<T>(w + b * W);
-        a1 = tag_value<T>(w + kCh * W);
-      }
-      for (int b0 = kCh; b0 < TR; b0 += kCh) {
-        tword w[kCh * W];
-        auto load = [&](int k) {
-          return b0 + k / W < TR ? tag_word(yp, ro + (unsigned)(b0 + k / W) * stride + 8u * (k % W)) : (tword)tag << 32;
-        };
-        tag_load(w, load, tag, fail);
-#pragma unroll
-        for (int b = 0; b < kCh; ++b) y += tag_value<T>(w + b * W);
-      }
-    }
-    if constexpr (!kTag) {
-      if (live || pivot) {
-        T t[kTRMax];
-#pragma unroll
-        for (int b = 0; b < kTRMax; ++b) t[b] = b < TR ? cload(yv + (unsigned)b * n + row) : T(0);
-        a1 = cload(cv + row);
-#pragma unroll
-        for (int b = 0; b < kTRMax; ++b) y += t[b];
-      }
-    }
-    if (sums) {
-      // the waves' sums of workgroup b (s0) and of diagonal workgroup b (s1)
-      auto gather = [&](const tword* base, int b) {
-        double g[RPL], s = 0.0;
-        if constexpr (kTag) {
-          tword w[2 * RPL];
-          tag_load(w, [&](int k) { return tag_word(base, 64u * b + 8u * k); }, tag, fail);
-#pragma unroll
-          for (int q = 0; q < RPL; ++q) g[q] = tag_value<double>(w + 2 * q);
-        } else {
-#pragma unroll
-          for (int q = 0; q < RPL; ++q) g[q] = cload(reinterpret_cast<const double*>(base + 8 * b + 2 * q));
+          vr[q] = vw[0][0][lane + q * kWave];
+          wr[q] = vw[0][1][lane + q * kWave];
         }
 #pragma unroll
-        for (int q = 0; q < RPL; ++q) s += g[q];
-        return s;
-      };
-      s0 = s1 = 0.0;
+        for (int c = 0; c < CW; ++c) {
+          const T vc = vw[0][2][cb + c], wc = vw[0][3][cb + c];
 #pragma unroll
-      for (int h = 0; h < kScN; ++h) {
-        const int b = sidx + h * (kGMax / kScN + 1);
-        if (b < G && !pivot) s0 += gather(xb + ex.s0, b);
-      }
-      if (sidx < TR && !pivot) s1 = gather(xb + ex.s1, sidx);
-      s0 = wsum(s0);
-      s1 = wsum(s1);
-      if (lane == 0) {
-        red[0][swave] = s0;
-        red[1][swave] = s1;
-      }
-    }
-    if (pivot) {
-      tword w[W];
-      auto load = [&](int k) { return tag_word(xb + ex.al, 8u * k); };
-      tag_load(w, load, tag, fail);
-      piv[0] = tag_value<T>(w);
-      piv[1] = y;
-      piv[2] = a1;
-    }
-    __syncthreads();
-    // v, w and the next u on the rows of the tile (the same values for a row
-    // in every workgroup that has it)
-    if (tid < TS || (offdiag && tid >= kKT && tid - kKT < TS)) {
-      const bool isI = tid < TS;
-      const int r = isI ? tid : tid - kKT;
-      const Reflector f((double)piv[0], (red[1][0] + red[1][1]) + (red[1][2] + red[1][3]),
-                        (red[0][0] + red[0][1]) + (red[0][2] + red[0][3]), (double)piv[1], (double)piv[2]);
-      const T w1 = (T)f.w((double)piv[1], (double)piv[2], 1.0);
-      T vr = T(0), wr = T(0), un = T(0);
-      if (live) {
-        const double vd = row == j + 1 ? 1.0 : f.c * (double)(isI ? uI[r] : uK[r]);
-        vr = (T)vd;
-        wr = (T)f.w((double)y, (double)a1, vd);
-        un = a1 - (vr * w1 + wr);
-        if (diag) {
-          A[row + (unsigned)j * ld] = vr;
-          if (row == j + 1) {
-            a.d[j + 1] = un;
-            a.e[j] = (T)f.beta;
-            a.tau[j] = (T)f.tau;
-          }
-        }
-      }
-      if (row == j + 1) un = T(0);
-      if (isI) {
-        vI[r] = vr;
-        wI[r] = wr;
-        uI[r] = un;
-      }
-      if (diag || !isI) {
-        vK[r] = vr;
-        wK[r] = wr;
-        uK[r] = un;
-      }
-    }
-    __syncthreads();
-    {
-      T vr[RPL], wr[RPL];
-#pragma unroll
-      for (int q = 0; q < RPL; ++q) {
-        vr[q] = vI[lane + q * kWave];
-        wr[q] = wI[lane + q * kWave];
-      }
-#pragma unroll
-      for (int c = 0; c < CW; ++c) {
-        const T vc = vK[cb + c], wc = wK[cb + c];
-#pragma unroll
-        for (int q = 0; q < RPL; ++q) {
-          if constexpr (kDelta) dl[c][q] += vr[q] * wc + wr[q] * vc;
-          else v[c][q] -= vr[q] * wc + wr[q] * vc;
+          for (int q = 0; q < RPL; ++q) dl[c][q] += vr[q] * wc + wr[q] * vc;
         }
       }
     }
     if constexpr (kDelta) {
-      if (jj % kFlush == kFlush - 1 || jj + 1 == a.nc) {
 #pragma unroll
-        for (int c = 0; c < CW; ++c)
+      for (int c = 0; c < CW; ++c)
+#pragma unroll
+        for (int q = 0; q < RPL; ++q) {
+          v[c][q] -= dl[c][q];
+          dl[c][q] = T(0);
+        }
+    } else {
+      constexpr int CC = 4;  // columns of the tile at a time
+      static_assert(CW % CC == 0, "whole groups of columns");
+#pragma unroll
+      for (int c0 = 0; c0 < CW; c0 += CC) {
+        T up[CC][RPL] = {};
+#pragma clang loop unroll(disable)
+        for (int t = 0; t < g1 - g0; ++t) {
+          T vr[RPL], wr[RPL];
 #pragma unroll
           for (int q = 0; q < RPL; ++q) {
-            v[c][q] -= dl[c][q];
-            dl[c][q] = T(0);
+            vr[q] = vw[t][0][lane + q * kWave];
+            wr[q] = vw[t][1][lane + q * kWave];
+          }
+#pragma unroll
+          for (int c = 0; c < CC; ++c) {
+            const T vc = vw[t][2][cb + c0 + c], wc = vw[t][3][cb + c0 + c];
+#pragma unroll
+            for (int q = 0; q < RPL; ++q) up[c][q] += vr[q] * wc + wr[q] * vc;
+          }
+        }
+#pragma unroll
+        for (int c = 0; c < CC; ++c)
+#pragma unroll
+          for (int q = 0; q < RPL; ++q) {
+            v[c0 + c][q] -= up[c][q];
+            // here, not after the other groups' loops with up kept until then
+            asm volatile("" : "+v"(v[c0 + c][q]));
           }
       }
     }
@@ -693,7 +770,7 @@ void sytrd_batched(hipStream_t st, int n, int batch, T* A, int64_t sA, T* d, T* 
     // Tile of 64 rpl rows: a small tile has less work per column (n = 1000:
     // 4.15 ms with 64 rows, 4.4 with 128, 5.1 with 192, 5.5 with 256) but
     // needs more workgroups; a batch that is not co-resident takes several
-    // launches, each as long as one (64 x 512: 2.1 ms with 256 rows in one
+    // launches, each as long as one (64 x 512: 2.3 ms with 256 rows in one
     // launch, 2.8 with 192 in two, 4.1 with 128 in three, all with the
     // barrier; with tags the 64-row tiles took 3.4 ms at n = 1000).
     int best = 0, TR = 0, chunk = 0;
