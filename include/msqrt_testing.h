@@ -86,6 +86,13 @@ msqrt_status msqrt_test_gemm_f32(int split, int ta, int tb, int64_t M, int64_t N
  * the 192 x 192-tile kernels. */
 msqrt_status msqrt_test_syrk(msqrt_prec prec, int64_t n, int64_t k, const void* A, void* C);
 
+/* Rows of the square tiles (64 or 128) that a BF16-split product op(A) op(B) of
+ * batch n x n outputs with inner dimension K takes on a device of `cus` compute
+ * units; ld: leading dimension of both operands, symmetric: lower triangle of
+ * the output only (no device work). */
+int msqrt_test_split_tile(int ta, int tb, int symmetric, int64_t n, int64_t K, int64_t ld, int64_t batch,
+                          int64_t cus);
+
 #ifdef __cplusplus
 }
 #endif

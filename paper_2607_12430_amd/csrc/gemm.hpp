@@ -1609,6 +1609,36 @@ inline GemmShape make_shape(int M, int N, int K, int64_t lda, int64_t ldb, int64
   return s;
 }
 
+// Whether gemm_split_kernel reads its k-contiguous operands 16 bytes at a time
+// in every batch entry.
+inline bool split_vec_loads(bool ta, bool tb, int64_t lda, int64_t ldb, int64_t sA, int64_t sB, const void* A,
+                            const void* B) {
+  auto ok = [](int64_t ld, int64_t stride, const void* p) {
+    return ld % 4 == 0 && stride % 4 == 0 && (reinterpret_cast<uintptr_t>(p) & 15) == 0;
+  };
+  return (!ta || ok(lda, sA, A)) && (tb || ok(ldb, sB, B));
+}
+
+// 64-tiles for a BF16-split product?  u64 and u128: tiles of the busiest CU.  The
+// split product is bound by loads and LDS writes; 64-tiles hide them better and
+// balance a few tiles better, 128-tiles load half as much.  Time of 64- over
+// 128-tiles at orders 1536 to 4224 (aligned):
+//  * one 128-tile per CU: 0.32 to 0.73; k-contiguous operands that the 128-tile
+//    kernel has to read word by word: 0.32 to 0.68;
+//  * no k-contiguous operand (NT): 0.52 to 0.97, with equal work 0.93 at two
+//    128-tiles per CU, 1.08 at three;
+//  * both k-contiguous (TN): K <= 1200 0.62 to 1.03; above, up to 6 against two
+//    128-tiles 0.91 to 1.00, 7 or 8 against two 1.03 to 1.29, against three
+//    1.03 to 1.22;
+//  * one k-contiguous (NN): K <= 300 0.59 to 0.67; from K = 512 on, up to 13/16
+//    of the work 0.74 to 0.96, 10/12 and more 0.96 to 1.21.
+inline bool split_narrow(bool ta, bool tb, int64_t K, bool vec_loads, int64_t u64, int64_t u128) {
+  if (u128 <= 1 || !vec_loads) return true;
+  if (!ta && tb) return u64 < 4 * u128 || u128 < 3;
+  if (ta && !tb) return K <= 1280 || (u128 == 2 && u64 <= 6);
+  return K < 512 || 4 * u64 <= 13 * u128;
+}
+
 // split = true selects the BF16-split kernel (float operands only).
 // Returns the number of tiles per batch entry of the launch (the count of
 // per-tile partial sums a reducing epilogue wrote), which depends on the
@@ -1625,18 +1655,14 @@ int launch_gemm(hipStream_t st, bool ta, bool tb, const GemmShape& s, const T* A
   // 165 -> 67; two against four, float 1280^3 111 -> 64; three against four,
   // float 1531^3 133 -> 130, double 246 -> 218, and nine against twelve, 64
   // symmetric 512^3 204 -> 155.  With equal work the larger tile reads LDS
-  // half as often: four against four, float 2048^3 174 -> 189.  The BF16-split
-  // product is bound by loads and LDS writes in either tile, and 64-tiles hide
-  // them better: four against four, 2048^3 160 -> 99, and 114 -> 43 for the
-  // symmetric 1531^3; only from sixteen against sixteen on the larger tile is
-  // level (4096^3 NT 719 -> 706, NN 618 -> 667), and with A transposed from
-  // three 128-tiles per CU on (symmetric 4096^3 374 -> 453).
+  // half as often: four against four, float 2048^3 174 -> 189.
   auto narrow = [&](auto sp) {
     constexpr bool kSplit = decltype(sp)::value;
     const int64_t ncu = gemm_cu_count();
     const GemmShape w0 = make_shape(s.M, s.N, s.K, s.lda, s.ldb, s.sA, s.sB, s.tri != 0, Narrow<T>::NT);
     const int64_t u128 = ceil_div((int64_t)s.ntiles * batch, ncu), u64 = ceil_div((int64_t)w0.ntiles * batch, ncu);
-    const bool fewer = kSplit ? (u64 < 4 * u128 || u128 < 4) && !(ta && !tb && u128 >= 3) : u64 <= 3 * u128;
+    const bool fewer = kSplit ? split_narrow(ta, tb, s.K, split_vec_loads(ta, tb, s.lda, s.ldb, s.sA, s.sB, A, B), u64, u128)
+                              : u64 <= 3 * u128;
     if (fewer) {
       GemmShape w = w0;
       w.K_last = s.K_last;

@@ -7,6 +7,7 @@
 
 #include "../../include/msqrt_testing.h"
 #include "kernels.hpp"
+#include "gemm.hpp"
 #include "qrchain.hpp"
 #include "schur.hpp"
 
@@ -256,6 +257,15 @@ extern "C" msqrt_status msqrt_test_gemm_f32(int split, int ta, int tb, int64_t M
     MSQRT_HIP(hipMemcpy(C, dC, sizeof(float) * nc, hipMemcpyDeviceToHost));
     return MSQRT_OK;
   });
+}
+
+extern "C" int msqrt_test_split_tile(int ta, int tb, int symmetric, int64_t n, int64_t K, int64_t ld, int64_t batch,
+                                     int64_t cus) {
+  auto per_cu = [&](int tile) {
+    return ceil_div(make_shape((int)n, (int)n, (int)K, ld, ld, 0, 0, symmetric != 0, tile).ntiles * batch, cus);
+  };
+  const bool vec = split_vec_loads(ta != 0, tb != 0, ld, ld, n * ld, n * ld, nullptr, nullptr);
+  return split_narrow(ta != 0, tb != 0, K, vec, per_cu(64), per_cu(128)) ? 64 : 128;
 }
 
 extern "C" msqrt_status msqrt_test_syrk(msqrt_prec prec, int64_t n, int64_t k, const void* A,
