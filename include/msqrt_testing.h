@@ -86,6 +86,10 @@ msqrt_status msqrt_test_gemm_f32(int split, int ta, int tb, int64_t M, int64_t N
  * the 192 x 192-tile kernels. */
 msqrt_status msqrt_test_syrk(msqrt_prec prec, int64_t n, int64_t k, const void* A, void* C);
 
+/* Co-resident workgroups per compute unit of the tile solvers of the general
+ * path, complex (cplx = 1) or real, for large orders; negative on an error. */
+int msqrt_test_tile_occupancy(msqrt_prec prec, int cplx);
+
 /* Rows of the square tiles (64 or 128) that a BF16-split product op(A) op(B) of
  * batch n x n outputs with inner dimension K takes on a device of `cus` compute
  * units; ld: leading dimension of both operands, symmetric: lower triangle of

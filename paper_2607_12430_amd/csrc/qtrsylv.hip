@@ -114,6 +114,28 @@ __device__ inline void qload_tile(T (*dst)[kQb + 1], const T* P, int64_t ld, int
   }
 }
 
+// The quasi-triangular diagonal tiles S_II and S2_JJ (mi and mj rows) in LDS: the
+// upper triangles share D, S_II(r, c) in D[c][r], S2_JJ(r, c) in D[r][c + 1]; the
+// subdiagonals S_II(c + 1, c) in sub[0][c], S2_JJ(c + 1, c) in sub[1][c].
+template <typename T>
+__device__ inline void qload_diagonals(T (*D)[kQb + 1], T (*sub)[kQb], const T* A, int64_t lda, int rA, int mi,
+                                       const T* B, int64_t ldb, int rB, int mj, bool coherent) {
+  auto get = [&](const T* P, int64_t ld, int r, int m, int i, int j) {
+    if (max(i, j) >= m) return T(0);
+    return coherent ? qload_c(P, ld, r + i, r + j) : P[(r + i) + (int64_t)(r + j) * ld];
+  };
+  for (int x = threadIdx.x; x < kQb * kQb; x += blockDim.x) {
+    const int i = x % kQb, j = x / kQb;
+    if (i <= j) {
+      D[j][i] = get(A, lda, rA, mi, i, j);
+      D[i][j + 1] = get(B, ldb, rB, mj, i, j);
+    } else if (i == j + 1) {
+      sub[0][j] = get(A, lda, rA, mi, i, j);
+      sub[1][j] = get(B, ldb, rB, mj, i, j);
+    }
+  }
+}
+
 // Partial products of C = A B (32 x 32 x 32) on MFMA: wave w sums the inner
 // indices 8w .. 8w+7 into P[w][col][row] (C = P0 + P1 + P2 + P3).  P may
 // overlay As and Bs: every wave reads its operands before the barrier.
@@ -210,14 +232,15 @@ __device__ inline void small_sylvester(int p, int q, const T (&A)[2][2], const T
   }
 }
 
-// Diagonal block structure of the LDS tile X[col][row] of order mm: block b
-// starts at bs[b] & 0xff and has bs[b] >> 8 rows, blk[i] is the block of row
-// i.  Row i is the second row of a 2x2 block when X(i, i-1) != 0.  Called by
-// one whole wave; returns the number of blocks in every lane of it.
-template <typename T>
-__device__ inline int tile_blocks(const T (*X)[kQb + 1], int mm, int* bs, int* blk) {
+// Diagonal block structure of a tile of order mm with subdiagonal entries
+// sub(c) = X(c + 1, c): block b starts at bs[b] & 0xff and has bs[b] >> 8 rows,
+// blk[i] is the block of row i.  Row i is the second row of a 2x2 block when
+// X(i, i-1) != 0.  Called by one whole wave; returns the number of blocks in
+// every lane of it.
+template <class Sub>
+__device__ inline int tile_blocks(Sub sub, int mm, int* bs, int* blk) {
   const int i = threadIdx.x % kWave;
-  const bool start = i < mm && (i == 0 || X[i - 1][i] == T(0));
+  const bool start = i < mm && (i == 0 || sub(i - 1) == 0);
   const unsigned mask = (unsigned)__ballot(start);
   if (i < mm) {
     const int b = __popc(mask & (~0u >> (31 - i))) - 1;
@@ -228,14 +251,18 @@ __device__ inline int tile_blocks(const T (*X)[kQb + 1], int mm, int* bs, int* b
   return __popc(mask);
 }
 
-template <typename T>
-__global__ __launch_bounds__(kQThreads) void qtile_kernel(QTileArgs a, const T* A, const T* B, T* X) {
-  __shared__ T ABs[4][kQb][kQb + 1];  // As = ABs[0], Bs = ABs[1]; products overlay all four
+// kOcc: workgroups of a CU to leave registers for (see launch_qtiles).
+template <typename T, int kOcc>
+__global__ __launch_bounds__(kQThreads, kOcc) void qtile_kernel(QTileArgs a, const T* A, const T* B, T* X) {
+  // As = ABs[0], Bs = ABs[1]; products overlay all four, and after the last one
+  // the tile's solution and right-hand side take two of them, so that LDS does
+  // not bound the workgroups of a CU, whose loads overlap
+  __shared__ T ABs[4][kQb][kQb + 1];
   T (*As)[kQb + 1] = ABs[0];
   T (*Bs)[kQb + 1] = ABs[1];
-  __shared__ T Ad[kQb][kQb + 1], Bd[kQb][kQb + 1];  // the diagonal tiles S_II and S2_JJ
-  __shared__ T Ys[kQb][kQb + 1];
-  __shared__ T Cs[kQb][kQb + 1];
+  T (*Ys)[kQb + 1] = ABs[2];
+  T (*Cs)[kQb + 1] = ABs[3];
+  __shared__ T D[kQb][kQb + 1], sub[2][kQb];  // the diagonal tiles, see qload_diagonals
   __shared__ int rbs[kQb], cbs[kQb], rblk[kQb], cblk[kQb];
   __shared__ int sh_nrb, sh_ncb, sh_tk;
   const int t = threadIdx.x;
@@ -280,7 +307,7 @@ __global__ __launch_bounds__(kQThreads) void qtile_kernel(QTileArgs a, const T* 
     for (int q = 0; q < 4; ++q) Ys[tj0 + 8 * q][ti] = acc[q];
     for (int x = t; x < kQb * kQb; x += blockDim.x) As[x / kQb][x % kQb] = T(0);
     __syncthreads();
-    if (wave == 0) sh_nrb = tile_blocks<T>(Ys, mi, rbs, rblk);
+    if (wave == 0) sh_nrb = tile_blocks([&](int c) { return Ys[c][c + 1]; }, mi, rbs, rblk);
     __syncthreads();
     const int nb = sh_nrb;
     if (t < nb) {
@@ -354,41 +381,38 @@ __global__ __launch_bounds__(kQThreads) void qtile_kernel(QTileArgs a, const T* 
     if (a.mode == 0) {
       qwait_tile(a, I, I);
       qwait_tile(a, J, J);
-      qload_tile(Ad, X, a.ldx, r0, r0, mi, mi, true);
-      qload_tile(Bd, X, a.ldx, c0, c0, mj, mj, true);
+      qload_diagonals(D, sub, (const T*)X, a.ldx, r0, mi, (const T*)X, a.ldx, c0, mj, true);
     } else {
-      qload_tile(Ad, A, a.lda, r0, r0, mi, mi, false);
-      qload_tile(Bd, B, a.ldb, c0, c0, mj, mj, false);
+      qload_diagonals(D, sub, A, a.lda, r0, mi, B, a.ldb, c0, mj, false);
     }
     __syncthreads();
-    if (wave == 0) sh_nrb = tile_blocks<T>(Ad, mi, rbs, rblk);
-    if (wave == 1) sh_ncb = tile_blocks<T>(Bd, mj, cbs, cblk);
+    if (wave == 0) sh_nrb = tile_blocks([&](int c) { return sub[0][c]; }, mi, rbs, rblk);
+    if (wave == 1) sh_ncb = tile_blocks([&](int c) { return sub[1][c]; }, mj, cbs, cblk);
     __syncthreads();
     const int nrb = sh_nrb, ncb = sh_ncb;
     T coef[4][4];   // entry (ti, tj0 + 8 q): Y = sum_v coef[v] C(i0 + v % 2, j0 + v / 2)
     int ed[4];      // block anti-diagonal of the entry (-1: outside the tile)
-    int src[4][4];  // C(i0 + v % 2, j0 + v / 2) as an offset into Cs
+    int src[4];     // C(i0, j0) as an offset into Cs; bit 16: the block has two columns
     const int ib = ti < mi ? rblk[ti] : 0;
+    const int i0 = rbs[ib] & 0xff, pr = rbs[ib] >> 8;
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
       const int j = tj0 + 8 * q;
       ed[q] = -1;
       if (ti < mi && j < mj) {
         const int jb = cblk[j];
-        const int i0 = rbs[ib] & 0xff, pr = rbs[ib] >> 8, j0 = cbs[jb] & 0xff, qc = cbs[jb] >> 8;
+        const int j0 = cbs[jb] & 0xff, qc = cbs[jb] >> 8;
         T At[2][2], Bt[2][2], ev[4];
 #pragma unroll
         for (int r = 0; r < 2; ++r)
 #pragma unroll
           for (int c = 0; c < 2; ++c) {
-            At[c][r] = (r < pr && c < pr) ? Ad[i0 + c][i0 + r] : T(0);
-            Bt[c][r] = (r < qc && c < qc) ? Bd[j0 + c][j0 + r] : T(0);
+            At[c][r] = r >= pr || c >= pr ? T(0) : r > c ? sub[0][i0] : D[i0 + c][i0 + r];
+            Bt[c][r] = r >= qc || c >= qc ? T(0) : r > c ? sub[1][j0] : D[j0 + r][j0 + c + 1];
           }
 #pragma unroll
-        for (int v = 0; v < 4; ++v) {
-          ev[v] = v == (ti - i0) + 2 * (j - j0) ? T(1) : T(0);
-          src[q][v] = (j0 + ((v >> 1) < qc ? v >> 1 : 0)) * (kQb + 1) + i0 + ((v & 1) < pr ? v & 1 : 0);
-        }
+        for (int v = 0; v < 4; ++v) ev[v] = v == (ti - i0) + 2 * (j - j0) ? T(1) : T(0);
+        src[q] = (j0 * (kQb + 1) + i0) | (qc - 1) << 16;
         small_sylvester<T>(pr, qc, At, Bt, ev, coef[q]);
         ed[q] = (nrb - 1 - ib) + jb;
       }
@@ -454,9 +478,9 @@ __global__ __launch_bounds__(kQThreads) void qtile_kernel(QTileArgs a, const T* 
 #pragma unroll
       for (int q = 0; q < 4; ++q)
         if (ed[q] == e) {
-          const T* c = &Cs[0][0];
-          Ys[tj0 + 8 * q][ti] = (coef[q][0] * c[src[q][0]] + coef[q][1] * c[src[q][1]]) +
-                                (coef[q][2] * c[src[q][2]] + coef[q][3] * c[src[q][3]]);
+          const T* c = &Cs[0][0] + (src[q] & 0xffff);
+          const T* d = c + (src[q] >> 16) * (kQb + 1);
+          Ys[tj0 + 8 * q][ti] = (coef[q][0] * c[0] + coef[q][1] * c[pr - 1]) + (coef[q][2] * d[0] + coef[q][3] * d[pr - 1]);
         }
       __syncthreads();
       T la[4][2], lb[4][2], ya[4][2], yb[2];
@@ -468,12 +492,12 @@ __global__ __launch_bounds__(kQThreads) void qtile_kernel(QTileArgs a, const T* 
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
         const int j = tj0 + 8 * q, k0 = kc4[q] & 0xff, k1 = k0 + (kc4[q] >> 8) - 1;
-        la[q][0] = Ad[k0][ti];
-        la[q][1] = Ad[k1][ti];
+        la[q][0] = D[k0][ti];
+        la[q][1] = D[k1][ti];
         ya[q][0] = Ys[j][k0];
         ya[q][1] = Ys[j][k1];
-        lb[q][0] = Bd[j][l0];
-        lb[q][1] = Bd[j][l1];
+        lb[q][0] = D[l0][j + 1];
+        lb[q][1] = D[l1][j + 1];
         kn[q] = kcode(q, e + 1);
       }
       lc = lcode(e + 1);
@@ -513,11 +537,33 @@ void launch_qtiles(hipStream_t st, QTileArgs a, const T* A, const T* B, T* X, Tr
   if (fresh) MSQRT_HIP(hipMemsetAsync(a.err, 0, sizeof(int) * 4, st));
   MSQRT_HIP(hipMemsetAsync(buf, 0, sizeof(int) * (nflags + 64), st));
   if (a.ntiles <= 0) return;
-  hipLaunchKernelGGL(qtile_kernel<T>, dim3(a.ntiles), dim3(kQThreads), 0, st, a, A, B, X);
+  // Up to order 4096 a solve is bound by the chain of tiles along its wavefronts,
+  // above by the tile products, whose loads more workgroups per CU hide.  Double
+  // fits three without spilling (order 6144: 68 ms with two, 49 with three).  Float
+  // takes 122 registers (four per CU); 96 (five) spill a part of the prepared
+  // block equations.  Solve with four and with five, ms: order 2048 4.0 and 4.9,
+  // 4096 11.2 and 11.3, 5120 20.3 and 18.7, 8192 75.5 and 66.5.  The square root
+  // has half the products: level at order 7168.
+  const bool many = sizeof(T) == 4 && a.mode != 0 && (int64_t)a.mt * a.pt > 128 * 128;
+  if constexpr (sizeof(T) == 4) {
+    if (many) hipLaunchKernelGGL((qtile_kernel<T, 5>), dim3(a.ntiles), dim3(kQThreads), 0, st, a, A, B, X);
+  }
+  if (!many)
+    hipLaunchKernelGGL((qtile_kernel<T, sizeof(T) == 4 ? 4 : 3>), dim3(a.ntiles), dim3(kQThreads), 0, st, a, A, B, X);
   MSQRT_LAUNCH_CHECK();
 }
 
 }  // namespace
+
+template <typename T>
+int qtile_occupancy() {
+  int k = 0;
+  const void* f = sizeof(T) == 4 ? (const void*)qtile_kernel<float, 5> : (const void*)qtile_kernel<double, 3>;
+  MSQRT_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&k, f, kQThreads, 0));
+  return k;
+}
+template int qtile_occupancy<float>();
+template int qtile_occupancy<double>();
 
 std::vector<int> quasi_partition(int n, const unsigned char* sub) {
   std::vector<int> b{0};

@@ -72,6 +72,12 @@ void trsyl_quasi(hipStream_t st, int m, int p, const T* S, int64_t lds, const in
 // timed_out = a dataflow wait timed out, nonprincipal = a diagonal entry of T
 // on or next to R<=0.
 void trsylv_reset(hipStream_t st, TrsylvWork& w);
+// Workgroups of a CU of the tile solvers (real: the variant for many tiles).
+template <typename T>
+int tile_occupancy();
+template <typename T>
+int qtile_occupancy();
+
 void trsylv_errors(hipStream_t st, TrsylvWork& w, int* timed_out, int* nonprincipal);
 
 // S = T^{1/2} (principal) for upper triangular T (stacked, n x n); S may not

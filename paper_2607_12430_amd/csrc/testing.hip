@@ -259,6 +259,16 @@ extern "C" msqrt_status msqrt_test_gemm_f32(int split, int ta, int tb, int64_t M
   });
 }
 
+extern "C" int msqrt_test_tile_occupancy(msqrt_prec prec, int cplx) {
+  int k = -1;
+  guarded([&] {
+    if (prec == MSQRT_PREC_FP64) k = cplx ? tile_occupancy<double>() : qtile_occupancy<double>();
+    else k = cplx ? tile_occupancy<float>() : qtile_occupancy<float>();
+    return MSQRT_OK;
+  });
+  return k;
+}
+
 extern "C" int msqrt_test_split_tile(int ta, int tb, int symmetric, int64_t n, int64_t K, int64_t ld, int64_t batch,
                                      int64_t cus) {
   auto per_cu = [&](int tile) {

@@ -123,6 +123,20 @@ __device__ inline void load_tile(cx<T> (*dst)[kTb + 1], const T* P, int64_t ld, 
   }
 }
 
+// The upper triangles of the diagonal tiles S_II and S2_JJ (mi and mj rows) in
+// one LDS tile: S_II(r, c) in D[c][r], S2_JJ(r, c) in D[r][c + 1].
+template <typename T>
+__device__ inline void load_diagonals(cx<T> (*D)[kTb + 1], const T* A, int64_t lda, int rA, int mi, const T* B,
+                                      int64_t ldb, int rB, int mj, bool coherent) {
+  for (int x = threadIdx.x; x < kTb * kTb; x += blockDim.x) {
+    const int i = x % kTb, j = x / kTb;
+    if (i > j) continue;
+    const cx<T> z = {T(0), T(0)};
+    D[j][i] = j >= mi ? z : coherent ? tload_c(A, lda, rA + i, rA + j) : tload(A, lda, rA + i, rA + j);
+    D[i][j + 1] = j >= mj ? z : coherent ? tload_c(B, ldb, rB + i, rB + j) : tload(B, ldb, rB + i, rB + j);
+  }
+}
+
 // The four real products of one complex 32 x 32 x 32 tile product C = A B
 // on MFMA, one per wave: P0 = Ar Br, P1 = Ai Bi, P2 = Ar Bi, P3 = Ai Br
 // (so Cr = P0 - P1, Ci = P2 + P3), stored to P[w][col][row].  A and B are
@@ -172,16 +186,21 @@ __device__ inline void tile_product_mfma(const cx<T> (*As)[kTb + 1], const cx<T>
 }
 
 template <typename T>
-__global__ __launch_bounds__(kTThreads) void tile_kernel(TileArgs a, const T* A, const T* B, T* X) {
+__global__ __launch_bounds__(kTThreads, sizeof(T) == 4 ? 6 : 3) void tile_kernel(TileArgs a, const T* A, const T* B, T* X) {
   // A and B operand tiles ([col][row]) in one array: after the MFMA products
-  // have read them, the same storage holds the four real products
+  // have read them, the same storage holds the four real products, and after the
+  // last product the tile's solution.  LDS bounds the workgroups of a CU and so
+  // the tiles whose loads overlap, which large orders are bound by (complex
+  // double 4096: 43 ms for a solve with one per CU, 21 with three; float 6144: 52
+  // and 34 with three and six).  The launch bounds keep the MFMA accumulators
+  // out of further registers, which count as well.
   __shared__ cx<T> ABs[2][kTb][kTb + 1];
   cx<T> (*As)[kTb + 1] = ABs[0];
   cx<T> (*Bs)[kTb + 1] = ABs[1];
   T (*Pp)[kTb][kTb + 1] = reinterpret_cast<T (*)[kTb][kTb + 1]>(&ABs[0][0][0]);
   static_assert(sizeof(ABs) == 4 * kTb * (kTb + 1) * sizeof(T), "product overlay");
-  __shared__ cx<T> Ad[kTb][kTb + 1], Bd[kTb][kTb + 1];  // the diagonal tiles S_II and S2_JJ
-  __shared__ cx<T> Ys[kTb][kTb + 1];
+  cx<T> (*Ys)[kTb + 1] = ABs[1];
+  __shared__ cx<T> D[kTb][kTb + 1];  // the diagonal tiles, see load_diagonals
   __shared__ int sh_tk;
   const int t = threadIdx.x;
   const int ti = t % kTb, tj0 = t / kTb;  // owned entries (ti, tj0 + 8 q)
@@ -259,11 +278,9 @@ __global__ __launch_bounds__(kTThreads) void tile_kernel(TileArgs a, const T* A,
       if (a.mode == 0) {
         wait_tile(a, I, I);
         wait_tile(a, J, J);
-        load_tile(Ad, X, a.ldx, kTb * I, kTb * I, mi, mi, true);
-        load_tile(Bd, X, a.ldx, kTb * J, kTb * J, mj, mj, true);
+        load_diagonals(D, (const T*)X, a.ldx, kTb * I, mi, (const T*)X, a.ldx, kTb * J, mj, true);
       } else {
-        load_tile(Ad, A, a.lda, kTb * I, kTb * I, mi, mi, false);
-        load_tile(Bd, B, a.ldb, kTb * J, kTb * J, mj, mj, false);
+        load_diagonals(D, A, a.lda, kTb * I, mi, B, a.ldb, kTb * J, mj, false);
       }
       __syncthreads();
       cx<T> inv[4];
@@ -273,7 +290,7 @@ __global__ __launch_bounds__(kTThreads) void tile_kernel(TileArgs a, const T* A,
         const int j = tj0 + 8 * q;
         const bool in = ti < mi && j < mj;
         ed[q] = in ? (mi - 1 - ti) + j : -1;
-        inv[q] = in ? cdiv(cx<T>{T(1), T(0)}, cadd(Ad[ti][ti], Bd[j][j])) : cx<T>{T(0), T(0)};
+        inv[q] = in ? cdiv(cx<T>{T(1), T(0)}, cadd(D[ti][ti], D[j][j + 1])) : cx<T>{T(0), T(0)};
       }
       if (a.mode == 0) {
         // S_IK S_KJ is ready once tiles (I, K) and (K, J) are, i.e. at
@@ -335,10 +352,10 @@ __global__ __launch_bounds__(kTThreads) void tile_kernel(TileArgs a, const T* A,
         for (int q = 0; q < 4; ++q) {
           const int j = tj0 + 8 * q;
           const int k = min(max(mi - 1 - e + j, 0), kTb - 1);  // (k, j) is on e
-          l1[q] = Ad[k][ti];
+          l1[q] = D[k][ti];
           y1[q] = Ys[j][k];
           y2[q] = Ys[k2c][ti];
-          l2[q] = Bd[j][k2c];
+          l2[q] = D[k2c][j + 1];
         }
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
@@ -383,6 +400,15 @@ void launch_tiles(hipStream_t st, TileArgs a, const T* A, const T* B, T* X, Trsy
 }
 
 }  // namespace
+
+template <typename T>
+int tile_occupancy() {
+  int k = 0;
+  MSQRT_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&k, (const void*)tile_kernel<T>, kTThreads, 0));
+  return k;
+}
+template int tile_occupancy<float>();
+template int tile_occupancy<double>();
 
 void trsylv_reset(hipStream_t st, TrsylvWork& w) {
   int* e = w.ticket.ensure<int>(4);
