@@ -24,6 +24,11 @@ msqrt_status msqrt_test_sytrd(msqrt_prec prec, int64_t n, const void* A, void* d
  * written for `column` (no device work). */
 uint32_t msqrt_test_sytrd_tag(int64_t column);
 
+/* Device memory in bytes, per matrix of the batch, through which the workgroups
+ * of the tridiagonal reduction exchange values on a device of `cus` compute
+ * units; -1 if the order is not supported (no device work). */
+int64_t msqrt_test_sytrd_exchange(msqrt_prec prec, int64_t n, int64_t batch, int64_t cus);
+
 /* Two-stage tridiagonalisation A = Q T Q^T (dense -> band -> tridiagonal) of
  * the symmetric n x n column-major A (n <= 4104): the diagonal d (n) and
  * off-diagonal e (n-1) of T, and Q (n x n column-major) formed by the

@@ -33,7 +33,7 @@ EXPORTED = [
     "msqrt_sqrtm_backward", "msqrt_factor_destroy", "msqrt_status_string", "msqrt_last_error",
     "msqrt_release_cached",
     "msqrt_factor_wrap", "msqrt_factor_export", "msqrt_test_sytrd", "msqrt_test_sy2tr",
-    "msqrt_test_sytrd_tag", "msqrt_test_stedc",
+    "msqrt_test_sytrd_tag", "msqrt_test_sytrd_exchange", "msqrt_test_stedc",
     "msqrt_test_gehrd", "msqrt_test_schur", "msqrt_test_qr_step", "msqrt_test_trsqrt", "msqrt_test_trsyl",
     "msqrt_test_trcbrt", "msqrt_rootm",
     "msqrt_test_gemm_f32", "msqrt_test_split_tile", "msqrt_test_tile_occupancy",
@@ -129,6 +129,8 @@ def lib():
     L.msqrt_profile_list.argtypes = [ctypes.c_char_p, ci]
     L.msqrt_profile_list.restype = ci
     L.msqrt_test_sytrd.argtypes = [ci, i64, vp, vp, vp, vp]
+    L.msqrt_test_sytrd_exchange.argtypes = [ci, i64, i64, i64]
+    L.msqrt_test_sytrd_exchange.restype = i64
     L.msqrt_test_sytrd_tag.argtypes = [i64]
     L.msqrt_test_sytrd_tag.restype = ctypes.c_uint32
     L.msqrt_test_sy2tr.argtypes = [ci, i64, vp, vp, vp, vp]

@@ -248,6 +248,16 @@ extern "C" msqrt_status msqrt_test_sytrd(msqrt_prec prec, int64_t n, const void*
   }
 }
 
+extern "C" int64_t msqrt_test_sytrd_exchange(msqrt_prec prec, int64_t n, int64_t batch, int64_t cus) {
+  if (n < 1 || n > sytrd_max_n() || batch < 1 || batch > (1 << 24) || cus < 1 || cus > (1 << 20)) return -1;
+  try {
+    return prec == MSQRT_PREC_FP64 ? sytrd_exchange_bytes<double>((int)n, (int)batch, (int)cus)
+                                   : sytrd_exchange_bytes<float>((int)n, (int)batch, (int)cus);
+  } catch (const Error&) {
+    return -1;
+  }
+}
+
 extern "C" uint32_t msqrt_test_sytrd_tag(int64_t column) { return sytrd_tag((int)column); }
 
 extern "C" msqrt_status msqrt_test_sy2tr(msqrt_prec prec, int64_t n, const void* A, void* d,

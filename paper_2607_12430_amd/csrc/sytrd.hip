@@ -717,16 +717,61 @@ void launch_tail(hipStream_t st, int n, int p, int batch, T* A, int64_t sA, T* d
 // Largest co-resident grid of one panel kernel.
 template <typename T, int RPL>
 int panel_resident() {
-  static int r = 0;
-  if (r == 0) {
+  static const int r = [] {
     int per_cu = 0, ncu = 0, dev = 0;
     MSQRT_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(
         &per_cu, (const void*)sytrd_panel_kernel<T, RPL>, (Tile<T, RPL>::NT), 0));
     MSQRT_HIP(hipGetDevice(&dev));
     MSQRT_HIP(hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev));
-    r = std::max(1, std::min(per_cu, 1)) * std::max(1, ncu);  // one workgroup per CU
-  }
+    return std::max(1, std::min(per_cu, 1)) * std::max(1, ncu);  // one workgroup per CU
+  }();
   return r;
+}
+
+// One panel launch: columns p .. p + nc - 1 with tiles of 64 rpl rows, TR per
+// dimension, `chunk` batch entries at a time.
+struct PanelLaunch {
+  int p, nc, rpl, TR, chunk;
+};
+
+// The launches that leave kTailRows rows; res[rpl - 1]: co-resident workgroups.
+// Tile of 64 rpl rows: a small tile has less work per column (n = 1000: 4.15 ms
+// with 64 rows, 4.4 with 128, 5.1 with 192, 5.5 with 256) but needs more
+// workgroups; a batch that is not co-resident takes several launches, each as
+// long as one (64 x 512: 2.3 ms with 256 rows in one launch, 2.8 with 192 in two,
+// 4.1 with 128 in three, all with the barrier; with tags the 64-row tiles took
+// 3.4 ms at n = 1000).
+template <typename T>
+std::vector<PanelLaunch> panel_launches(int n, int batch, const int (&res)[4]) {
+  std::vector<PanelLaunch> plan;
+  for (int p = 0; n - p > kTailRows<T>; p += plan.back().nc) {
+    const int m = n - p;
+    PanelLaunch best{p, std::min(kLaunchCols, m - kTailRows<T>), 0, 0, 0};
+    double cost = 0.0;
+    for (int rpl = 1; rpl <= 4; ++rpl) {
+      const int tr = (int)ceil_div(m, kWave * rpl), g = tr * (tr + 1) / 2;
+      if (tr > kTRMax || g > res[rpl - 1]) continue;
+      const int ch = std::min(batch, res[rpl - 1] / g);
+      // (256-row tiles of doubles spill: for the one order that needs them)
+      const double c = (double)ceil_div(batch, ch) * (5.0 + 0.25 * rpl * rpl) * (rpl == 4 && sizeof(T) == 8 ? 8.0 : 1.0);
+      if (best.rpl == 0 || c < cost) {
+        best = {p, best.nc, rpl, tr, ch};
+        cost = c;
+      }
+    }
+    if (best.rpl == 0) throw Error{MSQRT_ERR_UNSUPPORTED, "tridiagonal reduction: the device holds too few workgroups"};
+    plan.push_back(best);
+  }
+  return plan;
+}
+
+// Words that one batch entry's launches exchange through: two buffers of the
+// largest layout among them.
+template <typename T>
+int64_t exchange_words(int n, const std::vector<PanelLaunch>& plan) {
+  int64_t size = 0;
+  for (const PanelLaunch& l : plan) size = std::max(size, Exchange<T>(n, l.TR).size);
+  return 2 * size;
 }
 
 template <typename T>
@@ -757,39 +802,17 @@ void sytrd_batched(hipStream_t st, int n, int batch, T* A, int64_t sA, T* d, T* 
     launch_tail<T>(st, n, 0, batch, A, sA, d, e, tau, sD);
     return;
   }
-  const int64_t sX = 2 * Exchange<T>(n, kTRMax).size;
+  const int res[4] = {panel_resident<T, 1>(), panel_resident<T, 2>(), panel_resident<T, 3>(), panel_resident<T, 4>()};
+  const std::vector<PanelLaunch> plan = panel_launches<T>(n, batch, res);
+  const int64_t sX = exchange_words<T>(n, plan);
   tword* x = w.x.ensure<tword>(sX * batch);
   unsigned* bar = w.bar.ensure<unsigned>((int64_t)kBarWords * batch);
   // no word carries a tag yet
   MSQRT_HIP(hipMemsetAsync(x, 0, sizeof(tword) * (size_t)(sX * batch), st));
   MSQRT_HIP(hipMemsetAsync(bar, 0, sizeof(unsigned) * (size_t)kBarWords * batch, st));
   BarrierBase bar_base{};
-  int p = 0;
-  while (n - p > kTailRows<T>) {
-    const int m = n - p, nc = std::min(kLaunchCols, m - kTailRows<T>);
-    // Tile of 64 rpl rows: a small tile has less work per column (n = 1000:
-    // 4.15 ms with 64 rows, 4.4 with 128, 5.1 with 192, 5.5 with 256) but
-    // needs more workgroups; a batch that is not co-resident takes several
-    // launches, each as long as one (64 x 512: 2.3 ms with 256 rows in one
-    // launch, 2.8 with 192 in two, 4.1 with 128 in three, all with the
-    // barrier; with tags the 64-row tiles took 3.4 ms at n = 1000).
-    int best = 0, TR = 0, chunk = 0;
-    double cost = 0.0;
-    for (int rpl = 1; rpl <= 4; ++rpl) {
-      const int tr = (int)ceil_div(m, kWave * rpl), g = tr * (tr + 1) / 2;
-      const int res = rpl == 1 ? panel_resident<T, 1>() : rpl == 2 ? panel_resident<T, 2>() : rpl == 3 ? panel_resident<T, 3>() : panel_resident<T, 4>();
-      if (tr > kTRMax || g > res) continue;
-      const int ch = std::min(batch, res / g);
-      // (256-row tiles of doubles spill: for the one order that needs them)
-      const double c = (double)ceil_div(batch, ch) * (5.0 + 0.25 * rpl * rpl) * (rpl == 4 && sizeof(T) == 8 ? 8.0 : 1.0);
-      if (best == 0 || c < cost) {
-        best = rpl;
-        TR = tr;
-        chunk = ch;
-        cost = c;
-      }
-    }
-    if (best == 0) throw Error{MSQRT_ERR_UNSUPPORTED, "tridiagonal reduction: the device holds too few workgroups"};
+  for (const PanelLaunch& l : plan) {
+    const int p = l.p, m = n - p, nc = l.nc, best = l.rpl, TR = l.TR, chunk = l.chunk;
     const int G = TR * (TR + 1) / 2, ts = (int)ceil_div(m, TR);
     const int tok = prof_begin(st);
     for (int b0 = 0; b0 < batch; b0 += chunk) {
@@ -821,10 +844,17 @@ void sytrd_batched(hipStream_t st, int n, int batch, T* A, int64_t sA, T* d, T* 
       prof_end(tok, st, sizeof(T) == 4 ? "sytrd_panel_f32" : "sytrd_panel_f64",
                4.0 * (double)m * m * nc * batch, bytes * batch);
     }
-    p += nc;
   }
-  launch_tail<T>(st, n, p, batch, A, sA, d, e, tau, sD);
+  launch_tail<T>(st, n, plan.back().p + plan.back().nc, batch, A, sA, d, e, tau, sD);
 }
+
+template <typename T>
+int64_t sytrd_exchange_bytes(int n, int batch, int cus) {
+  const int res[4] = {cus, cus, cus, cus};
+  return (int64_t)sizeof(tword) * exchange_words<T>(n, panel_launches<T>(n, batch, res));
+}
+template int64_t sytrd_exchange_bytes<float>(int, int, int);
+template int64_t sytrd_exchange_bytes<double>(int, int, int);
 
 template <typename T>
 void sytrd(hipStream_t st, int n, T* A, T* d, T* e, T* tau, SytrdWork& w) {

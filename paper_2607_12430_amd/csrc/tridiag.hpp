@@ -42,6 +42,9 @@ void sytrd(hipStream_t st, int n, T* A, T* d, T* e, T* tau, SytrdWork& w);
 template <typename T>
 void sytrd_batched(hipStream_t st, int n, int batch, T* A, int64_t sA, T* d, T* e, T* tau,
                    int64_t sD, SytrdWork& w);
+// Exchanged words of one entry in bytes, on a device of `cus` compute units.
+template <typename T>
+int64_t sytrd_exchange_bytes(int n, int batch, int cus);
 // Tag of the words exchanged for a column.
 unsigned sytrd_tag(int column);
 // True if a wait of the last reduction timed out (synchronous).

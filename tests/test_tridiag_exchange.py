@@ -24,6 +24,27 @@ def test_no_value_looks_like_a_written_word():
     assert not set(tags.tolist()) & {0x7FC00000, 0xFFC00000, 0x7FF80000, 0xFFF80000}
 
 
+@pytest.mark.parametrize("prec,word", [("fp32", 1), ("fp64", 2)])
+def test_exchange_memory_is_that_of_the_tiles_in_use(prec, word):
+    """Two buffers of TR partial products, a column, a scalar and 64 bytes of sums
+    per workgroup and diagonal workgroup; with at least 64 rows to a tile TR is
+    at most n / 64 (not the 22 of the largest order), and at least one buffer of
+    the largest tiles' layout has to be there."""
+    from paper_2607_12430_amd import _lib
+    size = _lib.lib().msqrt_test_sytrd_exchange
+
+    def layout(n, tr):
+        return 2 * 8 * (tr * n * word + n * word + word + 8 * tr * (tr + 1) // 2 + 8 * tr)
+
+    for n in (193, 257, 300, 400, 512, 700, 1000, 1408, 1409, 2500, 4225):
+        for batch in (1, 2, 64, 1000):
+            got = size(_lib.PREC_NAMES[prec], n, batch, 256)
+            if prec == "fp32" and n <= 256:
+                assert got == 0  # the one-workgroup tail exchanges nothing
+                continue
+            assert layout(n, -(-n // 256)) <= got <= layout(n, min(22, -(-n // 64))), (n, batch)
+
+
 def _kernel_matrix(n, length, nugget):
     x = np.arange(n)
     return np.exp(-((x[:, None] - x[None, :]) / length) ** 2 / 2) + nugget * np.eye(n)
