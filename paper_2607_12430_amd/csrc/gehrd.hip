@@ -593,8 +593,10 @@ void reduce(hipStream_t st, int n, T* H, T* Z, GehrdWork& w) {
   T* Bo = w.W.ensure<T>((P == 2 ? 8 : 2) * pl);
   E* ex = w.part.ensure<E>(n + 2 * kMaxG * kNb);
   unsigned* bar = w.bar.ensure<unsigned>(kBarWords);
-  MSQRT_HIP(hipMemsetAsync(bar, 0, sizeof(unsigned) * kBarWords, st));
-  w.nbar = 1;
+  if (G > 1) {
+    MSQRT_HIP(hipMemsetAsync(bar, 0, sizeof(unsigned) * kBarWords, st));
+    w.nbar = 1;
+  }
   BarrierBase base{};
 
   // K-chunks of the V^* products: about four waves per CU, at least one group
