@@ -1017,15 +1017,9 @@ bool schur_qr(hipStream_t st, int n, typename A::T* H, typename A::T* Z, HseqrWo
               typename A::T hnorm) {
   using T = typename A::T;
   constexpr int W = A::W;
-  static bool attr_set = false;
-  if (!attr_set) {
-    MSQRT_HIP(hipFuncSetAttribute((const void*)qr_small_kernel<A>,
-                                  hipFuncAttributeMaxDynamicSharedMemorySize, (int)win_lds<A>()));
-    MSQRT_HIP(hipFuncSetAttribute((const void*)qr_chase_kernel<A>,
-                                  hipFuncAttributeMaxDynamicSharedMemorySize, (int)win_lds<A>()));
-    attr_set = true;
-  }
   if (n <= 0) return true;
+  gemm_lds_attr(qr_small_kernel<A>, win_lds<A>());
+  gemm_lds_attr(qr_chase_kernel<A>, win_lds<A>());
   // two neighbouring finished ranges together have more than W rows
   const int max_ranges = 2 * n / W + 2;
   T* U = w.U.ensure<T>(std::max(max_ranges, kMaxChains) * u_elems<A>());
