@@ -253,7 +253,7 @@ extern "C" int64_t msqrt_test_sytrd_exchange(msqrt_prec prec, int64_t n, int64_t
   try {
     return prec == MSQRT_PREC_FP64 ? sytrd_exchange_bytes<double>((int)n, (int)batch, (int)cus)
                                    : sytrd_exchange_bytes<float>((int)n, (int)batch, (int)cus);
-  } catch (const Error&) {
+  } catch (...) {
     return -1;
   }
 }

@@ -60,14 +60,6 @@ __device__ inline V rsum16(V v) {
   v += dpp_v<0x140>(v);
   return v;
 }
-// Sum over each group of 8 lanes (half a row), left in every lane of it.
-template <typename V>
-__device__ inline V hsum8(V v) {
-  v += dpp_v<0xB1>(v);
-  v += dpp_v<0x4E>(v);
-  v += dpp_v<0x141>(v);
-  return v;
-}
 template <typename V>
 __device__ inline V wsum(V v) {
   v += dpp_v<0xB1>(v);   // quad_perm [1, 0, 3, 2]
@@ -158,8 +150,9 @@ struct BarrierBase {
 // arrivals over 8 counters halves the cost of a barrier of 253 workgroups
 // against one shared counter.  Every thread waits for its own coherent
 // stores to complete before the workgroup arrives.  The counters are handled
-// by the first lane of the last wave (kBarT), which has no row work, so the
-// atomics' round trips hold up no thread that has.  A spin limit keeps a
+// by the first lane of the last wave (kBarT), which has no row work in the
+// tridiagonal kernel, nor in the Hessenberg one with blocks of less than 512
+// rows, so the atomics' round trips hold up no thread that has.  A spin limit keeps a
 // broken launch from hanging: it raises the sticky failure flag.
 template <int NT>
 constexpr int kBarT = NT - kWave;

@@ -554,8 +554,7 @@ msqrt_status msqrt_factor_wrap(msqrt_prec prec, msqrt_struct structure, msqrt_dt
   f->kexp.assign(1, 0);
   f->anorm.assign(1, 0.0);
   f->upload_scales(nullptr);
-  MSQRT_HIP(hipStreamSynchronize(nullptr));  // the factor may be used on any stream
-  MSQRT_HIP(hipDeviceSynchronize());
+  MSQRT_HIP(hipDeviceSynchronize());  // the factor may be used on any stream
   *out = reinterpret_cast<msqrt_factor_t>(f.release());
   return MSQRT_OK;
   MSQRT_API_END
