@@ -24,7 +24,7 @@ __global__ __launch_bounds__(256) void finish_hpd_kernel(int n, const double* la
   double mn = INFINITY;
   for (int i = threadIdx.x; i < n; i += blockDim.x) {
     const double l = lam[i];
-    mn = fmin(mn, l);
+    mn = l == l ? fmin(mn, l) : -INFINITY;
     s[i] = (T)sqrt(fmax(l, 0.0));
   }
   mn = -block_max(-mn, red);

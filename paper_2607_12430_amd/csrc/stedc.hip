@@ -20,6 +20,7 @@
 // non-deflated secular problem and unit columns for deflated entries, both
 // placed in ascending order of the merged eigenvalues.
 #include <algorithm>
+#include <climits>
 #include <cmath>
 #include <vector>
 
@@ -103,6 +104,12 @@ __device__ inline int64_t blk_off(int s, int n) {
   const int e = s / n, sl = s - e * n;
   return (int64_t)e * n * n + sl + (int64_t)sl * n;
 }
+
+// Exponent of an entry whose tridiagonal matrix has an Inf or NaN: its blocks are
+// solved as zero matrices, because the merges place columns by comparisons, and
+// its eigenvalues are NaN.
+constexpr int kNonFinite = INT_MIN;
+__device__ inline double scaled_eig(double l, int ex) { return ex == kNonFinite ? NAN : ldexp(l, ex); }
 
 // Per-position metadata arrays (all length n, indexed by s + local index).
 struct Meta {
@@ -225,7 +232,8 @@ __global__ __launch_bounds__(64) void leaf_kernel(int depth, const double* dg, c
   }
   __syncthreads();
   if (lane < L) {
-    lam[s + rank[lane]] = ldexp(d[lane], ex + (depth == 0 ? exs[blockIdx.x] : 0));
+    const double l = ldexp(d[lane], ex);
+    lam[s + rank[lane]] = depth == 0 ? scaled_eig(l, exs[blockIdx.x]) : l;
     T* Zb = Z + blk_off<kB>(s, n);
     for (int c = 0; c < L; ++c) Zb[lane + (int64_t)rank[c] * (kB ? kBand : n)] = (T)Zl[lane][c];
   }
@@ -248,6 +256,9 @@ __global__ __launch_bounds__(256) void merge_prep_kernel(int depth, const double
   const T* Zg = Z + blk_off<kB>(s, n);
   const int ldz = kB ? kBand : n;
   __shared__ double red[4];
+  // every position names a column whatever the values are
+  for (int i = threadIdx.x; i < m; i += blockDim.x) mt.tmpc[s + i] = i;
+  __syncthreads();
   // merge-path placement of the two ascending halves
   double dmax = 0.0, zmax = 0.0;
   for (int i = threadIdx.x; i < m; i += blockDim.x) {
@@ -640,7 +651,7 @@ __global__ __launch_bounds__(64) void vectors_kernel(int depth, Meta mt, const i
       col[mt.cl[g.s + i]] = (T)v;
     }
     for (int i = lane; i < nd; i += kWave) col[mt.defc[g.s + i]] = T(0);
-    if (lane == 0) lam_new[g.s + j + lo] = ldexp(lj, ex);
+    if (lane == 0) lam_new[g.s + j + lo] = scaled_eig(lj, ex);
   } else if (q < k + nd) {
     const int t = q - k;
     const double v = mt.defd[g.s + t];
@@ -649,7 +660,7 @@ __global__ __launch_bounds__(64) void vectors_kernel(int depth, Meta mt, const i
     T* col = Mb + (int64_t)(t + lo) * m;
     const int one = mt.defc[g.s + t];
     for (int i = lane; i < m; i += kWave) col[i] = T(i == one ? 1 : 0);
-    if (lane == 0) lam_new[g.s + t + lo] = ldexp(v, ex);
+    if (lane == 0) lam_new[g.s + t + lo] = scaled_eig(v, ex);
   }
 }
 
@@ -723,12 +734,20 @@ __global__ __launch_bounds__(1024) void tear_kernel(int n, int depth, const T* d
   dd += (int64_t)blockIdx.x * n;
   ee += (int64_t)blockIdx.x * n;
   double mx = 0.0;
-  for (int i = threadIdx.x; i < n; i += blockDim.x)
-    mx = fmax(mx, fmax(fabs((double)d[i]), i + 1 < n ? fabs((double)e[i]) : 0.0));
-  mx = block_max(mx, red);
-  const int ex = mx > 0.0 && mx < INFINITY ? ilogb(mx) : 0;
-  if (threadIdx.x == 0) exs[blockIdx.x] = ex;
+  auto take = [&](double v) { mx = v <= mx ? mx : v < INFINITY ? v : INFINITY; };  // NaN counts as Inf
   for (int i = threadIdx.x; i < n; i += blockDim.x) {
+    take(fabs((double)d[i]));
+    if (i + 1 < n) take(fabs((double)e[i]));
+  }
+  mx = block_max(mx, red);
+  const bool finite = mx < INFINITY;
+  const int ex = mx > 0.0 && finite ? ilogb(mx) : 0;
+  if (threadIdx.x == 0) exs[blockIdx.x] = finite ? ex : kNonFinite;
+  for (int i = threadIdx.x; i < n; i += blockDim.x) {
+    if (!finite) {
+      dd[i] = ee[i] = 0.0;
+      continue;
+    }
     double v = ldexp((double)d[i], -ex);
     Block bl{0, n, 0};
     for (int l = 0; l < depth && bl.m > kLeaf; ++l) {
