@@ -137,13 +137,14 @@ __device__ inline double swap_add16(double a, double b) {
 
 // The reflector and the product w of one column from its sums: alpha =
 // u_{j+1}, sig = ||u_{j+2..}||^2, uAu = u^T A u, y1 and a11 = entries j+1 of
-// A u and of column j+1.
+// A u and of column j+1.  A column of norm below 1e-140 (the matrix is scaled to
+// about 1) counts as reduced: its squares underflow and 1 / |u|^2 overflows.
 struct Reflector {
   double beta, tau, c, wv;  // wv = tau v^T A v
   __device__ Reflector(double alpha, double sig, double uAu, double y1, double a11) {
     beta = alpha;
     tau = c = 0.0;
-    if (sig != 0.0) {
+    if (sig != 0.0 && alpha * alpha + sig > 1e-280) {
       beta = -copysign(sqrt(alpha * alpha + sig), alpha);
       tau = (beta - alpha) / beta;
       c = 1.0 / (alpha - beta);
