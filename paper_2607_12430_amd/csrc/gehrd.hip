@@ -41,6 +41,12 @@ constexpr size_t kLdsMax = 150 * 1024;
 constexpr int kMaxBy = 8;  // workgroups (of four K-chunks) per 32 columns of a V^* product
 constexpr int kPad = 8 * (kThreads / 16);  // zeros behind the exchanged column in LDS: one group of 8 per lane
 
+// Squared norm of a column (of a matrix scaled to about 1) below which it counts
+// as reduced: its squares lose digits or underflow, and v would not be the
+// reflector of tau.  Its norm is far below the rounding of the reduction.
+template <typename T>
+constexpr T kTinyNorm2 = sizeof(T) == 4 ? T(1e-30) : T(1e-280);
+
 // Element arithmetic shared by the real and the complex reduction.
 template <typename T>
 struct HReal {
@@ -64,8 +70,9 @@ struct HReal {
   __device__ static void reflector(E alpha, T s2, T& beta, E& tau, E& scal) {
     beta = alpha;
     tau = scal = T(0);
-    if (s2 == T(0)) return;
-    beta = -copysign(sqrt(alpha * alpha + s2), alpha);
+    const T n2 = alpha * alpha + s2;
+    if (s2 == T(0) || n2 < kTinyNorm2<T>) return;
+    beta = -copysign(sqrt(n2), alpha);
     tau = (beta - alpha) / beta;
     scal = T(1) / (alpha - beta);
   }
@@ -99,8 +106,9 @@ struct HCplx {
   __device__ static void reflector(E alpha, T s2, T& beta, E& tau, E& scal) {
     beta = alpha.r;
     tau = scal = zero();
-    if (s2 == T(0) && alpha.i == T(0)) return;
-    beta = -copysign(sqrt(alpha.r * alpha.r + alpha.i * alpha.i + s2), alpha.r);
+    const T n2 = alpha.r * alpha.r + alpha.i * alpha.i + s2;
+    if ((s2 == T(0) && alpha.i == T(0)) || n2 < kTinyNorm2<T>) return;
+    beta = -copysign(sqrt(n2), alpha.r);
     tau = {(beta - alpha.r) / beta, -alpha.i / beta};
     scal = cdiv(cx<T>{T(1), T(0)}, csub(alpha, cx<T>{beta, T(0)}));
   }
