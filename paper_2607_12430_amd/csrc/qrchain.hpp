@@ -181,6 +181,27 @@ struct RealRoute {
   __device__ static void cols(Refl f, E (&y)[3]) { rows(f, y); }
   // shift pair q from the q-th trailing 2 x 2 block [[a, b], [c, d]]
   __device__ static Shift shift(int, E a, E b, E c, E d) { return {a + d, a * d - b * c}; }
+  // shift pairs from the quasi-triangular h of order m, the last blocks first; two
+  // real eigenvalues make a pair
+  __device__ static int eigen_shifts(const E* h, int ldh, int m, Shift* out) {
+    int cnt = 0;
+    bool single = false;
+    T x = T(0);
+    for (int k = m - 1; k >= 0;) {
+      const T d = h[k + k * ldh];
+      if (k > 0 && h[k + (k - 1) * ldh] != T(0)) {
+        out[cnt++] = shift(0, h[k - 1 + (k - 1) * ldh], h[k - 1 + k * ldh], h[k + (k - 1) * ldh], d);
+        k -= 2;
+      } else {
+        if (single) out[cnt++] = {x + d, x * d};
+        single = !single;
+        x = d;
+        k -= 1;
+      }
+    }
+    if (single) out[cnt++] = {x + x, x * x};
+    return cnt;
+  }
   __device__ static int shift_block(int q) { return q; }
   __device__ static Shift exceptional(int q, E d, T e) {
     const T re = d + (q % 2 ? -e : e) * T(0.75) * T(1 + q % 3), im = T(0.5) * e;
@@ -271,6 +292,10 @@ struct CplxRoute {
     const E l1 = cadd(mid, disc), l2 = csub(mid, disc);
     const bool first = abs1(csub(l1, d)) <= abs1(csub(l2, d));
     return first == (q % 2 == 0) ? l1 : l2;
+  }
+  __device__ static int eigen_shifts(const E* h, int ldh, int m, Shift* out) {
+    for (int k = 0; k < m; ++k) out[k] = h[m - 1 - k + (m - 1 - k) * ldh];
+    return m;
   }
   __device__ static int shift_block(int q) { return q / 2; }
   __device__ static Shift exceptional(int q, E d, T e) {
@@ -720,33 +745,24 @@ __device__ __forceinline__ void standardize_all(typename A::E* h, typename A::E*
   }
 }
 
-// Finishes the diagonal blocks list[2 b], list[2 b + 1] = first row, order
-// (at most W), b < *cnt: (quasi-)triangular form with U.  Sweeps of up to
-// kNb bulges; a wave finds the split points of the whole block by ballots,
-// so every wave knows them without an exchange.
+// (Quasi-)triangular form of the LDS block h (order m) with u: sweeps of up to
+// kNb bulges; a wave finds the split points of the whole block by ballots, so
+// every wave knows them without an exchange.  Shifts from several 2 x 2 blocks
+// can go round in circles (a block of 3 I + the cyclic permutation of order 600
+// did, in double); a block that has not deflated for kPatience sweeps gets the
+// one from its last 2 x 2 block.  Returns false when the iteration limit is hit.
+constexpr int kPatience = 20;
 template <class A>
-__global__ __launch_bounds__(kThreads) void qr_small_kernel(int n, typename A::T* H, const int* list,
-                                                            const int* cnt, typename A::T* U,
-                                                            int* status, typename A::T hnorm) {
+__device__ __forceinline__ bool lds_schur(typename A::E* h, typename A::E* u, int m, typename A::T hnorm,
+                                          typename A::Shift* sh) {
   using T = typename A::T;
   using E = typename A::E;
   constexpr int W = A::W, LD = W + 1;
   static_assert(W <= 2 * kWave, "two ballots cover a block");
-  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-  E* h = reinterpret_cast<E*>(smem);
-  E* u = h + (W + 1) * W + kPad;
-  __shared__ typename A::Shift sh[kNb];
-  const int b = blockIdx.x;
-  if (b >= cnt[0]) return;
-  const int s = list[2 * b], m = list[2 * b + 1];
-  const int64_t ld = A::ldim(n);
-  win_load<A>(h, u, H, ld, s, m, 1);
-  __syncthreads();
   const int lane = threadIdx.x % kWave;
   const bool w0 = __builtin_amdgcn_readfirstlane((int)threadIdx.x / kWave) == 0;
   const int itmax = 30 * max(10, m);
   int hi = m - 1, its = 0, total = 0;
-  bool ok = true;
   for (;;) {
     // split points: bit k of the mask is set when block boundary k | k-1 is
     // negligible (bit 0 always)
@@ -772,10 +788,10 @@ __global__ __launch_bounds__(kThreads) void qr_small_kernel(int n, typename A::T
     }
     hi = __builtin_amdgcn_readfirstlane(hi);
     l = __builtin_amdgcn_readfirstlane(l);
-    if (hi < 0) break;
+    if (hi < 0) return true;
     its = hi == hi0 ? its + 1 : 1;
-    if (++total > itmax) { ok = false; break; }
-    const int nb = A::small_bulges(hi - l + 1);
+    if (++total > itmax) return false;
+    const int nb = its > kPatience ? 1 : A::small_bulges(hi - l + 1);
     if ((int)threadIdx.x < nb) {
       const int q = threadIdx.x, p = hi - 2 * A::shift_block(q);
       typename A::Shift v = A::shift(q, h[p - 1 + (p - 1) * LD], h[p - 1 + p * LD], h[p + (p - 1) * LD], h[p + p * LD]);
@@ -789,10 +805,55 @@ __global__ __launch_bounds__(kThreads) void qr_small_kernel(int n, typename A::T
     __syncthreads();
     rounds<A, false>(h, u, m, l - 1, hi - l + A::SPAN * (nb - 1), l, hi, nb, sh);
   }
+}
+
+// Finishes the diagonal blocks list[2 b], list[2 b + 1] = first row, order
+// (at most W), b < *cnt: (quasi-)triangular form with U.
+template <class A>
+__global__ __launch_bounds__(kThreads) void qr_small_kernel(int n, typename A::T* H, const int* list,
+                                                            const int* cnt, typename A::T* U,
+                                                            int* status, typename A::T hnorm) {
+  using E = typename A::E;
+  constexpr int W = A::W;
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+  E* h = reinterpret_cast<E*>(smem);
+  E* u = h + (W + 1) * W + kPad;
+  __shared__ typename A::Shift sh[kNb];
+  const int b = blockIdx.x;
+  if (b >= cnt[0]) return;
+  const int s = list[2 * b], m = list[2 * b + 1];
+  const int64_t ld = A::ldim(n);
+  win_load<A>(h, u, H, ld, s, m, 1);
+  __syncthreads();
+  const bool ok = lds_schur<A>(h, u, m, hnorm, sh);
   __syncthreads();
   if (!ok && threadIdx.x == 0) atomicOr(status, 1);
   if constexpr (!A::kComplex) standardize_all<A>(h, u, m);
   win_store<A>(h, u, H, ld, s, m, A::kFinal - 1, U + b * u_elems<A>());
+}
+
+// Shifts of a batch as the eigenvalues of the trailing block of order m (rows
+// s ..) of the active block; H is only read.  One workgroup.  The shifts stay as
+// they are if that block does not converge.
+template <class A>
+__global__ __launch_bounds__(kThreads) void qr_shift_kernel(int n, typename A::T* H, int s, int m,
+                                                            typename A::T* shifts, typename A::T hnorm) {
+  using E = typename A::E;
+  constexpr int W = A::W, LD = W + 1;
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+  E* h = reinterpret_cast<E*>(smem);
+  E* u = h + (W + 1) * W + kPad;
+  __shared__ typename A::Shift sh[kNb], list[A::W];
+  __shared__ int cnt;
+  win_load<A>(h, u, H, A::ldim(n), s, m, 1);
+  __syncthreads();
+  const bool ok = lds_schur<A>(h, u, m, hnorm, sh);
+  __syncthreads();
+  if (!ok) return;
+  if (threadIdx.x == 0) cnt = A::eigen_shifts(h, LD, m, list);
+  __syncthreads();
+  typename A::Shift* sp = reinterpret_cast<typename A::Shift*>(shifts);
+  for (int q = threadIdx.x; q < kMaxChains * kNb; q += kThreads) sp[q] = list[q % cnt];
 }
 
 // Deflation test on rows 0..hi0 of H, one workgroup.  Negligible subdiagonal
@@ -1020,6 +1081,7 @@ bool schur_qr(hipStream_t st, int n, typename A::T* H, typename A::T* Z, HseqrWo
   if (n <= 0) return true;
   gemm_lds_attr(qr_small_kernel<A>, win_lds<A>());
   gemm_lds_attr(qr_chase_kernel<A>, win_lds<A>());
+  gemm_lds_attr(qr_shift_kernel<A>, win_lds<A>());
   // two neighbouring finished ranges together have more than W rows
   const int max_ranges = 2 * n / W + 2;
   T* U = w.U.ensure<T>(std::max(max_ranges, kMaxChains) * u_elems<A>());
@@ -1033,10 +1095,12 @@ bool schur_qr(hipStream_t st, int n, typename A::T* H, typename A::T* Z, HseqrWo
   aa.Z = Z;
   aa.U = U;
   int hi = n - 1, lo = 0, batches = 0, stuck = 0;
+  std::vector<int> ends;  // hi of every batch
   const int max_batches = 30 * std::max(10, n / 16) + 100;
   for (;;) {
+    const bool ex = stuck > 0 && stuck % 6 == 0;  // exceptional shifts if the block stays
     hipLaunchKernelGGL(qr_scan_kernel<A>, dim3(1), dim3(kThreads), sizeof(unsigned) * (hi / 32 + 1), st, n,
-                       H, hi, lo, (stuck > 0 && stuck % 6 == 0) ? 1 : 0, flag + 4, list, shifts, hnorm);
+                       H, hi, lo, ex ? 1 : 0, flag + 4, list, shifts, hnorm);
     MSQRT_LAUNCH_CHECK();
     int res[2];
     MSQRT_HIP(hipMemcpyAsync(res, flag + 4, sizeof(res), hipMemcpyDeviceToHost, st));
@@ -1046,7 +1110,25 @@ bool schur_qr(hipStream_t st, int n, typename A::T* H, typename A::T* Z, HseqrWo
     hi = res[0];
     lo = res[1];
     if (++batches > max_batches || stuck > 300) return false;  // no progress: give up
-    const int total = A::batch_bulges(hi - lo + 1);
+    int total = A::batch_bulges(hi - lo + 1);
+    // Shifts from separate 2 x 2 blocks are poor when the trailing block is close to
+    // a multiple of an orthogonal matrix (3 I + a cyclic permutation): then the
+    // eigenvalues of the whole trailing block, which cost as much as a few batches
+    // (float 0.3, complex double 0.9 ms).  Order 256 in double 63 -> 40 ms, where
+    // single chains with such shifts took 33; random matrices deflate faster and
+    // never get here.
+    ends.push_back(hi);
+    constexpr int kLook = 6;  // batches
+    const int eigs = total * (A::kComplex ? 1 : 2);
+    const bool poor = batches > 10 && 4 * (ends[ends.size() - 1 - kLook] - hi) < eigs;
+    if (poor && !ex) {
+      const int ms = 3 * kNb;
+      static_assert(3 * kNb <= W, "the block fits a window");
+      hipLaunchKernelGGL(qr_shift_kernel<A>, dim3(1), dim3(kThreads), win_lds<A>(), st, n, H, hi - ms + 1, ms, shifts,
+                         hnorm);
+      MSQRT_LAUNCH_CHECK();
+      total = std::min(total, A::kComplex ? ms : ms / 2);
+    }
     const int K = (int)ceil_div(total, chain_bulges<A>()), nb = (int)ceil_div(total, K);
     // the windows of one chain; bulge j sits at kbase - SPAN j
     std::vector<ChainWin> win;

@@ -1,0 +1,39 @@
+"""Shifted QR on matrices for which shifts from separate 2 x 2 blocks are poor or
+go round in circles: a multiple of the identity plus an orthogonal (unitary)
+matrix, plain permutations above all, whose Hessenberg form is the matrix
+itself and whose eigenvalues all have one distance from every diagonal block's."""
+
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+
+def _root(a, prec):
+    import torch
+    import paper_2607_12430_amd as msq
+    d = torch.from_numpy(np.ascontiguousarray(a)).cuda()
+    x, info = msq.sqrtm(d, prec=prec, structure="general", fallback=False)
+    assert info["status"] == "ok" and info["relres"] <= 1e-13
+    r = torch.linalg.matrix_norm(x @ x - d) / torch.linalg.matrix_norm(d)
+    assert float(r) <= 2e-13
+
+
+@pytest.mark.parametrize("prec", ["fp32", "fp64"])
+@pytest.mark.parametrize("n", [20, 64, 97, 129, 200, 256, 300, 500, 600, 601, 700])
+def test_cyclic_permutation(prec, n):
+    print(f"[qr convergence] cyclic {prec} n={n}", flush=True)
+    _root(3.0 * np.eye(n) + np.roll(np.eye(n), 1, axis=0), prec)
+    _root(3.0 * np.eye(n) + np.roll(np.eye(n), -1, axis=0), prec)
+    _root((3.0 + 0j) * np.eye(n) + 1j * np.roll(np.eye(n), 1, axis=0), prec)
+
+
+@pytest.mark.parametrize("prec", ["fp32", "fp64"])
+@pytest.mark.parametrize("n", [130, 257, 600])
+def test_orthogonal_and_permutation(prec, n):
+    r = np.random.default_rng(n)
+    print(f"[qr convergence] orthogonal {prec} n={n}", flush=True)
+    q, _ = np.linalg.qr(r.standard_normal((n, n)))
+    _root(3.0 * np.eye(n) + q, prec)
+    _root(3.0 * np.eye(n) + np.eye(n)[r.permutation(n)], prec)
+    _root(3.0 * np.eye(n) + np.kron(np.roll(np.eye(n // 4 + 1), 1, axis=0), np.eye(4))[:n, :n], prec)
