@@ -91,6 +91,13 @@ msqrt_status msqrt_test_gemm_f32(int split, int ta, int tb, int64_t M, int64_t N
  * the 192 x 192-tile kernels. */
 msqrt_status msqrt_test_syrk(msqrt_prec prec, int64_t n, int64_t k, const void* A, void* C);
 
+/* C_b = op(A_b) op(B_b) + beta C_b for `batch` double matrices one after the other
+ * (column-major host buffers; op(A_b) is M x K, op(B_b) K x N, leading dimensions
+ * the row counts).  K_last is the inner dimension of the last entry, whose
+ * operands are as large as the others'; K_last != K needs beta = 0. */
+msqrt_status msqrt_test_gemm_f64(int ta, int tb, int64_t M, int64_t N, int64_t K, int64_t K_last, int64_t batch,
+                                 const double* A, const double* B, double beta, double* C);
+
 /* Co-resident workgroups per compute unit of the tile solvers of the general
  * path, complex (cplx = 1) or real, for large orders; negative on an error. */
 int msqrt_test_tile_occupancy(msqrt_prec prec, int cplx);

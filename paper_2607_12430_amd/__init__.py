@@ -373,6 +373,22 @@ def test_gemm_f32(a, b, split=False, ta=False, tb=False):
     return c
 
 
+def test_gemm_f64(a, b, c=None, ta=False, tb=False, k_last=None):
+    """Test hook: C_b = op(A_b) op(B_b) + C_b (c = None: no C) for a batch of
+    float64 matrices (batch, rows, columns); k_last: inner dimension of the last."""
+    import numpy as np
+    cm = lambda x: np.ascontiguousarray(np.swapaxes(np.asarray(x, np.float64), 1, 2))
+    nb = a.shape[0]
+    m, k = (a.shape[2], a.shape[1]) if ta else (a.shape[1], a.shape[2])
+    n = b.shape[1] if tb else b.shape[2]
+    out = cm(c).copy() if c is not None else np.zeros((nb, n, m))
+    af, bf = cm(a), cm(b)
+    vp = lambda x: x.ctypes.data_as(ctypes.c_void_p)
+    check(lib().msqrt_test_gemm_f64(1 if ta else 0, 1 if tb else 0, m, n, k, k if k_last is None else k_last, nb,
+                                    vp(af), vp(bf), 0.0 if c is None else 1.0, vp(out)), "msqrt_test_gemm_f64")
+    return np.swapaxes(out, 1, 2)
+
+
 def test_syrk(a, prec="fp32"):
     """Test hook: C = A A^T through the symmetric-output (mirroring) GEMM."""
     import numpy as np

@@ -36,7 +36,7 @@ EXPORTED = [
     "msqrt_test_sytrd_tag", "msqrt_test_sytrd_exchange", "msqrt_test_stedc",
     "msqrt_test_gehrd", "msqrt_test_schur", "msqrt_test_qr_step", "msqrt_test_trsqrt", "msqrt_test_trsyl",
     "msqrt_test_trcbrt", "msqrt_rootm",
-    "msqrt_test_gemm_f32", "msqrt_test_split_tile", "msqrt_test_tile_occupancy",
+    "msqrt_test_gemm_f32", "msqrt_test_gemm_f64", "msqrt_test_split_tile", "msqrt_test_tile_occupancy",
     "msqrt_test_syrk", "msqrt_features", "msqrt_mlp_forward", "msqrt_mlp_grad",
     "msqrt_mlp_adam", "msqrt_selector_set", "msqrt_selector_load", "msqrt_selector_clear",
     "msqrt_selector_installed",
@@ -145,6 +145,7 @@ def lib():
                               ctypes.POINTER(Info)]
     L.msqrt_test_trsyl.argtypes = [ci, i64, i64, dp, dp, dp, dp]
     L.msqrt_test_gemm_f32.argtypes = [ci, ci, ci, i64, i64, i64, vp, vp, vp]
+    L.msqrt_test_gemm_f64.argtypes = [ci, ci, i64, i64, i64, i64, i64, vp, vp, cd, vp]
     L.msqrt_test_split_tile.argtypes = [ci, ci, ci, i64, i64, i64, i64, i64]
     L.msqrt_test_split_tile.restype = ci
     L.msqrt_test_tile_occupancy.argtypes = [ci, ci]
@@ -167,7 +168,7 @@ def lib():
                  "msqrt_test_stedc", "msqrt_test_gehrd", "msqrt_test_schur", "msqrt_test_qr_step",
                  "msqrt_test_trsqrt",
                  "msqrt_test_trcbrt", "msqrt_rootm",
-                 "msqrt_test_trsyl", "msqrt_test_gemm_f32", "msqrt_test_syrk", "msqrt_features",
+                 "msqrt_test_trsyl", "msqrt_test_gemm_f32", "msqrt_test_gemm_f64", "msqrt_test_syrk", "msqrt_features",
                  "msqrt_mlp_forward", "msqrt_mlp_grad", "msqrt_mlp_adam", "msqrt_selector_set",
                  "msqrt_selector_load"):
         getattr(L, name).restype = ci

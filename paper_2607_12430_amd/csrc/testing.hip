@@ -259,6 +259,29 @@ extern "C" msqrt_status msqrt_test_gemm_f32(int split, int ta, int tb, int64_t M
   });
 }
 
+extern "C" msqrt_status msqrt_test_gemm_f64(int ta, int tb, int64_t M, int64_t N, int64_t K, int64_t K_last,
+                                            int64_t batch, const double* A, const double* B, double beta, double* C) {
+  if (M < 1 || N < 1 || K < 1 || K_last < 1 || K_last > K || batch < 1 || !A || !B || !C || M > 65536 || N > 65536 ||
+      K > 65536 || batch > 65535 || (K_last != K && beta != 0.0))
+    return MSQRT_ERR_INVALID_ARG;
+  return guarded([&] {
+    DevBuf ab, bb, cb;
+    double* dA = upload(ab, std::vector<double>(A, A + M * K * batch));
+    double* dB = upload(bb, std::vector<double>(B, B + K * N * batch));
+    double* dC = upload(cb, std::vector<double>(C, C + M * N * batch));
+    const int64_t lda = ta ? K : M, ldb = tb ? N : K;
+    if (K_last != K)
+      gemm_store_splitk<double>(nullptr, ta != 0, tb != 0, (int)M, (int)N, (int)K, (int)K_last, dA, lda, M * K, dB,
+                                ldb, K * N, dC, M, M * N, (int)batch);
+    else
+      gemm_store_f64(nullptr, ta != 0, tb != 0, (int)M, (int)N, (int)K, dA, lda, M * K, dB, ldb, K * N, dC, M, M * N,
+                     1.0, beta, (int)batch, false);
+    MSQRT_HIP(hipDeviceSynchronize());
+    MSQRT_HIP(hipMemcpy(C, dC, sizeof(double) * M * N * batch, hipMemcpyDeviceToHost));
+    return MSQRT_OK;
+  });
+}
+
 extern "C" int msqrt_test_tile_occupancy(msqrt_prec prec, int cplx) {
   int k = -1;
   guarded([&] {

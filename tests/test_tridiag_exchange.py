@@ -71,11 +71,11 @@ def test_kernel_matrix(prec, n, length, nugget):
     assert np.max(np.abs(got - lam)) <= 2 * n * u * np.max(np.abs(lam))
 
 
-# The same change of tiles for dense matrices, and from 192- over 128- to
-# 64-row tiles in one reduction.
+# The same change of tiles for dense matrices, from 192- over 128- to 64-row tiles
+# in one reduction, and the largest order (256-row tiles first).
 @pytest.mark.gpu
 @pytest.mark.parametrize("prec", ["fp32", "fp64"])
-@pytest.mark.parametrize("n", [1409, 1500, 2900])
+@pytest.mark.parametrize("n", [1409, 1500, 2900, 4225])
 def test_dense(prec, n):
     import paper_2607_12430_amd as msq
     from scipy.linalg import eigvalsh_tridiagonal
