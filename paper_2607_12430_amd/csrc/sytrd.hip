@@ -16,7 +16,7 @@
 // columns, then writes its tiles back; the next one cuts the smaller trailing
 // matrix anew.  The last kTailRows rows take one workgroup (sytrd_tail_kernel).
 //
-// The exchange.  Small tiles (kTag): every word carries its column number, so
+// The exchange.  Small tiles (kTag): every word carries its column's tag, so
 // the reads that gather it are the wait; the scalars from every workgroup
 // also say that all have read the words of the column before, whose buffer
 // the next column takes.  Words go out twice as wide and are read again until
@@ -835,13 +835,9 @@ void sytrd_batched(hipStream_t st, int n, int batch, T* A, int64_t sA, T* d, T* 
         for (int g = 0; g < 8; ++g) bar_base.sub[g] += (unsigned)(G / 8 + (g < G % 8 ? 1 : 0)) * (unsigned)nc;
     }
     if (tok >= 0) {
-      // algorithmic traffic: one read of the symmetric trailing matrix (lower
-      // triangle) per column for its product with the reflector
-      double bytes = 0.0;
-      for (int jj = 0; jj < nc; ++jj) {
-        const double mj = (double)(m - 1 - jj);
-        bytes += 0.5 * mj * (mj + 1.0) * sizeof(T);
-      }
+      // what the launch has to move: the lower triangle of the trailing matrix
+      // into registers, the rest of it back, and the reflectors
+      const double r = m - nc, bytes = (0.5 * m * (m + 1.0) + 0.5 * r * (r + 1.0) + (double)nc * m) * sizeof(T);
       prof_end(tok, st, sizeof(T) == 4 ? "sytrd_panel_f32" : "sytrd_panel_f64",
                4.0 * (double)m * m * nc * batch, bytes * batch);
     }
