@@ -125,7 +125,10 @@ struct RealRoute {
   static constexpr int W = sizeof(T) == 4 ? 128 : 96;
   static constexpr int kFinal = 2;  // order of the blocks the iteration leaves
   struct Refl { T tau, w1, w2, tl; };  // tau + tl = 2 / v^T v
-  struct Shift { T tr, det; };  // sum and product of a shift pair
+  // Shift pair: the eigenvalues of [[a, b], [c, d]].  Its sum and product would do,
+  // but next to a diagonal that agrees with them to half the digits (a cluster, a
+  // defective eigenvalue) the first column below would be their rounding.
+  struct Shift { T a, d, bc; };
   __host__ __device__ static int64_t ldim(int n) { return n; }
   __device__ static E load(const T* p, int64_t) { return p[0]; }
   __device__ static void store(T* p, int64_t, E v) { p[0] = v; }
@@ -167,8 +170,9 @@ struct RealRoute {
   __device__ static void intro(const E* h, int ldh, int l, Shift sh, E (&x)[3]) {
     const T h00 = h[l + l * ldh], h10 = h[l + 1 + l * ldh], h01 = h[l + (l + 1) * ldh];
     const T h11 = h[l + 1 + (l + 1) * ldh], h21 = h[l + 2 + (l + 1) * ldh];
-    x[0] = h00 * h00 + h01 * h10 - sh.tr * h00 + sh.det;
-    x[1] = h10 * (h00 + h11 - sh.tr);
+    const T p = h00 - sh.a, q = h00 - sh.d;
+    x[0] = p * q - sh.bc + h01 * h10;
+    x[1] = h10 * (p + (h11 - sh.d));
     x[2] = h10 * h21;
   }
   __device__ static void rows(Refl f, E (&y)[3]) {
@@ -180,7 +184,7 @@ struct RealRoute {
   }
   __device__ static void cols(Refl f, E (&y)[3]) { rows(f, y); }
   // shift pair q from the q-th trailing 2 x 2 block [[a, b], [c, d]]
-  __device__ static Shift shift(int, E a, E b, E c, E d) { return {a + d, a * d - b * c}; }
+  __device__ static Shift shift(int, E a, E b, E c, E d) { return {a, d, b * c}; }
   // shift pairs from the quasi-triangular h of order m, the last blocks first; two
   // real eigenvalues make a pair
   __device__ static int eigen_shifts(const E* h, int ldh, int m, Shift* out) {
@@ -193,19 +197,19 @@ struct RealRoute {
         out[cnt++] = shift(0, h[k - 1 + (k - 1) * ldh], h[k - 1 + k * ldh], h[k + (k - 1) * ldh], d);
         k -= 2;
       } else {
-        if (single) out[cnt++] = {x + d, x * d};
+        if (single) out[cnt++] = {x, d, T(0)};
         single = !single;
         x = d;
         k -= 1;
       }
     }
-    if (single) out[cnt++] = {x + x, x * x};
+    if (single) out[cnt++] = {x, x, T(0)};
     return cnt;
   }
   __device__ static int shift_block(int q) { return q; }
   __device__ static Shift exceptional(int q, E d, T e) {
     const T re = d + (q % 2 ? -e : e) * T(0.75) * T(1 + q % 3), im = T(0.5) * e;
-    return {T(2) * re, re * re + im * im};
+    return {re, re, -im * im};
   }
   // bulges of an in-LDS sweep / of a batch on an active block of order m
   __host__ __device__ static int small_bulges(int m) { return m / 6 < 1 ? 1 : (m / 6 > kNb ? kNb : m / 6); }
@@ -1085,7 +1089,7 @@ bool schur_qr(hipStream_t st, int n, typename A::T* H, typename A::T* Z, HseqrWo
   // two neighbouring finished ranges together have more than W rows
   const int max_ranges = 2 * n / W + 2;
   T* U = w.U.ensure<T>(std::max(max_ranges, kMaxChains) * u_elems<A>());
-  T* shifts = w.shifts.ensure<T>(2 * kMaxChains * kNb);
+  T* shifts = w.shifts.ensure<T>(sizeof(typename A::Shift) / sizeof(T) * kMaxChains * kNb);
   int* flag = w.flag.ensure<int>(8);  // [0] status, [4..6] the scan's result
   int* list = w.scratch.ensure<int>(2 * max_ranges);
   MSQRT_HIP(hipMemsetAsync(flag, 0, sizeof(int) * 8, st));

@@ -37,3 +37,17 @@ def test_orthogonal_and_permutation(prec, n):
     _root(3.0 * np.eye(n) + q, prec)
     _root(3.0 * np.eye(n) + np.eye(n)[r.permutation(n)], prec)
     _root(3.0 * np.eye(n) + np.kron(np.roll(np.eye(n // 4 + 1), 1, axis=0), np.eye(4))[:n, :n], prec)
+
+
+@pytest.mark.parametrize("prec", ["fp32", "fp64"])
+@pytest.mark.parametrize("n", [8, 20, 70, 130, 257, 600])
+def test_clusters_and_defective_eigenvalues(prec, n):
+    """Four eigenvalues n / 4 times each, coupled by 1e-6, and sparse couplings on a
+    multiple of the identity (nilpotent parts): converging blocks agree with their
+    shifts to half the digits."""
+    r = np.random.default_rng(n)
+    print(f"[qr convergence] clusters {prec} n={n}", flush=True)
+    q, _ = np.linalg.qr(r.standard_normal((n, n)))
+    g = r.standard_normal((n, n)) / np.sqrt(n)
+    _root(q @ (np.diag(np.repeat([1.0, 2.0, 5.0, 9.0], n)[::4][:n]) + 1e-6 * np.triu(g, 1)) @ q.T, prec)
+    _root(3.0 * np.eye(n) + (r.random((n, n)) < 2.5 / n) * r.standard_normal((n, n)) * 0.5, prec)
