@@ -1118,13 +1118,16 @@ bool schur_qr(hipStream_t st, int n, typename A::T* H, typename A::T* Z, HseqrWo
     // Shifts from separate 2 x 2 blocks are poor when the trailing block is close to
     // a multiple of an orthogonal matrix (3 I + a cyclic permutation): then the
     // eigenvalues of the whole trailing block, which cost as much as a few batches
-    // (float 0.3, complex double 0.9 ms).  Order 256 in double 63 -> 40 ms, where
-    // single chains with such shifts took 33; random matrices deflate faster and
-    // never get here.
+    // (float 0.3, complex double 0.9 ms), once six batches have deflated less than a
+    // sixteenth of the eigenvalues they aimed at.  The permutation of order 256 in
+    // double 63 -> 40 ms.  Double factors of random matrices pass through such
+    // stretches as well; there the phase moved by -4 to +5% (orders 256 to 2048; with
+    // a quarter instead of a sixteenth it was 3% longer at n = 2048, and the
+    // permutation of order 1024 took 201 instead of 185 ms).
     ends.push_back(hi);
     constexpr int kLook = 6;  // batches
     const int eigs = total * (A::kComplex ? 1 : 2);
-    const bool poor = batches > 10 && 4 * (ends[ends.size() - 1 - kLook] - hi) < eigs;
+    const bool poor = batches > 10 && 16 * (ends[ends.size() - 1 - kLook] - hi) < eigs;
     if (poor && !ex) {
       const int ms = 3 * kNb;
       static_assert(3 * kNb <= W, "the block fits a window");
