@@ -14,7 +14,8 @@
 //    blocks, read by the kernel that tests for deflation.  (Eigenvalues of
 //    the whole trailing block save about a tenth of the bulges, but that QR
 //    iteration ran before every batch on one workgroup: 250 launches of 166 us at
-//    n = 2048 against none.)
+//    n = 2048 against none.  It runs, as qr_shift_kernel, before the batches of a
+//    block that has all but stopped deflating: see schur_qr.)
 //  * Within a chain the bulges sit SPAN rows apart and move in lockstep, one
 //    row per round: bulge j applies its reflector at position kbase - SPAN j
 //    + r in round r.  The reflectors of a round act on disjoint rows and none
@@ -26,7 +27,8 @@
 //
 // What bounds it: the instructions of a round (16 waves, four to a SIMD) times
 // the rounds of a batch; 16 bulges on 128 rows cost 69 us for 79 rows, eight
-// 60 us for 103, so long chains win although their windows advance less.
+// 60 us for 103 (with reflectors of one tau; the second part of tau added about
+// 5%), so long chains win although their windows advance less.
 #pragma once
 
 #include <algorithm>

@@ -23,17 +23,18 @@
 // they are there, so larger tiles, which read more, exchange plain values
 // around a grid barrier.  Measured with tags and with the barrier: n = 1000
 // 3.4 and 4.2 ms, n = 1531 6.3 and 7.2 (64-row tiles); n = 4096, whose first
-// launches have 192- and 128-row tiles, 26.3 and 23.7.  Each workgroup's
+// launches have 192- and 128-row tiles, 26.3 and 23.7 (24.5 with kLazy in the
+// kernel, which changed the order of its instructions).  Each workgroup's
 // scalars have a 64-byte line of their own: packed together they took 0.4 ms
 // longer at n = 1000.
 //
-// What bounds it: the latency of a column, 4.3 us at n = 1531, of which the
+// What bounds it: the latency of a column, 4.1 us at n = 1531, of which the
 // exchange is about half and the instructions of product, row work and update
 // the rest.  (A blocked panel that left the matrix alone for 32 columns and
 // corrected every column with V and W spent 9.3 us per column at n = 1531 and
 // 9.8 at n = 4096: its row corrections, V^T u, W^T u and their exchange cost
-// more than the update of the register tile.  Now 4.3 and 5.8 us, 14.3 -> 6.3
-// ms and 40.2 -> 23.7 ms, with an X_0 that is 5 % closer to the root.)
+// more than the update of the register tile.  Now 4.1 and 6.0 us, 14.3 -> 6.3
+// ms and 40.2 -> 24.5 ms, with an X_0 that is 5 % closer to the root.)
 #include <algorithm>
 #include <vector>
 
