@@ -63,6 +63,9 @@ msqrt_status msqrt_test_schur(msqrt_prec prec, int64_t n, const double* A, doubl
  * that maps (in[0] + i in[1], in[2] + i in[3]) likewise: c, Re s, Im s, h. */
 msqrt_status msqrt_test_qr_step(msqrt_prec prec, int cplx, int64_t nv, const double* in, double* out);
 
+/* The multiple of e_1 that the real reflector maps in[0..2] to, one double each. */
+msqrt_status msqrt_test_qr_beta(msqrt_prec prec, int64_t nv, const double* in, double* out);
+
 /* Principal square root S of the upper triangular T (Eq. (subst), blocked);
  * NO_PRINCIPAL if a diagonal entry lies on or next to R<=0. */
 msqrt_status msqrt_test_trsqrt(msqrt_prec prec, int64_t n, const double* T, double* S);

@@ -327,6 +327,16 @@ def test_qr_step(x, cplx, prec="fp32"):
     return out
 
 
+def test_qr_beta(x, prec="fp32"):
+    """Test hook: beta of the QR's reflectors for the rows of x (nv x 4, three used)."""
+    import numpy as np
+    x = np.ascontiguousarray(x, np.float64)
+    out = np.zeros(x.shape[0])
+    check(lib().msqrt_test_qr_beta(_lib.PREC_NAMES[prec], x.shape[0], _dp(x), _dp(out)),
+          "msqrt_test_qr_beta")
+    return out
+
+
 def test_trsqrt(t, prec="fp32"):
     """Test hook: principal square root of an upper triangular matrix."""
     import numpy as np

@@ -34,7 +34,8 @@ EXPORTED = [
     "msqrt_release_cached",
     "msqrt_factor_wrap", "msqrt_factor_export", "msqrt_test_sytrd", "msqrt_test_sy2tr",
     "msqrt_test_sytrd_tag", "msqrt_test_sytrd_exchange", "msqrt_test_stedc",
-    "msqrt_test_gehrd", "msqrt_test_schur", "msqrt_test_qr_step", "msqrt_test_trsqrt", "msqrt_test_trsyl",
+    "msqrt_test_gehrd", "msqrt_test_schur", "msqrt_test_qr_step", "msqrt_test_qr_beta",
+    "msqrt_test_trsqrt", "msqrt_test_trsyl",
     "msqrt_test_trcbrt", "msqrt_rootm",
     "msqrt_test_gemm_f32", "msqrt_test_gemm_f64", "msqrt_test_split_tile", "msqrt_test_tile_occupancy",
     "msqrt_test_syrk", "msqrt_features", "msqrt_mlp_forward", "msqrt_mlp_grad",
@@ -139,6 +140,7 @@ def lib():
     L.msqrt_test_gehrd.argtypes = [ci, i64, dp, dp, dp]
     L.msqrt_test_schur.argtypes = [ci, i64, dp, dp, dp]
     L.msqrt_test_qr_step.argtypes = [ci, ci, i64, dp, dp]
+    L.msqrt_test_qr_beta.argtypes = [ci, i64, dp, dp]
     L.msqrt_test_trsqrt.argtypes = [ci, i64, dp, dp]
     L.msqrt_test_trcbrt.argtypes = [ci, i64, dp, dp]
     L.msqrt_rootm.argtypes = [ctypes.POINTER(Options), ci, ci, i64, vp, i64, vp, i64, vp,
@@ -166,7 +168,7 @@ def lib():
                  "msqrt_sqrtm_backward",
                  "msqrt_factor_wrap", "msqrt_factor_export", "msqrt_test_sytrd",
                  "msqrt_test_stedc", "msqrt_test_gehrd", "msqrt_test_schur", "msqrt_test_qr_step",
-                 "msqrt_test_trsqrt",
+                 "msqrt_test_qr_beta", "msqrt_test_trsqrt",
                  "msqrt_test_trcbrt", "msqrt_rootm",
                  "msqrt_test_trsyl", "msqrt_test_gemm_f32", "msqrt_test_gemm_f64", "msqrt_test_syrk", "msqrt_features",
                  "msqrt_mlp_forward", "msqrt_mlp_grad", "msqrt_mlp_adam", "msqrt_selector_set",

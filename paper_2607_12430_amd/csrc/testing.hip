@@ -98,6 +98,29 @@ __global__ void qr_step_kernel(int nv, int cplx, const double* in, double* out) 
 }
 
 template <typename T>
+__global__ void qr_beta_kernel(int nv, const double* in, double* out) {
+  const int i = blockIdx.x * blockDim.x + threadIdx.x;
+  if (i >= nv) return;
+  const double* x = in + 4 * (int64_t)i;
+  const T v[3] = {(T)x[0], (T)x[1], (T)x[2]};
+  T beta;
+  qr::RealRoute<T>::make(v, beta);
+  out[i] = beta;
+}
+
+template <typename T>
+msqrt_status qr_beta_impl(int nv, const double* in, double* out) {
+  DevBuf ib, ob;
+  double* di = upload(ib, std::vector<double>(in, in + 4 * (size_t)nv));
+  double* dout = ob.ensure<double>(nv);
+  hipLaunchKernelGGL(qr_beta_kernel<T>, dim3((unsigned)ceil_div(nv, 256)), dim3(256), 0, nullptr, nv, di, dout);
+  MSQRT_LAUNCH_CHECK();
+  MSQRT_HIP(hipDeviceSynchronize());
+  MSQRT_HIP(hipMemcpy(out, dout, sizeof(double) * (size_t)nv, hipMemcpyDeviceToHost));
+  return MSQRT_OK;
+}
+
+template <typename T>
 msqrt_status qr_step_impl(int nv, int cplx, const double* in, double* out) {
   DevBuf ib, ob;
   double* di = upload(ib, std::vector<double>(in, in + 4 * (size_t)nv));
@@ -196,6 +219,15 @@ extern "C" msqrt_status msqrt_test_schur(msqrt_prec prec, int64_t n, const doubl
   return guarded([&] {
     if (prec == MSQRT_PREC_FP64) return gehrd_impl<double>((int)n, A, T, Q, true);
     if (prec == MSQRT_PREC_FP32) return gehrd_impl<float>((int)n, A, T, Q, true);
+    return MSQRT_ERR_INVALID_ARG;
+  });
+}
+
+extern "C" msqrt_status msqrt_test_qr_beta(msqrt_prec prec, int64_t nv, const double* in, double* out) {
+  if (nv < 1 || !in || !out || nv > (1 << 24)) return MSQRT_ERR_INVALID_ARG;
+  return guarded([&] {
+    if (prec == MSQRT_PREC_FP64) return qr_beta_impl<double>((int)nv, in, out);
+    if (prec == MSQRT_PREC_FP32) return qr_beta_impl<float>((int)nv, in, out);
     return MSQRT_ERR_INVALID_ARG;
   });
 }
